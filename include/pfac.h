@@ -374,6 +374,20 @@ int ac_probe_read(const uint8_t *d_buf, int64_t n, uint32_t *d_out, hipStream_t 
  *                                          {-1, first child, child count, 0} otherwise;
  *                                          bit 31 of the last field set when a keyword
  *                                          ends at the state
+ *   AC_TABLE_WINDOW2_KEYS, AC_TABLE_WINDOW4_KEYS  uint32[slots], slots a power of two:
+ *                          exact table of the 4-byte windows (little-endian) at
+ *                          keyword positions 1 .. 2 and 1 .. 4 in buckets of 4
+ *                          (empty when a keyword has fewer than stride + 4 bytes);
+ *                          window x lies in bucket b1 = x * 0x9E3779B1 >> (32 - nb)
+ *                          or b2 = (x ^ x >> 15) * 0x85EBCA77 >> (32 - nb), nb =
+ *                          log2(slots) - 2 (b1 ^ 1 if both agree)
+ *   AC_TABLE_WINDOW2_ENTRIES, AC_TABLE_WINDOW4_ENTRIES  int32[4*(slots + extra)]: per
+ *                          slot, then per further path through the same window,
+ *                          {keyword-byte position of the path's start, bytes to
+ *                          compare from there, keyword id or state, window position
+ *                          | general << 3 | (next entry + 1) << 4}; general: the
+ *                          compared path ends at that state and the walk goes on,
+ *                          else it is that whole keyword (length 0: empty slot)
  *   AC_TABLE_FILTER_BASE + k   filter map of kind k = AC_FILTER_* (stride 1),
  *                              k = 6 + AC_FILTER_* (stride 2, may be empty),
  *                              k = 12 + AC_FILTER_* (stride 4, may be empty);
@@ -397,6 +411,10 @@ int ac_probe_read(const uint8_t *d_buf, int64_t n, uint32_t *d_out, hipStream_t 
 #define AC_TABLE_PREFIX     8
 #define AC_TABLE_TAIL       9
 #define AC_TABLE_TAIL_INFO  10
+#define AC_TABLE_WINDOW2_KEYS    11
+#define AC_TABLE_WINDOW2_ENTRIES 12
+#define AC_TABLE_WINDOW4_KEYS    13
+#define AC_TABLE_WINDOW4_ENTRIES 14
 #define AC_TABLE_FILTER_BASE 100
 
 int ac_compile(const uint8_t *bytes, const int64_t *offsets, int32_t n_patterns,

@@ -17,6 +17,8 @@ AC_FILTER_PAIR20 = 6
 AC_TABLE_CLASS_MAP, AC_TABLE_DENSE, AC_TABLE_NODE, AC_TABLE_LABEL = 1, 2, 3, 4
 AC_TABLE_OUT_OFF, AC_TABLE_OUT_PID, AC_TABLE_DEPTH, AC_TABLE_FILTER_BASE = 5, 6, 7, 100
 AC_TABLE_PREFIX, AC_TABLE_TAIL, AC_TABLE_TAIL_INFO = 8, 9, 10
+AC_TABLE_WINDOW2_KEYS, AC_TABLE_WINDOW2_ENTRIES = 11, 12
+AC_TABLE_WINDOW4_KEYS, AC_TABLE_WINDOW4_ENTRIES = 13, 14
 
 # every symbol include/pfac.h declares
 EXPORTS = [

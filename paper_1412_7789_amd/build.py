@@ -16,7 +16,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libpfac.so")
 # the filtered kernels of each stride compile in their own unit, in parallel
 SOURCES = ["filtered_s1k1.hip", "filtered_s1k2.hip", "filtered_s1k3.hip", "filtered_s2.hip", "filtered_s4.hip",
-           "kernels.hip", "plan.cpp", "capi.cpp", "serve.cpp", "host_match.cpp"]
+           "filtered_s2w.hip", "filtered_s4w.hip", "kernels.hip", "plan.cpp", "capi.cpp", "serve.cpp", "host_match.cpp"]
 ARCH = os.environ.get("PFAC_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [

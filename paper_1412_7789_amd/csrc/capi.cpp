@@ -180,6 +180,7 @@ int upload(ac_automaton *a) {
     Sec tinfo{P.tailinfo.data(), int64_t(P.tailinfo.size()) * 4, 0};
     Sec kwb{P.kw_bytes.data(), int64_t(P.kw_bytes.size()), 0};
     Sec kwo{P.kw_off.data(), int64_t(P.kw_off.size()) * 4, 0};
+    Sec wkey[2], went[2];
     int64_t at = 0;
     auto place = [&](Sec &s) { s.at = at; at += pad256(std::max<int64_t>(s.bytes, 1)); };
     place(cls);
@@ -189,11 +190,17 @@ int upload(ac_automaton *a) {
     }
     place(dense); place(node); place(label); place(ooff); place(opid);
     place(ptab); place(tail); place(tinfo); place(kwb); place(kwo);
+    for (int k = 0; k < 2; ++k) {
+        wkey[k] = Sec{P.win[k].keys.data(), int64_t(P.win[k].keys.size()) * 4, 0};
+        went[k] = Sec{P.win[k].entries.data(), int64_t(P.win[k].entries.size() * sizeof(WindowEntry)), 0};
+        place(wkey[k]); place(went[k]);
+    }
     a->dbytes = at;
     std::vector<uint8_t> staging(size_t(at), 0);
     auto copy = [&](const Sec &s) { if (s.bytes) std::memcpy(staging.data() + s.at, s.src, size_t(s.bytes)); };
     copy(cls); for (auto &f : filt) copy(f); copy(dense); copy(node); copy(label); copy(ooff); copy(opid);
     copy(ptab); copy(tail); copy(tinfo); copy(kwb); copy(kwo);
+    for (int k = 0; k < 2; ++k) { copy(wkey[k]); copy(went[k]); }
     e = hipMalloc(&a->dmem, size_t(at));
     if (e != hipSuccess) { a->dmem = nullptr; return fail(AC_ENOMEM, std::string("hipMalloc(automaton): ") + hipGetErrorString(e)); }
     e = hipMemcpy(a->dmem, staging.data(), size_t(at), hipMemcpyHostToDevice);
@@ -202,6 +209,11 @@ int upload(ac_automaton *a) {
     DevAut &D = a->dev;
     D.cls = b + cls.at;
     for (int k = 0; k < kNumFilters; ++k) a->dfilter[k] = b + filt[k].at;
+    for (int k = 0; k < 2; ++k) {
+        if (P.win[k].bits == 0) continue;
+        a->dwin_keys[k] = reinterpret_cast<const uint32_t *>(b + wkey[k].at);
+        a->dwin_entries[k] = reinterpret_cast<const WindowEntry *>(b + went[k].at);
+    }
     D.dense = reinterpret_cast<const int32_t *>(b + dense.at);
     D.node = reinterpret_cast<const int32_t *>(b + node.at);
     D.label = b + label.at;
@@ -240,7 +252,9 @@ void fill_info(const Plan &P, ac_info_t *o) {
     o->tail_bytes = int64_t(P.tail.size() + P.tailinfo.size()) * 4 + int64_t(P.kw_bytes.size()) +
                     int64_t(P.kw_off.size()) * 4;
     for (const auto &f : P.filter) o->filter_bytes += int64_t(f.size());
-    o->device_bytes = 256 + o->dense_bytes + o->compact_bytes + o->output_bytes + o->filter_bytes +
+    int64_t window_bytes = 0;
+    for (const auto &w : P.win) window_bytes += int64_t(w.keys.size() * 4 + w.entries.size() * sizeof(WindowEntry));
+    o->device_bytes = 256 + window_bytes + o->dense_bytes + o->compact_bytes + o->output_bytes + o->filter_bytes +
                       o->prefix_table_bytes + o->tail_bytes;
     o->build_ms = P.build_ms;
 }
@@ -930,6 +944,14 @@ int64_t ac_plan_export(const ac_plan *p, int32_t table, void *dst, int64_t dst_b
         case AC_TABLE_PREFIX: src = P.ptab.data(); bytes = int64_t(P.ptab.size()) * 4; break;
         case AC_TABLE_TAIL: src = P.tail.data(); bytes = int64_t(P.tail.size()) * 4; break;
         case AC_TABLE_TAIL_INFO: src = P.tailinfo.data(); bytes = int64_t(P.tailinfo.size()) * 4; break;
+        case AC_TABLE_WINDOW2_KEYS: case AC_TABLE_WINDOW4_KEYS: {
+            const auto &k = P.win[table == AC_TABLE_WINDOW4_KEYS].keys;
+            src = k.data(); bytes = int64_t(k.size()) * 4; break;
+        }
+        case AC_TABLE_WINDOW2_ENTRIES: case AC_TABLE_WINDOW4_ENTRIES: {
+            const auto &e = P.win[table == AC_TABLE_WINDOW4_ENTRIES].entries;
+            src = e.data(); bytes = int64_t(e.size() * sizeof(WindowEntry)); break;
+        }
         default:
             if (table > AC_TABLE_FILTER_BASE && table <= AC_TABLE_FILTER_BASE + kNumFilters) {
                 const auto &f = P.filter[table - AC_TABLE_FILTER_BASE - 1];

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "pfac_internal.hpp"
 
@@ -20,6 +21,8 @@ constexpr int kQueueCap = 256;   // per-wave candidate queue (entries)
 // for the next chunk's loads also waits for them, and the data registers a
 // store reads cannot be reused until it is done), so records stay on chip.
 constexpr int kLdsHits = 64;
+// the same with the window table, whose records are half as large
+constexpr int kLdsWinHits = 2 * kLdsHits;
 constexpr int kDrain = 64;       // candidates taken per drain (1 per lane; 128 and 192 measured slower)
 // A queue holds fewer than kDrain entries before a push round and gains at
 // most one per lane in it, so its last entries are never used by the queue:
@@ -62,6 +65,7 @@ constexpr int kBufferFlags = 0x00020000;
 // of a by-value struct otherwise lower to flat loads, which also occupy the
 // LDS counter and would serialise with the filter lookups.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(1))) u32x4 global_u32x4;
 typedef const __attribute__((address_space(1))) uint32_t global_u32;
 
@@ -77,6 +81,17 @@ __device__ __forceinline__ void gstore16(uint4 *p, uint32_t a, uint32_t b, uint3
     v.z = c;
     v.w = d;
     *(__attribute__((address_space(1))) u32x4 *)(p) = v;
+}
+
+__device__ __forceinline__ void gstore8(uint2 *p, uint32_t a, uint32_t b) {
+    u32x2 v;
+    v.x = a;
+    v.y = b;
+    *(__attribute__((address_space(1))) u32x2 *)(p) = v;
+}
+__device__ __forceinline__ uint2 gload8(const uint2 *p) {
+    const u32x2 v = *(const __attribute__((address_space(1))) u32x2 *)(p);
+    return make_uint2(v.x, v.y);
 }
 
 // Orders LDS traffic between lanes of one wave (queue producer -> consumer).
@@ -342,8 +357,8 @@ __device__ __forceinline__ int find_byte16(u32x4 v, int n, uint32_t b) {
     return at < n ? at : -1;
 }
 
-// The rest of the walk from offset o (relative to the scanned buffer) once
-// the exact prefix table gave e = {state at depth K | final bit}.  Each step
+// The walk from offset o (relative to the scanned buffer) below a state s of
+// depth d0 whose path is known to match.  Each step
 // reads the state's 16-byte walk record (tail info): whether a keyword ends
 // there, and either a forced path (a unary chain to a leaf with no keyword
 // ending in between, whose leaf keyword is then compared with the text
@@ -354,18 +369,17 @@ __device__ __forceinline__ int find_byte16(u32x4 v, int n, uint32_t b) {
 // state's children are consecutive states with sorted edge labels, found
 // among up to 16 labels read in one load.  The walk never compares or steps
 // past `end` (the end of o's text).  With REC, rb holds the 8 text bytes
-// that follow the prefix (as captured by the streaming kernel), which pick
-// the first transitions without waiting for a load; the 32 bytes after the
-// prefix are loaded at the start, beside the first record, and serve the
-// first compare and the next transitions.  Every keyword starting at o is
-// reported, through ids(state) for all keyword ids of a final state or
-// one(pid) for a single id.
+// after depth d0 (as captured by the streaming kernel), which pick
+// the first transitions without waiting for a load; the 32 bytes after it
+// are loaded at the start, beside the first record, and serve the
+// first compare and the next transitions.  Every keyword starting at o and
+// ending at s or below is reported, through ids(state) for all keyword ids of
+// a final state or one(pid) for a single id.
 template <bool REC, typename Ids, typename One>
-__device__ __forceinline__ void walk_rest(const DevAut &A, const ScanArgs &S, int64_t o, int64_t end, uint32_t e,
-                                          uint2 rb, Ids &&ids, One &&one) {
-    const int K = A.K;
-    if (o + K > end) return;          // the prefix ran into the next text of a batch
-    // The 32 text bytes after the prefix, loaded beside the first walk
+__device__ __forceinline__ void walk_below(const DevAut &A, const ScanArgs &S, int64_t o, int64_t end, int32_t s,
+                                           int d0, uint2 rb, Ids &&ids, One &&one) {
+    if (o + d0 > end) return;         // the path ran into the next text of a batch
+    // The 32 text bytes after the path, loaded beside the first walk
     // record: most walks compare them with a forced path's keyword and read
     // no other text.
     const uintptr_t tend = reinterpret_cast<uintptr_t>(S.text) + uintptr_t(S.n);
@@ -375,12 +389,12 @@ __device__ __forceinline__ void walk_rest(const DevAut &A, const ScanArgs &S, in
         return reinterpret_cast<uintptr_t>(p) + 16u <= tend ? load16_any(p) : load16_clamped(p, tlast);
     };
     u32x4 t0 = {0u, 0u, 0u, 0u}, t1 = t0;
-    if (o + K < end) {
-        t0 = text16(o + K);
-        if (o + K + 16 < S.n) t1 = text16(o + K + 16);
+    if (o + d0 < end) {
+        t0 = text16(o + d0);
+        if (o + d0 + 16 < S.n) t1 = text16(o + d0 + 16);
     }
-    auto byte_at = [&](int64_t j) -> uint32_t {   // text byte j (o + K <= j < end)
-        const int64_t r = j - o - K;
+    auto byte_at = [&](int64_t j) -> uint32_t {   // text byte j (o + d0 <= j < end)
+        const int64_t r = j - o - d0;
         if (REC && r < 8) return r < 4 ? (rb.x >> (8 * r)) & 0xFFu : (rb.y >> (8 * (r - 4))) & 0xFFu;
         if (r < 32) {
             const u32x4 t = r < 16 ? t0 : t1;
@@ -391,16 +405,15 @@ __device__ __forceinline__ void walk_rest(const DevAut &A, const ScanArgs &S, in
         return gload1(S.text + j);
     };
     // whether text bytes o + dd .. o + dd + z equal keyword bytes kw[0 .. z):
-    // from the preloaded bytes while the walk is still at the prefix
+    // from the preloaded bytes while the walk is still at its first state
     auto same = [&](int64_t dd, const uint8_t *kw, int32_t z) -> bool {
-        if (dd == K && z <= 32) {
+        if (dd == d0 && z <= 32) {
             const u32x4 k0 = load16_any(kw), k1 = load16_any(kw + 16);
             return (diff16(t0, k0, z) | diff16(t1, k1, z - 16)) == 0u;
         }
         return equal_bytes(S.text + o + dd, kw, z, S.text, S.n);
     };
-    int32_t s = int32_t(e & kStateMask);
-    int64_t d = K;
+    int64_t d = d0;
     while (true) {
         const int4 ti = A.tailinfo[s];
         const bool has_byte = o + d < end;
@@ -453,6 +466,61 @@ __device__ __forceinline__ void walk_rest(const DevAut &A, const ScanArgs &S, in
     }
 }
 
+// The rest of the walk from offset o once the exact prefix table gave e =
+// {state at depth K | final bit}.
+template <bool REC, typename Ids, typename One>
+__device__ __forceinline__ void walk_rest(const DevAut &A, const ScanArgs &S, int64_t o, int64_t end, uint32_t e,
+                                          uint2 rb, Ids &&ids, One &&one) {
+    walk_below<REC>(A, S, o, end, int32_t(e & kStateMask), A.K, rb, ids, one);
+}
+
+// Slot of the 4-byte window x in the exact window table (2^nb buckets of four
+// keys), or -1.  Both buckets, 16 bytes each, are read at once.
+template <typename LoadBucket>
+__device__ __forceinline__ int window_slot(LoadBucket load, int nb, uint32_t x) {
+    uint32_t b1, b2;
+    window_buckets(x, nb, b1, b2);
+    const u32x4 q1 = load(b1), q2 = load(b2);
+    int at = -1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (q1[i] == x) at = int(4 * b1) + i;
+        if (q2[i] == x) at = int(4 * b2) + i;
+    }
+    return at;
+}
+
+// Everything the window at offset w (found in `slot` of the window table)
+// belongs to: each of its entries fixes the offset o that the window's path
+// starts from and the bytes to compare there, either a whole keyword or the
+// path down to a state from which a walk goes on.  locate(o, tstart, end,
+// tid) gives the text holding o; ids(o - tstart, tid, state) and one(o -
+// tstart, tid, pid) report.
+template <typename Locate, typename Ids, typename One>
+__device__ __forceinline__ void walk_window(const DevAut &A, const ScanArgs &S, const int4 *entries, int slot,
+                                            int64_t w, Locate &&locate, Ids &&ids, One &&one) {
+    while (true) {
+        const int4 e = entries[slot];
+        const int64_t o = w - (e.w & 7);
+        if (o >= 0 && o + e.y <= S.n) {
+            int64_t tstart, end;
+            int32_t tid;
+            locate(o, tstart, end, tid);
+            if (o + e.y <= end && equal_bytes(S.text + o, A.kw_bytes + e.x, e.y, S.text, S.n)) {
+                if (uint32_t(e.w) & kWinGeneral)
+                    walk_below<false>(A, S, o, end, e.z, e.y, make_uint2(0u, 0u),
+                                      [&](int32_t st) { ids(o - tstart, tid, st); },
+                                      [&](int32_t pid) { one(o - tstart, tid, pid); });
+                else
+                    one(o - tstart, tid, e.z);
+            }
+        }
+        const uint32_t next = uint32_t(e.w) >> 4;
+        if (next == 0) return;
+        slot = int(next) - 1;
+    }
+}
+
 struct FilterLaunch {
     const uint8_t *base;     // text pointer rounded down to 16 bytes
     int64_t mis;             // text - base
@@ -462,7 +530,11 @@ struct FilterLaunch {
     const uint8_t *filter;   // the filter map this launch stages in LDS
     int32_t hit_cap;         // entries per wave region
     uint4 *hits;             // [waves * hit_cap]: {slot << 12 | position, prefix-table value,
-                             //  the 8 text bytes after the prefix}
+                             //  the 8 text bytes after the prefix}; with the window
+                             //  table two {slot << 12 | position, table slot} in each
+    const uint32_t *win_keys;   // exact window table (4 << win_nb keys)
+    const int4 *win_entries;
+    int32_t win_nb;             // log2(buckets)
 };
 
 // The filtered kernel's one argument.
@@ -547,13 +619,7 @@ __device__ __forceinline__ void load_partial(const FilterLaunch &F, int64_t c, u
 // rotating the word right by p (mod 32) moves the key's bit (x * mul) mod 32
 // to b.  Adding c may carry into the word index; the host sets each key's
 // bit in both words that can result.
-// PAIR (strides 2 and 4): the window at s is four bytes (the whole register
-// d[s / 4] when s is a multiple of 4), tested against the keywords' 4-byte
-// windows at positions 1 .. STRIDE: its first three bytes pick the word, and
-// the bits (x * mul) mod 32 and (byte 3) mod 32 of that word must both be set;
-// at stride 2 also bit (byte 2) mod 32, read from the next sampled window
-// (whose low bits are byte 2) at no extra extraction.
-template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, bool PAIR>
+template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL>
 __device__ __forceinline__ unsigned long long filter_chunk(const ChunkRegs<SEGS> &R, unsigned lane,
                                                            const uint8_t *sfilt, uint32_t mul) {
     constexpr uint32_t kmask = K >= 3 ? 0xFFFFFFu : ((1u << (8 * K)) - 1u);
@@ -597,19 +663,7 @@ __device__ __forceinline__ unsigned long long filter_chunk(const ChunkRegs<SEGS>
                 const int b = s - STRIDE;                 // destination bit
                 const uint32_t c = uint32_t(32 - b) & 31u;
                 const uint32_t p = hash24(x, mul) + c;
-                if (PAIR) {
-                    const uint32_t p0 = hash24(x, mul);
-                    const uint32_t w1 = fm[p0 >> shift];
-                    uint32_t v = __builtin_amdgcn_alignbit(w1, w1, p0) & __builtin_amdgcn_alignbit(w1, w1, x >> 24);
-                    if (STRIDE == 2) {
-                        // third bit: (byte 2) mod 32, the low bits of the next sampled window
-                        const int s2 = s + 2, w2 = s2 >> 2;
-                        const uint32_t x2 = s2 > 16 ? d[4] >> 16
-                                          : (s2 & 3) ? __builtin_amdgcn_alignbyte(d[w2 + 1], d[w2], 2u) : d[w2];
-                        v &= __builtin_amdgcn_alignbit(w1, w1, x2);
-                    }
-                    mj |= (v & 1u) << b;
-                } else if (BITMAP) {
+                if (BITMAP) {
                     uint32_t v;
                     if (DUAL) {
                         // two maps of 2^(FLOG2 - 3) words, independent hashes: both bits must be set
@@ -637,6 +691,65 @@ __device__ __forceinline__ unsigned long long filter_chunk(const ChunkRegs<SEGS>
     const uint32_t hi = SEGS >= 4 ? (mseg[2 % SEGS] | (mseg[3 % SEGS] << 16)) : 0u;
     return (static_cast<unsigned long long>(hi) << 32) | lo;
 }
+
+// Positive windows of the N segments from J0 on, for the strides with the
+// window table: bit i (16 / STRIDE) + t is set when the window starting at
+// STRIDE (t + 1) of the lane's 16 bytes in segment J0 + i may lie at keyword
+// positions 1 .. STRIDE.  d4[i] receives the dword after the lane's 16 bytes.
+// PAIR: the window's first three bytes pick the word, and the bits (x * mul)
+// mod 32 and (byte 3) mod 32 of that word must both be set; at stride 2 also
+// bit (byte 2) mod 32.
+// Bound by VALU issue, so the bits are moved as little as possible: each test
+// shifts the word right so that its bit becomes bit 0 (a shift amount taken
+// from a byte of x is an operand select, not an instruction), and one
+// alignbit per window shifts the result into the mask: 8 instructions per
+// window at stride 2 with the window's extraction apart, 7 at stride 4, where
+// masking each result and shifting it into place took 10 and 8.
+template <bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, bool PAIR, int J0, int N>
+__device__ __forceinline__ uint32_t filter_windows(const ChunkRegs<SEGS> &R, unsigned lane, const uint8_t *sfilt,
+                                                   uint32_t mul, uint32_t (&d4)[N]) {
+    constexpr int shift = BITMAP ? 32 - (FLOG2 - 2) : 32 - FLOG2;
+    constexpr int kWin = 16 / STRIDE;
+    static_assert(N * kWin <= 32, "one mask word");
+    const uint32_t *fm = reinterpret_cast<const uint32_t *>(sfilt);
+    uint32_t acc = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int j = J0 + i;
+        const uint32_t from_next_lane = __builtin_amdgcn_ds_bpermute(int((lane + 1) * 4), int(R.d[j][0]));
+        const uint32_t from_next_seg = (j + 1 < SEGS) ? __builtin_amdgcn_readlane(R.d[(j + 1) % SEGS][0], 0)
+                                                      : R.tail;
+        d4[i] = lane == 63 ? from_next_seg : from_next_lane;
+        const uint32_t d[5] = {R.d[j][0], R.d[j][1], R.d[j][2], R.d[j][3], d4[i]};
+#pragma unroll
+        for (int s = STRIDE; s <= 16; s += STRIDE) {
+            const int w = s >> 2, r = s & 3;
+            const uint32_t x = r == 0 ? d[w] : __builtin_amdgcn_alignbyte(d[w + 1], d[w], uint32_t(r));
+            const uint32_t p = hash24(x, mul);
+            uint32_t v;
+            if (PAIR) {
+                const uint32_t w1 = fm[p >> shift];
+                v = (w1 >> (p & 31u)) & (w1 >> ((x >> 24) & 31u));
+                if (STRIDE == 2) v &= w1 >> ((x >> 16) & 31u);
+            } else if (DUAL) {
+                const uint32_t p2 = hash24(x, kFilterMul2);
+                v = (fm[p >> (shift + 1)] >> (p & 31u)) &
+                    (fm[(1u << (FLOG2 - 3)) + (p2 >> (shift + 1))] >> (p2 & 31u));
+            } else if (BITMAP) {
+                v = fm[p >> shift] >> (p & 31u);
+            } else {
+                v = sfilt[p >> shift];
+            }
+            acc = __builtin_amdgcn_alignbit(v, acc, 1u);
+        }
+    }
+    return acc >> (32 - N * kWin);
+}
+
+// All ones when bit i of b is set, else 0; and the choice between two values
+// by such a mask.
+__device__ __forceinline__ uint32_t bit_mask(int b, int i) { return uint32_t(int32_t(uint32_t(b) << (31 - i)) >> 31); }
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
 
 // A condition every lane of the wave agrees on, marked as such for the
 // compiler, so that branching on it needs no exec-mask bookkeeping.  The
@@ -675,6 +788,14 @@ __device__ __forceinline__ uint2 probe_prefix(bool in_lds, const uint32_t *sptab
     }, bits, x, mul);
 }
 
+// Exact window lookup through the LDS copy of the window keys when there is
+// one, else through global memory.
+__device__ __forceinline__ int find_window(bool in_lds, const uint32_t *skeys, const uint32_t *gkeys, int nb,
+                                           uint32_t x) {
+    if (in_lds) return window_slot([&](uint32_t b) { return reinterpret_cast<const u32x4 *>(skeys)[b]; }, nb, x);
+    return window_slot([&](uint32_t b) { return gload16(reinterpret_cast<const uint8_t *>(gkeys + 4 * b)); }, nb, x);
+}
+
 // Streaming kernel of the filtered policy.
 //
 // Work is dealt out in slots: slot i of block b is interior chunk c_lo + b W
@@ -685,18 +806,36 @@ __device__ __forceinline__ uint2 probe_prefix(bool in_lds, const uint32_t *sptab
 // very different rates (the SIMDs favour older waves), and with a fixed
 // share per wave the block would wait for its slowest one.
 //
-// Candidate offsets wait in a per-wave LDS queue; a drain takes kDrain of
-// them at once (each lane loads the prefix window of kDrain / 64 candidates
-// with independent loads, then looks the prefix up in the exact prefix table)
-// and appends the surviving prefixes, with the 8 text bytes after them, to
-// the wave's hit region with plain stores.  The chunk loop has no walk,
-// atomic in global memory, call or other dependent global access.  A wave
+// Candidates wait in a per-wave LDS queue; a drain takes kDrain of them at
+// once.  The chunk loop has no walk, atomic in global memory, call or other
+// dependent global access apart from drains.
+//
+// WIN (strides 2 and 4, when every keyword has stride + 4 bytes): a queue
+// entry is a positive window and its four bytes, taken from the registers
+// that were filtered.  A drain looks the bytes up in the exact window table
+// (two 16-byte loads per lane) and keeps {position, table slot} of those that
+// are a keyword's window.  It reads no text, and a positive is one entry
+// where the offsets it stands for were STRIDE of them, each with a 16-byte
+// text read (often from memory again: the stream is non-temporal) and a
+// 64-byte prefix lookup.  The table's entry gives the walk the offset and,
+// mostly, the one keyword to compare.  Measured on MI355X against prefix
+// drains (kernel): 50000 keywords, 64 MiB 53.5 -> 30.5 us; 4096 texts, 267 MB,
+// 72.9 -> 63.5; paper lines, 671 KB, 17.9 -> 14.0; 20000 keywords, 1 GiB,
+// stride 2, 216 -> 217, and 197 with filter_windows' shorter tests; 1000
+// keywords, 1 GiB, 173 -> 171 (bound by the stream), 220.8 -> 199.6 per call
+// between other work.
+//
+// Otherwise a drain loads each candidate offset's text, looks its prefix up
+// in the exact prefix table and keeps the survivors with the 8 text bytes
+// after the prefix.
+//
+// Kept hits go to the wave's hit records (LDS, then its region).  A wave
 // whose region has no room for another drain leaves the loop and goes on in
 // a slow mode: it scans the rest of its slots one chunk at a time and walks
-// every hit as soon as the prefix table confirms it.  So does every wave with
-// the partial chunks at the text's ends.  Finally each wave (one text) or the
+// every hit as soon as a table confirms it.  So does every wave with the
+// partial chunks at the text's ends.  Finally each wave (one text) or the
 // whole block (a batch) walks the stored hits.
-template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, bool PAIR>
+template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, bool PAIR, bool WIN>
 __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     __shared__ __align__(16) uint8_t sfilt[1 << FLOG2];
     __shared__ __align__(16) uint32_t squeue[kMaxWaves * kQueueCap];
@@ -707,6 +846,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     __shared__ __align__(16) uint32_t sxtra[(2 * PT_SLOTS * 4 + kHitBytes) / 4];
     uint32_t *const sptab = sxtra;                                        // [2 * PT_SLOTS]
     uint4 *const shits = reinterpret_cast<uint4 *>(sxtra + 2 * PT_SLOTS);  // [waves * kLdsHits]
+    uint2 *const swhits = reinterpret_cast<uint2 *>(shits);               // [waves * kLdsWinHits]
     constexpr int64_t CH = int64_t(SEGS) * kSegBytes;
     constexpr int PER_LANE = kDrain / kWave;
     const int waves_per_block = int(blockDim.x) / kWave;
@@ -719,6 +859,16 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     uint32_t &snext = squeue[kQueueCap - 1];              // next slot to hand out
     int hcount = 0;                    // hits stored in this wave's region
     int qlen = 0;
+
+    // Where the streaming loop stopped: every slot from `cur` on is left to
+    // the slow mode (none if cur_ok is false), cur's candidates not yet
+    // queued in `rest` (with the window table: those of group rest_g, and the
+    // groups after it), and lane 0's `ahead` holding the slot after nxt
+    // (taken when nxt is a chunk of the text).
+    bool slow = false;
+    bool cur_ok = false;
+    uint32_t cur = 0, nxt = 0, ahead = 0;
+    unsigned long long rest = 0;
 
     // Queues the candidate offsets of mask m (chunk slot k), draining the
     // queue whenever it holds kDrain entries.  Returns false, leaving the
@@ -748,15 +898,80 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         wave_sync();
         qlen -= take;
     };
-
-    // Where the streaming loop stopped: every slot from `cur` on is left to
-    // the slow mode (none if cur_ok is false), cur's candidates not yet
-    // queued in `rest`, and lane 0's `ahead` holding the slot after nxt
-    // (taken when nxt is a chunk of the text).
-    bool slow = false;
-    bool cur_ok = false;
-    uint32_t cur = 0, nxt = 0, ahead = 0;
-    unsigned long long rest = 0;
+    // The same for windows (WIN): a queue entry also carries the window's
+    // bytes, so that looking it up reads no text.  Filters and queues a chunk
+    // in groups of at most kGroup segments (more at once spill registers),
+    // from group g0 on; on a refusal `rest` and `rest_g` tell what is left.
+    // `only` (unless all ones) replaces group g0's mask.
+    constexpr int kGroup = SEGS < 2 ? 1 : 2;
+    constexpr int kWin = 16 / STRIDE;    // windows per segment and lane
+    uint2 *wq = reinterpret_cast<uint2 *>(q);
+    int rest_g = 0;
+    auto queue_group = [&](unsigned m, const ChunkRegs<SEGS> &R, const uint32_t (&d4)[kGroup], auto j0, uint32_t k,
+                           unsigned &left, auto &&drain) __attribute__((always_inline)) {
+        if (!uniform(m != 0)) return true;
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i) {
+            constexpr int J0 = decltype(j0)::value;
+            const uint32_t (&d)[4] = R.d[J0 + i];
+            uint32_t mj = __builtin_amdgcn_ubfe(m, uint32_t(kWin * i), uint32_t(kWin));
+            while (true) {
+                if (qlen >= kDrain && !drain(kDrain)) {
+                    left = mj << (kWin * i) | (m >> (kWin * (i + 1)) << (kWin * (i + 1)));
+                    return false;
+                }
+                const unsigned long long act = __ballot(mj != 0);
+                if (act == 0) break;
+                if (mj) {
+                    const int t = __builtin_ctz(mj), b = t * STRIDE;
+                    // the window's bytes, picked without branches
+                    const uint32_t c2 = bit_mask(b, 2), c3 = bit_mask(b, 3);
+                    uint32_t x;
+                    if (STRIDE == 4) {
+                        x = pick(c3, pick(c2, d4[i], d[3]), pick(c2, d[2], d[1]));
+                    } else {
+                        const uint32_t lo = pick(c3, pick(c2, d[3], d[2]), pick(c2, d[1], d[0]));
+                        const uint32_t hi = pick(c3, pick(c2, d4[i], d[3]), pick(c2, d[2], d[1]));
+                        x = pick(bit_mask(b, 1), hi, __builtin_amdgcn_alignbyte(hi, lo, 2u));
+                    }
+                    wq[qlen + int(rank_in(act))] =
+                        make_uint2((k << 12) | uint32_t((J0 + i) * kSegBytes + int(lane) * 16 + b), x);
+                    mj &= mj - 1;
+                }
+                qlen += __popcll(act);
+            }
+        }
+        return true;
+    };
+    auto push_windows = [&](const ChunkRegs<SEGS> &R, uint32_t mul, uint32_t k, int g0, unsigned only,
+                            auto &&drain) __attribute__((always_inline)) {
+        auto group = [&](auto g) __attribute__((always_inline)) {
+            constexpr int G = decltype(g)::value;
+            if (G < g0) return true;
+            uint32_t d4[kGroup];
+            unsigned m = filter_windows<BITMAP, SEGS, FLOG2, STRIDE, DUAL, PAIR, G * kGroup, kGroup>(R, lane, sfilt, mul,
+                                                                                                   d4);
+            if (G == g0) m &= only;
+            unsigned left = 0;
+            if (queue_group(m, R, d4, std::integral_constant<int, G * kGroup>{}, k, left, drain)) return true;
+            rest = left;
+            rest_g = G;
+            return false;
+        };
+        if (!group(std::integral_constant<int, 0>{})) return false;
+        if constexpr (SEGS / kGroup > 1)
+            if (!group(std::integral_constant<int, 1>{})) return false;
+        if constexpr (SEGS / kGroup > 2)
+            if (!group(std::integral_constant<int, 2>{}) || !group(std::integral_constant<int, 3>{})) return false;
+        return true;
+    };
+    auto pop_window = [&](int take) __attribute__((always_inline)) {
+        wave_sync();
+        const uint2 e = wq[qlen - take + (int(lane) < take ? int(lane) : 0)];
+        wave_sync();
+        qlen -= take;
+        return e;
+    };
 
     // ---- set-up and streaming: the fields they read, and no others ----
     {
@@ -766,7 +981,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         const uint32_t *gptab = P1->A.ptab;
         const int ptab_bits = P1->A.ptab_bits;
         const uint32_t mul = P1->A.hash_mul;
-        const bool pt_lds = FLOG2 < 17 && ptab_bits <= 13;
+        const bool pt_lds = FLOG2 < 17 && (WIN ? F.win_nb <= 12 : ptab_bits <= 13);
         // Tables to LDS, two loads in flight per thread.  Every block reads
         // the same lines, so the blocks of one XCD (blockIdx mod 8) start at
         // different ones (n16 is a power of two).
@@ -782,7 +997,10 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             }
         };
         stage(reinterpret_cast<const uint4 *>(F.filter), reinterpret_cast<uint4 *>(sfilt), (1 << FLOG2) / 16);
-        if (pt_lds) stage(reinterpret_cast<const uint4 *>(gptab), reinterpret_cast<uint4 *>(sptab), (2 << ptab_bits) / 4);
+        if (pt_lds) {
+            if (WIN) stage(reinterpret_cast<const uint4 *>(F.win_keys), reinterpret_cast<uint4 *>(sptab), 1 << F.win_nb);
+            else stage(reinterpret_cast<const uint4 *>(gptab), reinterpret_cast<uint4 *>(sptab), (2 << ptab_bits) / 4);
+        }
         SlotMap M;
         M.bfirst = F.c_lo + int64_t(blockIdx.x) * waves_per_block;
         M.nw = nw;
@@ -842,6 +1060,25 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             return true;
         };
 
+        // The same for windows: one lookup in the exact window table.
+        uint2 *whits = reinterpret_cast<uint2 *>(hits);
+        uint2 *lwhits = swhits + wave * kLdsWinHits;
+        auto drain_windows = [&](int take) __attribute__((always_inline)) {
+            if (hcount + kDrain > kLdsWinHits + 2 * F.hit_cap) return false;
+            const uint2 e = pop_window(take);
+            int slot = -1;
+            if (int(lane) < take) slot = find_window(pt_lds, sptab, F.win_keys, F.win_nb, e.y);
+            const unsigned long long hit = __ballot(slot >= 0);
+            if (hit == 0) return true;
+            if (slot >= 0) {
+                const int at = hcount + int(rank_in(hit));
+                if (at < kLdsWinHits) lwhits[at] = make_uint2(e.x, uint32_t(slot));
+                else gstore8(whits + (at - kLdsWinHits), e.x, uint32_t(slot));
+            }
+            hcount += __popcll(hit);
+            return true;
+        };
+
         // Interior chunks, two register sets in turn so that the next chunk's
         // loads are in flight while this one is filtered.  The next chunk's
         // loads are issued unconditionally (the last step reloads its own
@@ -863,8 +1100,14 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             const bool nxt_ok = uniform(M.chunk(nxt) < c_hi);
             load_interior<SEGS>(F, M.chunk(nxt_ok ? nxt : cur), lane, into);
             if (lane == 0 && nxt_ok) ahead = atomicAdd(&snext, 1u);
-            rest = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL, PAIR>(regs, lane, sfilt, mul);
-            if (!uniform(push(rest, cur, drain_store))) { slow = true; return false; }
+            bool pushed;
+            if constexpr (WIN) {
+                pushed = push_windows(regs, mul, cur, 0, ~0u, drain_windows);
+            } else {
+                rest = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(regs, lane, sfilt, mul);
+                pushed = push(rest, cur, drain_store);
+            }
+            if (!uniform(pushed)) { slow = true; return false; }
             // slots held by a wave only grow, and so do their chunks: once
             // one is past the end, so is every later one
             cur = nxt;
@@ -876,8 +1119,12 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             if (!half(ra, rb)) break;
             if (!half(rb, ra)) break;
         }
-        while (!slow && qlen > 0)
-            if (!drain_store(imin(qlen, kDrain))) slow = true;
+        while (!slow && qlen > 0) {
+            bool done;
+            if constexpr (WIN) done = drain_windows(imin(qlen, kDrain));
+            else done = drain_store(imin(qlen, kDrain));
+            if (!done) slow = true;
+        }
     }
 
     // ---- slow mode, partial chunks, walks and output ----
@@ -890,7 +1137,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     M.nw = nw;
     M.wmask = uint32_t(waves_per_block - 1);
     M.wlog = wlog;
-    const bool pt_lds = FLOG2 < 17 && A.ptab_bits <= 13;
+    const bool pt_lds = FLOG2 < 17 && (WIN ? F.win_nb <= 12 : A.ptab_bits <= 13);
     const uint32_t mul = A.hash_mul;
     uint4 *hits = F.hits + w * F.hit_cap;
     auto offset_of = [&](uint32_t ent) __attribute__((always_inline)) {
@@ -919,45 +1166,89 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             }
             return true;
         };
-        if (slow) {
-            // the rest of cur's candidates, then cur's successors, one chunk
-            // at a time
-            (void)push(rest, cur, drain_walk);
-            uint32_t sl = nxt;
-            uint32_t after = __builtin_amdgcn_readfirstlane(ahead);
-            bool ok = cur_ok && M.chunk(sl) < F.c_hi;
-            while (ok) {
-                ChunkRegs<SEGS> r;
-                load_interior<SEGS>(F, M.chunk(sl), lane, r);
-                unsigned long long m = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL, PAIR>(r, lane, sfilt, mul);
-                (void)push(m, sl, drain_walk);
-                sl = after;
-                ok = M.chunk(sl) < F.c_hi;
-                if (ok) {
-                    uint32_t t = 0;
-                    if (lane == 0) t = atomicAdd(&snext, 1u);
-                    after = __builtin_amdgcn_readfirstlane(t);
-                }
-            }
-            while (qlen > 0) drain_walk(imin(qlen, kDrain));
-        }
-        // chunks overlapping an end of the text, [0, p0) and [p1, n_chunks),
-        // filtered with byte loads
+        auto drain_walk_windows = [&](int take) __attribute__((always_inline)) {
+            const uint2 e = pop_window(take);
+            if (int(lane) >= take) return true;
+            const int slot = find_window(pt_lds, sptab, F.win_keys, F.win_nb, e.y);
+            if (slot < 0) return true;
+            const int64_t at = (pchunk >= 0 ? pchunk : M.chunk(e.x >> 12)) * CH + int64_t(e.x & 4095u) - F.mis + STRIDE;
+            walk_window(A, S, F.win_entries, slot, at,
+                        [&](int64_t o, int64_t &ts, int64_t &te, int32_t &tid) { locate_text(S, nullptr, o, ts, te, tid); },
+                        [&](int64_t off, int32_t tid, int32_t st) { emit(A, S, off, tid, st); },
+                        [&](int64_t off, int32_t tid, int32_t pid) { emit_one(S, nullptr, off, tid, pid); });
+            return true;
+        };
+        // One loop takes what is left of slow mode's slots (cur first, with
+        // what its queueing left: its text is read again, then its
+        // successors), then the chunks overlapping an end of the text,
+        // [0, p0) and [p1, n_chunks), filtered with byte loads.  A queue that
+        // fills up is walked empty before its chunk goes on, so that the walk
+        // is in the code once.
         const int64_t p0 = lmin(F.c_lo, F.n_chunks);
         const int64_t p1 = lmax(F.c_hi, F.c_lo);
         const int64_t n_partial = p0 + (F.n_chunks - p1);
-        for (int64_t i = w; i < n_partial; i += nw) {
-            pchunk = i < p0 ? i : p1 + (i - p0);
+        auto full = [](int) __attribute__((always_inline)) { return false; };
+        uint32_t sl = cur;
+        bool ok = slow && cur_ok, first = true;
+        int64_t part = w;
+        while (ok || qlen > 0 || part < n_partial) {
             ChunkRegs<SEGS> r;
-            load_partial<SEGS>(F, pchunk, lane, r);
-            unsigned long long m = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL, PAIR>(r, lane, sfilt, mul);
-            for (int b = 0; b < SEGS * 16; ++b) {
-                // keep offsets o with 0 <= o and o + K <= n
-                const int64_t o = pchunk * CH + (b >> 4) * kSegBytes + int64_t(lane) * 16 + (b & 15) - F.mis;
-                if (o < 0 || o + K > S.n) m &= ~(1ull << b);
+            bool queued = true;       // nothing (more) of this chunk to queue
+            int g0 = 0;
+            unsigned only = ~0u;
+            unsigned long long m = 0;
+            if (ok) {
+                load_interior<SEGS>(F, M.chunk(sl), lane, r);
+                queued = false;
+                if (first) {
+                    g0 = rest_g;
+                    only = unsigned(rest);
+                }
+                if constexpr (!WIN)
+                    m = first ? rest : filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(r, lane, sfilt, mul);
+            } else if (qlen == 0) {
+                pchunk = part < p0 ? part : p1 + (part - p0);
+                load_partial<SEGS>(F, pchunk, lane, r);
+                queued = false;
+                if constexpr (!WIN) {
+                    m = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(r, lane, sfilt, mul);
+                    for (int b = 0; b < SEGS * 16; ++b) {
+                        // keep offsets o with 0 <= o and o + K <= n (a
+                        // window's walk checks the offsets it leads to)
+                        const int64_t o = pchunk * CH + (b >> 4) * kSegBytes + int64_t(lane) * 16 + (b & 15) - F.mis;
+                        if (o < 0 || o + K > S.n) m &= ~(1ull << b);
+                    }
+                }
+                part += nw;
             }
-            (void)push(m, 0, drain_walk);
-            while (qlen > 0) drain_walk(imin(qlen, kDrain));
+            first = false;
+            while (true) {
+                if (!queued) {
+                    if constexpr (WIN) {
+                        queued = push_windows(r, mul, sl, g0, only, full);
+                        g0 = rest_g;
+                        only = unsigned(rest);
+                    } else {
+                        queued = push(m, sl, full);
+                    }
+                }
+                while (qlen > 0) {
+                    if constexpr (WIN) drain_walk_windows(imin(qlen, kDrain));
+                    else drain_walk(imin(qlen, kDrain));
+                }
+                if (queued) break;
+            }
+            if (ok) {
+                sl = nxt;
+                ok = M.chunk(sl) < F.c_hi;
+                if (ok) {
+                    // the slot after it: taken by the streaming loop, or now
+                    nxt = __builtin_amdgcn_readfirstlane(ahead);
+                    uint32_t t = 0;
+                    if (lane == 0 && M.chunk(nxt) < F.c_hi) t = atomicAdd(&snext, 1u);
+                    ahead = t;
+                }
+            }
         }
     }
 
@@ -974,7 +1265,34 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         // the hit records were stored by other lanes of this wave
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         wave_sync();
-        for (int i = int(lane); i < hcount; i += kWave) {
+        // stages one match (queue entry with the match's position, keyword id)
+        auto stage_one = [&](uint32_t ent, int64_t o, int32_t pid) __attribute__((always_inline)) {
+            const uint32_t at = atomicAdd(&q[0], 1u);
+            if (at < uint32_t(kWaveStageCap)) {
+                q[2 + 2 * at] = ent;
+                q[3 + 2 * at] = uint32_t(pid);
+            } else {
+                emit_one(S, nullptr, o, 0, pid);
+            }
+        };
+        for (int i = int(lane); WIN && i < hcount; i += kWave) {
+            uint2 rec;
+            if (i < kLdsWinHits) rec = swhits[wave * kLdsWinHits + i];
+            else rec = gload8(reinterpret_cast<const uint2 *>(hits) + (i - kLdsWinHits));
+            const int64_t first = offset_of(rec.x);     // the window's first candidate
+            // a match at o = first .. first + STRIDE - 1 has the entry's
+            // position moved by as much (it stays below 4096)
+            auto put = [&](int64_t o, int32_t pid) __attribute__((always_inline)) {
+                stage_one(rec.x + uint32_t(o - first), o, pid);
+            };
+            walk_window(A, S, F.win_entries, int(rec.y), first + STRIDE,
+                        [&](int64_t, int64_t &ts, int64_t &te, int32_t &tid) { ts = 0; te = S.n; tid = 0; },
+                        [&](int64_t o, int32_t, int32_t st) {
+                            for (int32_t k = A.out_off[st], k1 = A.out_off[st + 1]; k < k1; ++k) put(o, A.out_pid[k]);
+                        },
+                        [&](int64_t o, int32_t, int32_t pid) { put(o, pid); });
+        }
+        for (int i = int(lane); !WIN && i < hcount; i += kWave) {
             uint4 rec;
             if (i < kLdsHits) {
                 rec = shits[wave * kLdsHits + i];
@@ -983,15 +1301,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 rec = make_uint4(g.x, g.y, g.z, g.w);
             }
             const int64_t o = offset_of(rec.x);
-            auto put = [&](int32_t pid) __attribute__((always_inline)) {
-                const uint32_t at = atomicAdd(&q[0], 1u);
-                if (at < uint32_t(kWaveStageCap)) {
-                    q[2 + 2 * at] = rec.x;
-                    q[3 + 2 * at] = uint32_t(pid);
-                } else {
-                    emit_one(S, nullptr, o, 0, pid);
-                }
-            };
+            auto put = [&](int32_t pid) __attribute__((always_inline)) { stage_one(rec.x, o, pid); };
             walk_rest<true>(A, S, o, S.n, rec.y, make_uint2(rec.z, rec.w),
                             [&](int32_t st) {
                                 for (int32_t k = A.out_off[st], k1 = A.out_off[st + 1]; k < k1; ++k) put(A.out_pid[k]);
@@ -1089,6 +1399,16 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             int j = 0;
             while (wfirst[j + 1] <= i) ++j;          // wave (region) of flat index i
             const int k = i - wfirst[j];
+            if constexpr (WIN) {
+                const uint2 rec = k < kLdsWinHits
+                                      ? swhits[j * kLdsWinHits + k]
+                                      : reinterpret_cast<const uint2 *>(F.hits + (r0 + j) * F.hit_cap)[k - kLdsWinHits];
+                walk_window(A, S, F.win_entries, int(rec.y), offset_of(rec.x) + STRIDE,
+                            [&](int64_t o, int64_t &ts, int64_t &te, int32_t &tid) { locate_text(S, loff, o, ts, te, tid); },
+                            [&](int64_t off, int32_t tid, int32_t s2) { emit_staged(A, S, st, off, tid, s2); },
+                            [&](int64_t off, int32_t tid, int32_t pid) { emit_one(S, st, off, tid, pid); });
+                continue;
+            }
             const uint4 rec = k < kLdsHits ? shits[j * kLdsHits + k] : F.hits[(r0 + j) * F.hit_cap + (k - kLdsHits)];
             const int64_t o = offset_of(rec.x);
             int64_t tstart, end;
@@ -1125,27 +1445,27 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
 
 using FilteredFn = void (*)(const KArgs);
 
-template <int K, bool BM, int FLOG2, int STRIDE, bool DUAL = false, bool PAIR = false>
+template <int K, bool BM, int FLOG2, int STRIDE, bool DUAL, bool PAIR, bool WIN>
 FilteredFn pick_segs(int segs) {
     switch (segs) {
-        case 1: return filtered_kernel<K, BM, 1, FLOG2, STRIDE, DUAL, PAIR>;
-        case 2: return filtered_kernel<K, BM, 2, FLOG2, STRIDE, DUAL, PAIR>;
-        default: return filtered_kernel<K, BM, 4, FLOG2, STRIDE, DUAL, PAIR>;
+        case 1: return filtered_kernel<K, BM, 1, FLOG2, STRIDE, DUAL, PAIR, WIN>;
+        case 2: return filtered_kernel<K, BM, 2, FLOG2, STRIDE, DUAL, PAIR, WIN>;
+        default: return filtered_kernel<K, BM, 4, FLOG2, STRIDE, DUAL, PAIR, WIN>;
     }
 }
 
-template <int K, int STRIDE>
+template <int K, int STRIDE, bool WIN>
 FilteredFn pick_filter(int kind, int segs) {
     switch (kind) {
-        case AC_FILTER_BYTES17: return pick_segs<K, false, 17, STRIDE>(segs);
-        case AC_FILTER_BITS20: return pick_segs<K, true, 17, STRIDE>(segs);
-        case AC_FILTER_BYTES16: return pick_segs<K, false, 16, STRIDE>(segs);
-        case AC_FILTER_DUAL19: return pick_segs<K, true, 17, STRIDE, true>(segs);
+        case AC_FILTER_BYTES17: return pick_segs<K, false, 17, STRIDE, false, false, WIN>(segs);
+        case AC_FILTER_BITS20: return pick_segs<K, true, 17, STRIDE, false, false, WIN>(segs);
+        case AC_FILTER_BYTES16: return pick_segs<K, false, 16, STRIDE, false, false, WIN>(segs);
+        case AC_FILTER_DUAL19: return pick_segs<K, true, 17, STRIDE, true, false, WIN>(segs);
         case AC_FILTER_PAIR20:
-            // strides 2 and 4 only (resolve_launch never pairs it with stride 1)
-            if constexpr (STRIDE == 2 || STRIDE == 4) return pick_segs<K, true, 17, STRIDE, false, true>(segs);
+            // its keys are the window table's, so it always has one (strides 2 and 4)
+            if constexpr (WIN) return pick_segs<K, true, 17, STRIDE, false, true, true>(segs);
             else return nullptr;
-        default: return pick_segs<K, true, 16, STRIDE>(segs);
+        default: return pick_segs<K, true, 16, STRIDE, false, false, WIN>(segs);
     }
 }
 
@@ -1158,5 +1478,8 @@ dev::FilteredFn pick_filtered_s1k2(int kind, int segs);
 dev::FilteredFn pick_filtered_s1k3(int kind, int segs);
 dev::FilteredFn pick_filtered_s2(int kind, int segs);
 dev::FilteredFn pick_filtered_s4(int kind, int segs);
+// strides 2 and 4 with the window table
+dev::FilteredFn pick_filtered_s2w(int kind, int segs);
+dev::FilteredFn pick_filtered_s4w(int kind, int segs);
 
 }  // namespace pfac

@@ -1,8 +1,8 @@
-// Filtered-scan kernels of stride 1, prefix length 3 (see filtered.hpp).
+// Filtered-scan kernels of stride 1 and prefix length 3 (see filtered.hpp).
 #include "filtered.hpp"
 
 namespace pfac {
 
-dev::FilteredFn pick_filtered_s1k3(int kind, int segs) { return dev::pick_filter<3, 1>(kind, segs); }
+dev::FilteredFn pick_filtered_s1k3(int kind, int segs) { return dev::pick_filter<3, 1, false>(kind, segs); }
 
 }  // namespace pfac

@@ -3,6 +3,6 @@
 
 namespace pfac {
 
-dev::FilteredFn pick_filtered_s2(int kind, int segs) { return dev::pick_filter<3, 2>(kind, segs); }
+dev::FilteredFn pick_filtered_s2(int kind, int segs) { return dev::pick_filter<3, 2, false>(kind, segs); }
 
 }  // namespace pfac

@@ -3,6 +3,6 @@
 
 namespace pfac {
 
-dev::FilteredFn pick_filtered_s4(int kind, int segs) { return dev::pick_filter<3, 4>(kind, segs); }
+dev::FilteredFn pick_filtered_s4(int kind, int segs) { return dev::pick_filter<3, 4, false>(kind, segs); }
 
 }  // namespace pfac

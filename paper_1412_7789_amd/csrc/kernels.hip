@@ -99,8 +99,9 @@ __global__ __launch_bounds__(256) void probe_read_kernel(const uint8_t *buf, int
     if (lane_id() == 0 && acc == 0x9E3779B9u) *out = acc;   // practically never taken
 }
 
-// strides 2 and 4 exist for K = 3 only
-FilteredFn pick_filtered(int K, int kind, int segs, int stride) {
+// strides 2 and 4 exist for K = 3 only; `win`: with the stride's window table
+FilteredFn pick_filtered(int K, int kind, int segs, int stride, bool win) {
+    if (win) return stride == 4 ? pick_filtered_s4w(kind, segs) : pick_filtered_s2w(kind, segs);
     if (stride == 4) return pick_filtered_s4(kind, segs);
     if (stride == 2) return pick_filtered_s2(kind, segs);
     if (K == 1) return pick_filtered_s1k1(kind, segs);
@@ -131,6 +132,12 @@ FilteredGeom filtered_geom(const ac_automaton *a, const uint8_t *text, int64_t n
     F.c_lo = F.mis > 0 ? 1 : 0;
     F.c_hi = F.V >= 16 ? (F.V - 16) / CH : 0;
     F.filter = a->dfilter[stride_set(cfg.stride) * kNumFilterKinds + cfg.filter - 1];
+    if (cfg.stride > 1) {
+        const int ws = window_set(cfg.stride);
+        F.win_keys = a->dwin_keys[ws];
+        F.win_entries = reinterpret_cast<const int4 *>(a->dwin_entries[ws]);
+        F.win_nb = a->host.win[ws].bits - 2;
+    }
     const int waves = cfg.block / kWave;
     const int64_t interior = std::max<int64_t>(0, F.c_hi - F.c_lo);
     const int64_t want = (std::max<int64_t>(interior, 1) + waves - 1) / waves;
@@ -307,7 +314,9 @@ int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &cfg, 
             err = "text too large for one launch";
             return AC_EINVAL;
         }
-        FilteredFn fn = pick_filtered(P.K, cfg.filter, cfg.segs, cfg.stride);
+        // the window table exists for keywords of stride + 4 bytes and more
+        const bool win = F.win_keys != nullptr;
+        FilteredFn fn = pick_filtered(P.K, cfg.filter, cfg.segs, cfg.stride, win);
         if (!fn) { err = "no kernel for this filter and stride"; return AC_EINVAL; }
         KArgs KA{a->dev, S, F};
         void *fargs[] = {&KA};

@@ -62,6 +62,36 @@ constexpr int kNumFilters = 3 * kNumFilterKinds;   // strides 1, 2 and 4
 // Filter set of a sampling stride: 0 (stride 1), 1 (stride 2), 2 (stride 4).
 constexpr int stride_set(int stride) { return stride == 4 ? 2 : stride - 1; }
 
+// Exact table of the 4-byte windows x at keyword positions 1 .. stride: every
+// window leads to the keyword paths it lies on.  A two-choice cuckoo table of
+// 4-key buckets (16 bytes, one load) holds the windows; the entry of slot i
+// is entries[i], further ones of the same window follow its `next` links.
+// Empty slots hold a key that never hashes to their bucket.
+struct WindowEntry {
+    int32_t kw;        // position in kw_bytes of a keyword on this path
+    int32_t len;       // bytes to compare with the text from the path's start
+    int32_t what;      // general: the state at depth len; else the keyword id
+    uint32_t link;     // window position (bits 0..2) | general << 3 | (next entry + 1) << 4
+};
+struct WindowTable {
+    int32_t bits = 0;                    // log2(slots)
+    std::vector<uint32_t> keys;          // [1 << bits]
+    std::vector<WindowEntry> entries;    // [1 << bits] and the links' targets
+};
+constexpr uint32_t kWinGeneral = 8u;
+constexpr uint32_t kWinMul1 = 0x9E3779B1u, kWinMul2 = 0x85EBCA77u;
+// The two buckets (of 4 slots) of window x among 2^nb (nb >= 1).
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline void window_buckets(uint32_t x, int nb, uint32_t &b1, uint32_t &b2) {
+    b1 = (x * kWinMul1) >> (32 - nb);
+    b2 = ((x ^ (x >> 15)) * kWinMul2) >> (32 - nb);
+    if (b2 == b1) b2 = b1 ^ 1u;
+}
+// Index of a stride's window table.
+constexpr int window_set(int stride) { return stride == 4 ? 1 : 0; }
+
 // Host-side build result (the "plan").  States are numbered breadth first,
 // so the children of a state are contiguous and sorted by byte, and every
 // state of depth <= dense_depth precedes every deeper state.
@@ -89,6 +119,8 @@ struct Plan {
     int32_t n_quads2 = 0;          // distinct 4-byte windows at keyword positions 1 and 2
     bool pair2 = false;            // the stride-2 AC_FILTER_PAIR20 map exists
     std::vector<uint8_t> filter[kNumFilters];   // indexed by stride_set(stride) * kNumFilterKinds + kind - 1
+    // exact window tables of strides 2 and 4 (empty without the 4-byte windows)
+    WindowTable win[2];
     int32_t ptab_bits = 0;
     std::vector<uint32_t> ptab;    // [2 << ptab_bits]: buckets of 4 {key, value} slots
     std::vector<int32_t> tail;     // [S]: leaf of a forced path, or -1
@@ -154,6 +186,9 @@ struct ac_automaton {
     int64_t dbytes = 0;
     pfac::DevAut dev{};
     const uint8_t *dfilter[pfac::kNumFilters] = {};   // device filter maps, by stride_set * kinds + kind - 1
+    // device window tables of strides 2 and 4, by window_set (null without one)
+    const uint32_t *dwin_keys[2] = {};
+    const pfac::WindowEntry *dwin_entries[2] = {};
     int cu_count = 0;
     int64_t lds_per_block = 0;
     int64_t lds_per_cu = 0;

@@ -83,6 +83,76 @@ bool build_cuckoo(const std::vector<std::pair<uint32_t, uint32_t>> &items, int b
     return true;
 }
 
+// Builds the exact window table of one stride from (window, state) pairs
+// sorted by window; entry_of(state) gives the state's entry without its link.
+template <typename EntryOf>
+void build_windows(const std::vector<uint64_t> &pairs, EntryOf &&entry_of, WindowTable &W) {
+    std::vector<uint32_t> first;              // index of each distinct window's first pair
+    for (size_t i = 0; i < pairs.size(); ++i)
+        if (i == 0 || (pairs[i] >> 32) != (pairs[i - 1] >> 32)) first.push_back(uint32_t(i));
+    const size_t n = first.size();
+    int bits = 4;                             // four buckets at least: see the empty slots below
+    while (double(size_t(1) << bits) * 0.85 < double(n)) ++bits;
+    constexpr uint32_t kFree = ~0u;
+    std::vector<uint32_t> slot;               // the window in each slot, by its rank
+    for (;; ++bits) {
+        const int nb = bits - 2;
+        slot.assign(size_t(1) << bits, kFree);
+        uint32_t rng = 0x2545F491u;
+        bool placed = true;
+        for (size_t k = 0; k < n && placed; ++k) {
+            uint32_t item = uint32_t(k), from = kFree;
+            placed = false;
+            for (int kick = 0; kick < 2000 && !placed; ++kick) {
+                uint32_t b[2];
+                window_buckets(uint32_t(pairs[first[item]] >> 32), nb, b[0], b[1]);
+                for (uint32_t c : b)
+                    for (uint32_t j = 0; j < 4 && !placed; ++j)
+                        if (slot[size_t(c) * 4 + j] == kFree) {
+                            slot[size_t(c) * 4 + j] = item;
+                            placed = true;
+                        }
+                if (placed) break;
+                // evict from the bucket the item did not come from
+                rng ^= rng << 13; rng ^= rng >> 17; rng ^= rng << 5;
+                from = b[0] == from ? b[1] : b[0];
+                std::swap(item, slot[size_t(from) * 4 + (rng & 3u)]);
+            }
+        }
+        if (placed) break;
+    }
+    W.bits = bits;
+    const int nb = bits - 2;
+    W.keys.resize(size_t(1) << bits);
+    W.entries.assign(size_t(1) << bits, WindowEntry{0, 0, 0, 0u});
+    for (uint32_t at = 0; at < uint32_t(slot.size()); ++at) {
+        if (slot[at] == kFree) {
+            // a key whose buckets are others
+            for (uint32_t f = 0;; ++f) {
+                uint32_t b1, b2;
+                window_buckets(f, nb, b1, b2);
+                if (b1 != at / 4 && b2 != at / 4) {
+                    W.keys[at] = f;
+                    break;
+                }
+            }
+            continue;
+        }
+        const size_t i0 = first[slot[at]];
+        W.keys[at] = uint32_t(pairs[i0] >> 32);
+        WindowEntry e = entry_of(int32_t(uint32_t(pairs[i0])));
+        size_t end = i0 + 1;
+        while (end < pairs.size() && (pairs[end] >> 32) == (pairs[i0] >> 32)) ++end;
+        if (end > i0 + 1) e.link |= uint32_t(W.entries.size() + 1) << 4;
+        W.entries[at] = e;
+        for (size_t i = i0 + 1; i < end; ++i) {
+            e = entry_of(int32_t(uint32_t(pairs[i])));
+            if (i + 1 < end) e.link |= uint32_t(W.entries.size() + 2) << 4;
+            W.entries.push_back(e);
+        }
+    }
+}
+
 }  // namespace
 
 int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
@@ -281,26 +351,37 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     const std::vector<uint32_t> windows4 = P.sampled4 ? windows_of(4) : std::vector<uint32_t>();
     P.n_windows2 = int32_t(windows.size());
     P.n_windows4 = int32_t(windows4.size());
-    // 4-byte windows at positions 1 .. count (keywords of count + 4 bytes or more)
+    // 4-byte windows at positions 1 .. count (keywords of count + 4 bytes or
+    // more), with the states whose paths end with them: (window << 32 | state)
+    // for every state of depth 5 .. count + 4, sorted.  rep[s] = a keyword
+    // whose path passes through s down to a leaf.
+    std::vector<int32_t> rep(size_t(S), -1);
+    for (int32_t s = S - 1; s >= 0; --s)
+        rep[size_t(s)] = P.n_child[size_t(s)] > 0 ? rep[size_t(P.first_child[size_t(s)])]
+                                                  : P.out_pid[size_t(P.out_off[size_t(s)])];
     auto quads_of = [&](int count) {
-        std::vector<uint32_t> w;
-        w.reserve(size_t(n) * size_t(count));
-        for (int32_t p = 0; p < n; ++p) {
-            const uint8_t *k = kw(p);
-            for (int j = 1; j <= count; ++j)
-                w.push_back(uint32_t(k[j]) | uint32_t(k[j + 1]) << 8 | uint32_t(k[j + 2]) << 16 |
-                            uint32_t(k[j + 3]) << 24);
+        std::vector<uint64_t> w;
+        for (int32_t s = 0; s < S && P.depth[size_t(s)] <= count + 4; ++s) {
+            const int32_t j = P.depth[size_t(s)] - 4;
+            if (j < 1) continue;
+            const uint8_t *k = kw(rep[size_t(s)]) + j;
+            const uint32_t x = uint32_t(k[0]) | uint32_t(k[1]) << 8 | uint32_t(k[2]) << 16 | uint32_t(k[3]) << 24;
+            w.push_back(uint64_t(x) << 32 | uint32_t(s));
         }
         std::sort(w.begin(), w.end());
-        w.erase(std::unique(w.begin(), w.end()), w.end());
         return w;
+    };
+    auto distinct = [](const std::vector<uint64_t> &w) {
+        int32_t c = 0;
+        for (size_t i = 0; i < w.size(); ++i) c += i == 0 || (w[i] >> 32) != (w[i - 1] >> 32);
+        return c;
     };
     P.pair2 = P.K == 3 && P.min_len >= 6;
     P.pair4 = P.K == 3 && P.min_len >= 8;
-    const std::vector<uint32_t> quads2 = P.pair2 ? quads_of(2) : std::vector<uint32_t>();
-    const std::vector<uint32_t> quads4 = P.pair4 ? quads_of(4) : std::vector<uint32_t>();
-    P.n_quads2 = int32_t(quads2.size());
-    P.n_quads4 = int32_t(quads4.size());
+    const std::vector<uint64_t> quads2 = P.pair2 ? quads_of(2) : std::vector<uint64_t>();
+    const std::vector<uint64_t> quads4 = P.pair4 ? quads_of(4) : std::vector<uint64_t>();
+    P.n_quads2 = distinct(quads2);
+    P.n_quads4 = distinct(quads4);
     // A key x with hash h = x * mul (mod 2^32) owns bit h mod 32 of word (or
     // byte) h >> shift.  The sampled kernels hash x * mul + c with 0 <= c <
     // 32, which may carry into the index: those maps also set the key's bit
@@ -319,7 +400,8 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
                 const bool have = (set == 1 && P.pair2) || (set == 2 && P.pair4);
                 if (!have) { f.clear(); continue; }
                 f.assign(size_t(g.bytes), 0);
-                for (uint32_t x : set == 1 ? quads2 : quads4) {
+                for (uint64_t q : set == 1 ? quads2 : quads4) {
+                    const uint32_t x = uint32_t(q >> 32);
                     const uint32_t h = prefix_hash(x & 0xFFFFFFu, mul);
                     const size_t w = size_t(h >> g.shift) * 4;
                     const uint32_t third = set == 1 ? (x >> 16) & 31u : h & 31u;
@@ -409,13 +491,10 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     }
     // Unary chains that do not end at a leaf: chain[s] = the first state
     // below s that ends a keyword or has other than one child, when s has
-    // one child (else -1); rep[s] = a keyword whose path passes through s
-    // down to a leaf (so it spells every chain below s).
-    std::vector<int32_t> chain(size_t(S), -1), rep(size_t(S), -1);
+    // one child (else -1).
+    std::vector<int32_t> chain(size_t(S), -1);
     for (int32_t s = S - 1; s >= 0; --s) {
-        const int32_t nc = P.n_child[size_t(s)];
-        rep[size_t(s)] = nc > 0 ? rep[size_t(P.first_child[size_t(s)])] : P.out_pid[size_t(P.out_off[size_t(s)])];
-        if (nc == 1) {
+        if (P.n_child[size_t(s)] == 1) {
             const int32_t c = P.first_child[size_t(s)];
             chain[size_t(s)] = (is_final(c) || P.n_child[size_t(c)] != 1) ? c : chain[size_t(c)];
         }
@@ -456,6 +535,24 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
         }
         if (is_final(s)) ti[3] = int32_t(uint32_t(ti[3]) | kFinalBit);
     }
+    // ---- exact window tables ------------------------------------------------
+    // No keyword ends above a window's state (every keyword has at least
+    // stride + 4 bytes), so the path down to it is compared as a whole: with
+    // its keyword, when the rest is forced down to a leaf with one keyword
+    // (and none ends on the way), else down to the state, where a walk goes on.
+    auto entry_of = [&](int32_t s) {
+        const int32_t d = P.depth[size_t(s)], l = P.tail[size_t(s)];
+        const int32_t p = rep[size_t(s)];
+        WindowEntry e{int32_t(offsets[p] - offsets[0]), d, s, uint32_t(d - 4) | kWinGeneral};
+        if (l >= 0 && (l == s || !is_final(s)) && P.out_off[size_t(l) + 1] - P.out_off[size_t(l)] == 1) {
+            e.len = P.depth[size_t(l)];
+            e.what = P.out_pid[size_t(P.out_off[size_t(l)])];
+            e.link = uint32_t(d - 4);
+        }
+        return e;
+    };
+    if (P.pair2) build_windows(quads2, entry_of, P.win[window_set(2)]);
+    if (P.pair4) build_windows(quads4, entry_of, P.win[window_set(4)]);
     // keyword bytes (for tail comparisons) with int32 offsets
     P.kw_bytes.assign(bytes + offsets[0], bytes + offsets[0] + total);
     P.kw_off.resize(size_t(n) + 1);

@@ -366,3 +366,73 @@ def test_build_errors(lib):
     assert b"keyword" in lib.ac_last_error()
     # a NULL automaton is rejected before any GPU call
     assert lib.ac_match(None, None, 0, None, None) == L.AC_EINVAL
+
+
+def _window_slots(keys, x):
+    """Slots of x's two buckets in a window table."""
+    nb = len(keys).bit_length() - 1 - 2
+    b1 = ((x * 0x9E3779B1) & 0xFFFFFFFF) >> (32 - nb)
+    b2 = (((x ^ (x >> 15)) * 0x85EBCA77) & 0xFFFFFFFF) >> (32 - nb)
+    b2 = b1 ^ 1 if b2 == b1 else b2
+    return [4 * b + j for b in (b1, b2) for j in range(4)]
+
+
+@pytest.mark.parametrize("kws", [
+    make_keywords(SPECS["sweep"], np.random.default_rng(3), np.random.default_rng(4)),
+    make_keywords(dataclasses.replace(SPECS["large"], n=600), np.random.default_rng(5), np.random.default_rng(6)),
+    [b"aaaaaaaa", b"aaaaaaaaa", b"aaaaaaaabbbb", b"baaaaaaaa", b"aaaaaaaa", b"cccccaaaa"],
+    [b"\x00" * 6, b"\x00" * 5 + b"\x01"],
+    [b"abcdefgh"],
+], ids=["sweep", "shared", "periodic", "six-bytes", "one"])
+def test_window_tables_lead_to_every_path(kws):
+    """Every 4-byte window of every keyword at positions 1 .. stride is found
+    in one of its two buckets, exactly once, and its entries are exactly the
+    distinct paths that pass through it: each fixes the path's start and
+    compares either the whole of the one keyword the path is forced to, or the
+    path down to the state where the walk goes on.  Other values are absent."""
+    T = Tables(kws)
+    flat = b"".join(kws)
+    rng = np.random.default_rng(9)
+    for stride, kt, et in ((2, L.AC_TABLE_WINDOW2_KEYS, L.AC_TABLE_WINDOW2_ENTRIES),
+                           (4, L.AC_TABLE_WINDOW4_KEYS, L.AC_TABLE_WINDOW4_ENTRIES)):
+        keys, ent = T.plan.export(kt, np.uint32), T.plan.export(et, np.int32).reshape(-1, 4)
+        if min(map(len, kws)) < stride + 4:
+            assert len(keys) == 0 and len(ent) == 0
+            continue
+        assert len(keys) & (len(keys) - 1) == 0 and len(ent) >= len(keys)
+        paths = {}
+        for k in kws:
+            for j in range(1, stride + 1):
+                paths.setdefault(int.from_bytes(k[j:j + 4], "little"), set()).add(k[:j + 4])
+
+        def find(x):
+            return [i for i in _window_slots(keys, x) if int(keys[i]) == x]
+
+        for x, want in paths.items():
+            at = find(x)
+            assert len(at) == 1
+            i, got = at[0], set()
+            while True:
+                kw, n, what, link = (int(v) for v in ent[i])
+                j, compared = link & 7, flat[kw:kw + n]
+                path = compared[:j + 4]
+                assert 1 <= j <= stride and path not in got
+                got.add(path)
+                through = [p for p, k in enumerate(kws) if k.startswith(path)]
+                if link & 8:
+                    assert n == j + 4
+                    s = 0
+                    for b in path:
+                        s = T.step(s, b)[0]
+                    assert what == s
+                else:
+                    assert through == [what] and compared == kws[what]
+                link = (link & 0xFFFFFFFF) >> 4
+                if link == 0:
+                    break
+                i = link - 1
+            assert got == want
+        for x in rng.integers(0, 1 << 32, size=3000).tolist() + [0, 0xFFFFFFFF]:
+            if x not in paths:
+                assert all(int(ent[i][1]) == 0 for i in find(x)) or not find(x)
+                assert not find(x)

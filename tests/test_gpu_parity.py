@@ -461,3 +461,40 @@ def test_single_text_graph_replays_match_eager():
         assert int(d_count.item()) == n
         assert_same((off[:n].cpu().numpy(), pid[:n].cpu().numpy()), exp, f"replay {r}")
         assert a.count(t) == n                              # eager work between replays
+
+
+@pytest.mark.parametrize("stride", [2, 4])
+@pytest.mark.parametrize("segs", [1, 2, 4])
+def test_windows_shared_nested_and_cut(stride, segs):
+    """The exact window table's paths: windows that lie on many keywords and
+    at several positions of one (periodic keywords), keywords nested in longer
+    ones and duplicated, on a text dense in them (queues and hit regions
+    fill up, so slow mode resumes in the middle of a chunk), cut at both ends
+    inside keywords, and as a batch cut inside keywords.  Every filter map."""
+    rng = np.random.default_rng(31)
+    kws = [b"abababab", b"ababababab", b"babababa", b"abababac", b"abababab", b"aaaaaaaa", b"aaaaaaaaaaaab",
+           bytes(range(1, 9)), bytes(range(1, 60)), b"xyxyxyxyz" + b"q" * 90, b"xyxyxyxyz" + b"q" * 89 + b"r"]
+    pieces = [np.frombuffer(k, dtype=np.uint8) for k in kws] + [np.frombuffer(b"ab" * 700, dtype=np.uint8),
+              np.full(900, ord("a"), dtype=np.uint8), rng.integers(97, 99, size=500, dtype=np.uint8)]
+    parts, n = [], 0
+    while n < (1 << 20):
+        parts.append(pieces[int(rng.integers(0, len(pieces)))])
+        n += len(parts[-1])
+    text = np.concatenate([rng.integers(0, 256, size=1 << 20, dtype=np.uint8)] + parts)
+    a = pf.Automaton(kws)
+    cut = text[len(text) // 2 + 3:-5]
+    exp, exp_cut = oracle_match(kws, text), oracle_match(kws, cut)
+    bounds = np.unique(np.concatenate([[0, len(text)], rng.integers(0, len(text), size=200)])).astype(np.int64)
+    want = [oracle_match(kws, text[s:e]) for s, e in zip(bounds[:-1], bounds[1:])]
+    key = lambda t, o, p: np.sort((t.astype(np.int64) << 40) | (o << 8) | p)
+    want_key = key(np.repeat(np.arange(len(want)), [len(w[0]) for w in want]), np.concatenate([w[0] for w in want]),
+                   np.concatenate([w[1] for w in want]))
+    d, b = torch.from_numpy(text).cuda(), torch.from_numpy(bounds).cuda()
+    for f in range(1, 7):
+        cfg = pf.launch_config(policy=1, filter=f, segs=segs, stride=stride)
+        say("windows", stride, segs, f)
+        assert_same(gpu_match(kws, text, launch=cfg, offset=5, automaton=a), exp, f"filter {f}")
+        assert_same(gpu_match(kws, cut, launch=cfg, offset=2, automaton=a), exp_cut, f"cut, filter {f}")
+        tid, off, pid, per = (x.cpu().numpy() for x in a.match_batch(d, b, launch=cfg, capacity=len(want_key)))
+        assert np.array_equal(key(tid, off, pid), want_key), f"batch, filter {f}"
+        assert np.array_equal(per, [len(w[0]) for w in want])
