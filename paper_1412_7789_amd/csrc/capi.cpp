@@ -41,11 +41,11 @@ int hip_fail(const char *what, hipError_t e) {
 // The filtered policy's hit regions are sized for the widest launch when the
 // slot is created and never change afterwards, so a HIP graph that captured
 // their address stays valid.
+constexpr int kDoneWord = 16, kSlotWords = 32;   // the two words on 128-byte lines of their own
 struct CountSlot {
-    unsigned long long *d = nullptr;           // [0] match count, [1] finished blocks
-    unsigned long long *h = nullptr;           // pinned: [0] count, [1] sequence number of the last report
+    unsigned long long *d = nullptr;           // [0] match count, [kDoneWord] finished blocks
+    unsigned long long *h = nullptr;           // pinned: [0] count, [1] report_tag of the last report
     unsigned long long seq = 0;                // last sequence number handed to a scan
-    unsigned long long done_total = 0;         // value of d[1] after the last synchronous call
     bool stale = false;                        // a failed call may have left *d != *h
     hipEvent_t ev[2] = {nullptr, nullptr};   // kernel timing: scan start, stop
     HitScratch hs;                             // hit regions of the filtered policy
@@ -109,7 +109,7 @@ int count_slot(int device, hipStream_t stream, CountSlot **out, int64_t regions)
                                                 : fail(AC_EINVAL, "stream scratch has fewer hit regions than the launch");
     }
     CountSlot s;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(&s.d), 2 * sizeof(unsigned long long));
+    hipError_t e = hipMalloc(reinterpret_cast<void **>(&s.d), kSlotWords * sizeof(unsigned long long));
     if (e != hipSuccess) return hip_fail("hipMalloc(count)", e);
     // coherent: the scan kernel stores the count here itself
     e = hipHostMalloc(reinterpret_cast<void **>(&s.h), 2 * sizeof(unsigned long long), hipHostMallocCoherent);
@@ -318,16 +318,15 @@ ac_launch resolved(const ac_automaton *a, const ScanArgs &S, const ac_launch *la
 // S.count_base.
 int enqueue(const ac_automaton *a, ScanArgs S, const ac_launch &cfg, bool batch, bool clear,
             unsigned long long *d_count, const HitScratch &hs, hipStream_t stream,
-            const KernelTiming *timing = nullptr, int64_t *blocks = nullptr) {
+            const KernelTiming *timing = nullptr) {
     S.count = d_count;
     std::string err;
     if (clear) {
         S.count_base = 0;
-        S.done_base = 0;
         int rc = launch_zero(d_count, S.done, S.per_text, batch ? S.n_texts : 0, stream, err);
         if (rc) return fail(rc, err);
     }
-    int rc = launch_scan(a, S, cfg, hs, stream, err, timing, blocks);
+    int rc = launch_scan(a, S, cfg, hs, stream, err, timing);
     return rc ? fail(rc, err) : AC_OK;
 }
 
@@ -353,13 +352,10 @@ int64_t sync_count(const ac_automaton *a, ScanArgs S, const ac_launch *launch, b
     slot->stale = true;
     // the filtered policy's last block stores the count into the pinned word
     const bool reported = cfg.policy == AC_POLICY_FILTERED && S.n > 0;
-    S.done = slot->d + 1;                          // cleared with the count
-    if (clear) slot->done_total = 0;
-    S.done_base = slot->done_total;
+    S.done = slot->d + kDoneWord;                  // cleared with the count
     S.host_count = reported ? slot->h : nullptr;
     S.host_seq = ++slot->seq;
-    int64_t blocks = 0;
-    rc = enqueue(a, S, cfg, batch, clear, slot->d, slot->hs, stream, timed ? &T : nullptr, &blocks);
+    rc = enqueue(a, S, cfg, batch, clear, slot->d, slot->hs, stream, timed ? &T : nullptr);
     if (rc) return rc;
     hipError_t e = hipSuccess;
     if (!reported) {
@@ -367,12 +363,16 @@ int64_t sync_count(const ac_automaton *a, ScanArgs S, const ac_launch *launch, b
         if (e != hipSuccess) return hip_fail("hipMemcpyAsync(count)", e);
     }
     if (reported && !timed) {
-        // The count is final once the last block has stored it with this
-        // call's sequence number; every match and per-text count is written
+        // The count is final once the last block has stored it with its tag
+        // of this call's sequence number; every match and per-text count is written
         // by then.  Waiting on the word skips the stream's completion path.
         // The stream is polled now and then, so a failed launch or a kernel
         // that ended without reporting ends the wait too.
-        for (uint64_t spin = 1; __atomic_load_n(&slot->h[1], __ATOMIC_ACQUIRE) != S.host_seq; ++spin) {
+        auto reported_count = [&] {
+            const unsigned long long tag = __atomic_load_n(&slot->h[1], __ATOMIC_ACQUIRE);
+            return tag == report_tag(__atomic_load_n(&slot->h[0], __ATOMIC_ACQUIRE), S.host_seq);
+        };
+        for (uint64_t spin = 1; !reported_count(); ++spin) {
 #if defined(__x86_64__)
             __builtin_ia32_pause();
 #endif
@@ -380,7 +380,7 @@ int64_t sync_count(const ac_automaton *a, ScanArgs S, const ac_launch *launch, b
             e = hipStreamQuery(stream);
             if (e == hipErrorNotReady) continue;
             if (e != hipSuccess) return hip_fail("hipStreamQuery", e);
-            if (__atomic_load_n(&slot->h[1], __ATOMIC_ACQUIRE) != S.host_seq)
+            if (!reported_count())
                 return fail(AC_EHIP, "scan finished without reporting its count");
             break;
         }
@@ -388,7 +388,6 @@ int64_t sync_count(const ac_automaton *a, ScanArgs S, const ac_launch *launch, b
         e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return hip_fail("hipStreamSynchronize", e);
     }
-    if (reported) slot->done_total += uint64_t(blocks);
     slot->stale = false;
     if (timed) {
         float ms = -1.0f;
@@ -544,7 +543,7 @@ int tune(ac_automaton *a, const ScanArgs &S, bool batch, hipStream_t stream, ac_
             T.scan0 = e0;
             T.scan1 = e1;
             ScanArgs SA = S;
-            SA.done = slot->d + 1;
+            SA.done = slot->d + kDoneWord;
             slot->stale = true;                  // the next synchronous call clears the count
             if ((rc = enqueue(a, SA, cfg, batch, true, slot->d, slot->hs, stream, &T))) break;
             if ((e = hipStreamSynchronize(stream)) != hipSuccess) { rc = hip_fail("hipStreamSynchronize", e); break; }
@@ -609,7 +608,7 @@ int pfac::reserve_stream_scratch(hipStream_t stream, int64_t *device_bytes) {
     CountSlot *slot = nullptr;
     rc = count_slot(dev, stream, &slot, widest_scan_regions(cus, lds_cu));
     if (!rc && device_bytes)
-        *device_bytes = 2 * int64_t(sizeof(unsigned long long)) + slot->hs.regions * slot->hs.cap * int64_t(sizeof(uint4));
+        *device_bytes = kSlotWords * int64_t(sizeof(unsigned long long)) + slot->hs.regions * slot->hs.cap * int64_t(sizeof(uint4));
     return rc;
 }
 

@@ -526,7 +526,7 @@ struct FilterLaunch {
     int64_t mis;             // text - base
     int64_t V;               // mis + n: end of the text in `base` coordinates
     int64_t n_chunks;        // ceil(V / chunk bytes)
-    int64_t c_lo, c_hi;      // interior chunks [c_lo, c_hi): whole chunk + 16 B inside the text
+    int64_t c_hi;            // chunks from c_hi on (two at most) reach past the text's last 16 bytes
     const uint8_t *filter;   // the filter map this launch stages in LDS
     int32_t hit_cap;         // entries per wave region
     uint4 *hits;             // [waves * hit_cap]: {slot << 12 | position, prefix-table value,
@@ -545,7 +545,7 @@ struct KArgs {
 };
 typedef const __attribute__((address_space(4))) KArgs *KArgsPtr;
 
-// Slot -> interior chunk of one block (see filtered_kernel).
+// Slot -> chunk of one block (see filtered_kernel).
 struct SlotMap {
     int64_t bfirst;    // the block's first chunk
     int64_t nw;        // waves in the grid
@@ -562,7 +562,7 @@ struct ChunkRegs {
     uint32_t tail;   // first dword after the chunk (halo of the last lane)
 };
 
-// Interior chunk: one coalesced 16-byte load per lane and segment, as buffer
+// One chunk: one coalesced 16-byte load per lane and segment, as buffer
 // loads from a descriptor based at the chunk (uniform, in SGPRs) with
 // per-lane offsets that never change, so issuing the next chunk's loads
 // needs no address register that an earlier load might still be writing.
@@ -571,12 +571,22 @@ struct ChunkRegs {
 // 1000 keywords: 0.178 ms instead of 0.191; the 4096-text batch, whose
 // block-wide walk follows the stream closely, 1% slower; a uniform branch
 // that kept the default policy for batches cost more than either).
+//
+// The first and the last chunks need no other path: the 16-byte granules that
+// hold the text's ends are read whole (a granule never straddles a page), and
+// the descriptor of a last chunk ends with the text's last dword, past which
+// loads return 0.  Offsets that do not lie in the text are dropped where they
+// are looked up.  (A path of its own for them, byte loads and walks by one
+// wave, took 1.3 to 3.5 us at the end of every scan; kernel without it and with
+// report_count's one store: 1 KiB 8.2 -> 5.9 us, 1 MiB 12.4 -> 10.6, paper
+// lines 671 KB 14.0 -> 11.5, 64 MiB at stride 1 46.2 -> 41.8.)
 template <int SEGS>
-__device__ __forceinline__ void load_interior(const FilterLaunch &F, int64_t c, unsigned lane, ChunkRegs<SEGS> &R) {
+__device__ __forceinline__ void load_chunk(const FilterLaunch &F, int64_t c, unsigned lane, ChunkRegs<SEGS> &R) {
     constexpr int64_t CH = int64_t(SEGS) * kSegBytes;
     constexpr int kNonTemporal = 2;     // cache-policy operand of the buffer loads: nt
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t *>(F.base + c * CH), short(0), int(CH + 16), kBufferFlags);
+    const int records = c < F.c_hi ? int(CH + 16) : int(((F.V + 3) & ~int64_t(3)) - c * CH);
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(F.base + c * CH), short(0), records, kBufferFlags);
 #pragma unroll
     for (int j = 0; j < SEGS; ++j) {
         const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(lane * 16u + uint32_t(j) * kSegBytes), 0,
@@ -584,23 +594,6 @@ __device__ __forceinline__ void load_interior(const FilterLaunch &F, int64_t c, 
         R.d[j][0] = q.x; R.d[j][1] = q.y; R.d[j][2] = q.z; R.d[j][3] = q.w;
     }
     R.tail = __builtin_amdgcn_raw_buffer_load_b32(rsrc, int(CH), 0, 0);
-}
-
-// Chunk that overlaps either end of the text: bytes outside it read as 0.
-template <int SEGS>
-__device__ __forceinline__ void load_partial(const FilterLaunch &F, int64_t c, unsigned lane, ChunkRegs<SEGS> &R) {
-    constexpr int64_t CH = int64_t(SEGS) * kSegBytes;
-    auto get4 = [&](int64_t p) {
-        uint32_t v = 0;
-        for (int b = 0; b < 4; ++b)
-            if (p + b >= F.mis && p + b < F.V) v |= uint32_t(F.base[p + b]) << (8 * b);
-        return v;
-    };
-#pragma unroll
-    for (int j = 0; j < SEGS; ++j)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) R.d[j][w] = get4(c * CH + j * kSegBytes + lane * 16 + w * 4);
-    R.tail = get4((c + 1) * CH);
 }
 
 // Candidate mask of one chunk: bit 16 j + s is set when offset s of the
@@ -796,9 +789,43 @@ __device__ __forceinline__ int find_window(bool in_lds, const uint32_t *skeys, c
     return window_slot([&](uint32_t b) { return gload16(reinterpret_cast<const uint8_t *>(gkeys + 4 * b)); }, nb, x);
 }
 
+// Called by every thread at the scan's end: the last block to finish hands the
+// count to the host, once every block's matches are stored.  The barrier waits
+// for this block's stores, the release fence makes them visible to the device
+// before the block counts itself done, and the last block's acquire fence
+// pairs with the other blocks' release fences.  The count and its tag go out
+// in one store; the host takes them only when they belong together, so nothing
+// orders them (a fence between two stores waited for the host link).
+__device__ __forceinline__ void report_count(const ScanArgs &S) {
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    if (gridDim.x > 1) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (atomicAdd(S.done, 1ull) != gridDim.x - 1) return;
+        atomicExch(S.done, 0ull);    // for the next scan
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    const unsigned long long c = atomicAdd(S.count, 0ull);
+    const unsigned long long tag = report_tag(c, S.host_seq);
+    gstore16(reinterpret_cast<uint4 *>(S.host_count), uint32_t(c), uint32_t(c >> 32), uint32_t(tag), uint32_t(tag >> 32));
+    __threadfence_system();
+}
+
+// Sum of v over lanes 0 .. lane - 1 (exclusive prefix), for the first 16
+// lanes; v must be 0 in the others.
+__device__ __forceinline__ int prefix16(int v, unsigned lane) {
+    int s = v;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+        const int up = __shfl_up(s, unsigned(d));
+        if (int(lane) >= d) s += up;
+    }
+    return s - v;
+}
+
 // Streaming kernel of the filtered policy.
 //
-// Work is dealt out in slots: slot i of block b is interior chunk c_lo + b W
+// Work is dealt out in slots: slot i of block b is chunk b W
 // + (i mod W) + (i div W) nw (W waves per block, nw waves in the grid, so a
 // step of the grid still reads one contiguous stretch of text).  Each wave
 // starts with slots `wave` and `wave + W` and takes every further slot from
@@ -832,8 +859,7 @@ __device__ __forceinline__ int find_window(bool in_lds, const uint32_t *skeys, c
 // Kept hits go to the wave's hit records (LDS, then its region).  A wave
 // whose region has no room for another drain leaves the loop and goes on in
 // a slow mode: it scans the rest of its slots one chunk at a time and walks
-// every hit as soon as a table confirms it.  So does every wave with the
-// partial chunks at the text's ends.  Finally each wave (one text) or the
+// every hit as soon as a table confirms it.  Finally each wave (one text) or the
 // whole block (a batch) walks the stored hits.
 template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, bool PAIR, bool WIN>
 __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
@@ -1002,7 +1028,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             else stage(reinterpret_cast<const uint4 *>(gptab), reinterpret_cast<uint4 *>(sptab), (2 << ptab_bits) / 4);
         }
         SlotMap M;
-        M.bfirst = F.c_lo + int64_t(blockIdx.x) * waves_per_block;
+        M.bfirst = int64_t(blockIdx.x) * waves_per_block;
         M.nw = nw;
         M.wmask = uint32_t(waves_per_block - 1);
         M.wlog = wlog;
@@ -1011,26 +1037,35 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
 
         uint4 *hits = F.hits + w * F.hit_cap;
         uint4 *lhits = shits + wave * kLdsHits;
-        // Streaming-loop drain of the newest `take` entries (interior chunks
-        // only: there o + 16 <= n, so the aligned 16 bytes from (o & ~3) lie
-        // in the text and give the prefix and the 8 bytes after it).  Refuses
-        // when the region might not hold its hits.
+        // Streaming-loop drain of the newest `take` entries.  Reads the
+        // aligned 16 bytes from each offset's dword on (the prefix and the 8
+        // bytes after it), held back to the text's last dword.  Refuses when
+        // the region might not hold its hits.
+        const int64_t n = P1->S.n;
+        const uintptr_t tlast = (reinterpret_cast<uintptr_t>(text) + uintptr_t(n) - 1u) & ~uintptr_t(3);
         auto drain_store = [&](int take) __attribute__((always_inline)) {
             if (hcount + kDrain > kLdsHits + F.hit_cap) return false;
             uint32_t ent[PER_LANE];
             pop(take, ent);
             u32x4 win[PER_LANE];
             uint32_t sh[PER_LANE];
+            bool inside[PER_LANE];
 #pragma unroll
             for (int r = 0; r < PER_LANE; ++r) {
                 const int64_t o = M.chunk(ent[r] >> 12) * CH + int64_t(ent[r] & 4095u) - F.mis;
                 const uintptr_t a = reinterpret_cast<uintptr_t>(text + o);
                 sh[r] = uint32_t(a & 3u);
-                const uint8_t *pa = reinterpret_cast<const uint8_t *>(a & ~uintptr_t(3));
-                win[r].x = gload4(pa);
-                win[r].y = gload4(pa + 4);
-                win[r].z = gload4(pa + 8);
-                win[r].w = gload4(pa + 12);
+                inside[r] = o >= 0 && o + K <= n;
+                const uintptr_t pa = inside[r] ? a & ~uintptr_t(3) : tlast;
+                if (pa + 12 <= tlast) {
+                    win[r] = gload16(reinterpret_cast<const uint8_t *>(pa));
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uintptr_t pi = pa + 4u * uintptr_t(i);
+                        win[r][i] = gload4(reinterpret_cast<const uint8_t *>(pi < tlast ? pi : tlast));
+                    }
+                }
             }
 #pragma unroll
             for (int r = 0; r < PER_LANE; ++r) {
@@ -1041,7 +1076,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 const uint32_t rb0 = __builtin_amdgcn_alignbyte(y1, y0, uint32_t(K));
                 const uint32_t rb1 = __builtin_amdgcn_alignbyte(y2, y1, uint32_t(K));
                 uint32_t e = 0;
-                if (int(lane) + r * kWave < take) {
+                if (int(lane) + r * kWave < take && inside[r]) {
                     const uint2 kv = probe_prefix(pt_lds, sptab, gptab, ptab_bits, x, mul);
                     e = kv.y;
                     // a non-final prefix state whose only child's byte differs
@@ -1079,17 +1114,17 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             return true;
         };
 
-        // Interior chunks, two register sets in turn so that the next chunk's
+        // The chunks, two register sets in turn so that the next chunk's
         // loads are in flight while this one is filtered.  The next chunk's
         // loads are issued unconditionally (the last step reloads its own
         // chunk): with a fixed number of loads between a chunk's loads and
         // its first use, the compiler waits for that chunk only.
         ChunkRegs<SEGS> ra, rb;
-        const int64_t c_hi = uniform64(F.c_hi);
+        const int64_t n_chunks = uniform64(F.n_chunks);
         cur = uint32_t(wave);
         nxt = uint32_t(wave + waves_per_block);
-        cur_ok = uniform(M.chunk(cur) < c_hi);
-        if (cur_ok) load_interior<SEGS>(F, M.chunk(cur), lane, ra);
+        cur_ok = uniform(M.chunk(cur) < n_chunks);
+        if (cur_ok) load_chunk<SEGS>(F, M.chunk(cur), lane, ra);
         // One half step: issue the next chunk's loads into `into` (or reload
         // the current one), take the slot after nxt from the block's counter
         // (lane 0), filter and queue the current chunk held in `regs`, then
@@ -1097,8 +1132,8 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         // atomic, so the loop's back edge merges only uniform conditions.
         // Returns false when the loop must end (slow mode, or no slot left).
         auto half = [&](ChunkRegs<SEGS> &regs, ChunkRegs<SEGS> &into) __attribute__((always_inline)) {
-            const bool nxt_ok = uniform(M.chunk(nxt) < c_hi);
-            load_interior<SEGS>(F, M.chunk(nxt_ok ? nxt : cur), lane, into);
+            const bool nxt_ok = uniform(M.chunk(nxt) < n_chunks);
+            load_chunk<SEGS>(F, M.chunk(nxt_ok ? nxt : cur), lane, into);
             if (lane == 0 && nxt_ok) ahead = atomicAdd(&snext, 1u);
             bool pushed;
             if constexpr (WIN) {
@@ -1133,7 +1168,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     const ScanArgs S = P2->S;
     const FilterLaunch F = P2->F;
     SlotMap M;
-    M.bfirst = F.c_lo + int64_t(blockIdx.x) * waves_per_block;
+    M.bfirst = int64_t(blockIdx.x) * waves_per_block;
     M.nw = nw;
     M.wmask = uint32_t(waves_per_block - 1);
     M.wlog = wlog;
@@ -1144,15 +1179,15 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         return M.chunk(ent >> 12) * CH + int64_t(ent & 4095u) - F.mis;
     };
 
-    {
-        int64_t pchunk = -1;         // a partial chunk's number, else -1 (entries hold slots)
-        // Drain that probes with byte loads and walks the hits right here.
+    if (slow) {
+        // Drains that walk what they confirm right here.
         auto drain_walk = [&](int take) __attribute__((always_inline)) {
             uint32_t ent[PER_LANE];
             pop(take, ent);
             for (int r = 0; r < PER_LANE; ++r) {
                 if (int(lane) + r * kWave >= take) continue;
-                const int64_t o = (pchunk >= 0 ? pchunk : M.chunk(ent[r] >> 12)) * CH + int64_t(ent[r] & 4095u) - F.mis;
+                const int64_t o = offset_of(ent[r]);
+                if (o < 0 || o + K > S.n) continue;
                 uint32_t x = 0;
                 for (int j = 0; j < K; ++j) x |= gload1(S.text + o + j) << (8 * j);
                 const uint2 kv = probe_prefix(pt_lds, sptab, A.ptab, A.ptab_bits, x, mul);
@@ -1164,62 +1199,38 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                                  [&](int32_t st) { emit(A, S, o - tstart, tid, st); },
                                  [&](int32_t pid) { emit_one(S, nullptr, o - tstart, tid, pid); });
             }
-            return true;
         };
         auto drain_walk_windows = [&](int take) __attribute__((always_inline)) {
             const uint2 e = pop_window(take);
-            if (int(lane) >= take) return true;
+            if (int(lane) >= take) return;
             const int slot = find_window(pt_lds, sptab, F.win_keys, F.win_nb, e.y);
-            if (slot < 0) return true;
-            const int64_t at = (pchunk >= 0 ? pchunk : M.chunk(e.x >> 12)) * CH + int64_t(e.x & 4095u) - F.mis + STRIDE;
-            walk_window(A, S, F.win_entries, slot, at,
+            if (slot < 0) return;
+            walk_window(A, S, F.win_entries, slot, offset_of(e.x) + STRIDE,
                         [&](int64_t o, int64_t &ts, int64_t &te, int32_t &tid) { locate_text(S, nullptr, o, ts, te, tid); },
                         [&](int64_t off, int32_t tid, int32_t st) { emit(A, S, off, tid, st); },
                         [&](int64_t off, int32_t tid, int32_t pid) { emit_one(S, nullptr, off, tid, pid); });
-            return true;
         };
-        // One loop takes what is left of slow mode's slots (cur first, with
-        // what its queueing left: its text is read again, then its
-        // successors), then the chunks overlapping an end of the text,
-        // [0, p0) and [p1, n_chunks), filtered with byte loads.  A queue that
+        // What is left of the wave's slots: cur first, with what its queueing
+        // left (its text is read again), then its successors.  A queue that
         // fills up is walked empty before its chunk goes on, so that the walk
         // is in the code once.
-        const int64_t p0 = lmin(F.c_lo, F.n_chunks);
-        const int64_t p1 = lmax(F.c_hi, F.c_lo);
-        const int64_t n_partial = p0 + (F.n_chunks - p1);
         auto full = [](int) __attribute__((always_inline)) { return false; };
         uint32_t sl = cur;
-        bool ok = slow && cur_ok, first = true;
-        int64_t part = w;
-        while (ok || qlen > 0 || part < n_partial) {
+        bool ok = cur_ok, first = true;
+        while (ok || qlen > 0) {
             ChunkRegs<SEGS> r;
-            bool queued = true;       // nothing (more) of this chunk to queue
+            bool queued = !ok;        // nothing (more) of this chunk to queue
             int g0 = 0;
             unsigned only = ~0u;
             unsigned long long m = 0;
             if (ok) {
-                load_interior<SEGS>(F, M.chunk(sl), lane, r);
-                queued = false;
+                load_chunk<SEGS>(F, M.chunk(sl), lane, r);
                 if (first) {
                     g0 = rest_g;
                     only = unsigned(rest);
                 }
                 if constexpr (!WIN)
                     m = first ? rest : filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(r, lane, sfilt, mul);
-            } else if (qlen == 0) {
-                pchunk = part < p0 ? part : p1 + (part - p0);
-                load_partial<SEGS>(F, pchunk, lane, r);
-                queued = false;
-                if constexpr (!WIN) {
-                    m = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(r, lane, sfilt, mul);
-                    for (int b = 0; b < SEGS * 16; ++b) {
-                        // keep offsets o with 0 <= o and o + K <= n (a
-                        // window's walk checks the offsets it leads to)
-                        const int64_t o = pchunk * CH + (b >> 4) * kSegBytes + int64_t(lane) * 16 + (b & 15) - F.mis;
-                        if (o < 0 || o + K > S.n) m &= ~(1ull << b);
-                    }
-                }
-                part += nw;
             }
             first = false;
             while (true) {
@@ -1240,12 +1251,12 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             }
             if (ok) {
                 sl = nxt;
-                ok = M.chunk(sl) < F.c_hi;
+                ok = M.chunk(sl) < F.n_chunks;
                 if (ok) {
                     // the slot after it: taken by the streaming loop, or now
                     nxt = __builtin_amdgcn_readfirstlane(ahead);
                     uint32_t t = 0;
-                    if (lane == 0 && M.chunk(nxt) < F.c_hi) t = atomicAdd(&snext, 1u);
+                    if (lane == 0 && M.chunk(nxt) < F.n_chunks) t = atomicAdd(&snext, 1u);
                     ahead = t;
                 }
             }
@@ -1310,30 +1321,23 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         }
         __syncthreads();
         // every wave's matches are staged: one atomic reserves the block's
-        // output range, the filter's LDS holds the waves' prefix sums
-        int32_t *wpre = reinterpret_cast<int32_t *>(sfilt);                                // [waves + 1]
-        unsigned long long *wbase = reinterpret_cast<unsigned long long *>(sfilt + 128);
-        if (threadIdx.x == 0) {
-            int32_t t = 0;
-            for (int j = 0; j < waves_per_block; ++j) {
-                wpre[j] = t;
-                t += imin(int32_t(squeue[j * kQueueCap]), kWaveStageCap);
-            }
-            wpre[waves_per_block] = t;
-            *wbase = t ? atomicAdd(S.count, static_cast<unsigned long long>(t)) - S.count_base : 0ull;
-        }
-        __syncthreads();
-        const int32_t total = wpre[waves_per_block];
-        const unsigned long long base = *wbase;
-        for (int32_t i = int32_t(threadIdx.x); i < total; i += int32_t(blockDim.x)) {
-            int j = 0;
-            while (wpre[j + 1] <= i) ++j;
-            const uint32_t *pr = squeue + j * kQueueCap + 2 + 2 * (i - wpre[j]);
-            const uint32_t ent = pr[0];
-            const unsigned long long idx = base + unsigned(i);
-            if (idx < static_cast<unsigned long long>(S.cap)) {
-                S.out_off[idx] = offset_of(ent);
-                S.out_pid[idx] = int32_t(pr[1]);
+        // output range, and each wave stores its own from where the waves
+        // before it end (each adds the counts up for itself)
+        const int staged = int(lane) < waves_per_block ? imin(int(squeue[int(lane) * kQueueCap]), kWaveStageCap) : 0;
+        const int before = prefix16(staged, lane);
+        const int total = __builtin_amdgcn_readlane(before + staged, kMaxWaves - 1);
+        unsigned long long *wbase = reinterpret_cast<unsigned long long *>(sfilt);   // the filter is done with
+        if (total > 0) {
+            if (threadIdx.x == 0) *wbase = atomicAdd(S.count, static_cast<unsigned long long>(total)) - S.count_base;
+            __syncthreads();
+            const int mine = __builtin_amdgcn_readlane(staged, wave);
+            const unsigned long long base = *wbase + unsigned(__builtin_amdgcn_readlane(before, wave));
+            for (int i = int(lane); i < mine; i += kWave) {
+                const unsigned long long idx = base + unsigned(i);
+                if (idx < static_cast<unsigned long long>(S.cap)) {
+                    S.out_off[idx] = offset_of(q[2 + 2 * i]);
+                    S.out_pid[idx] = int32_t(q[3 + 2 * i]);
+                }
             }
         }
     } else {
@@ -1365,14 +1369,15 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         static_assert((sizeof(MatchStage) + 15) / 16 * 16 + (2 * kMaxWaves + 1) * 4 <= (1u << FLOG2),
                       "the walk's stage must fit where the filter was");
         MatchStage *st = reinterpret_cast<MatchStage *>(sfilt);
-        int32_t *wfirst = reinterpret_cast<int32_t *>(sfilt + (sizeof(MatchStage) + 15) / 16 * 16);   // [waves + 1]
-        if (threadIdx.x == 0) {
-            wfirst[0] = 0;
-            for (int j = 0; j < waves_per_block; ++j) wfirst[j + 1] = wfirst[j] + int32_t(squeue[j * kQueueCap]);
-            st->n = 0;
-        }
+        int32_t *wfirst = reinterpret_cast<int32_t *>(sfilt + (sizeof(MatchStage) + 15) / 16 * 16);   // [kMaxWaves]
+        // each wave adds the counts up for itself; the first leaves the sums
+        // for the flat index's search
+        const int whits = int(lane) < waves_per_block ? int(squeue[int(lane) * kQueueCap]) : 0;
+        const int wbefore = prefix16(whits, lane);
+        const int32_t total = __builtin_amdgcn_readlane(wbefore + whits, kMaxWaves - 1);
+        if (wave == 0 && lane < kMaxWaves) wfirst[lane] = int(lane) < waves_per_block ? wbefore : 0x7fffffff;
+        if (threadIdx.x == 0) st->n = 0;
         __syncthreads();
-        const int32_t total = wfirst[waves_per_block];
         // The text starts (as offsets from the first text) are copied to LDS
         // when they fit, beside the stage or where the prefix table was.
         constexpr int kStageEnd = ((sizeof(MatchStage) + 15) / 16 * 16 + (2 * kMaxWaves + 1) * 4 + 15) / 16 * 16;
@@ -1396,8 +1401,10 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             loff = lds_off;
         }
         for (int32_t i = int32_t(threadIdx.x); i < total; i += int32_t(blockDim.x)) {
-            int j = 0;
-            while (wfirst[j + 1] <= i) ++j;          // wave (region) of flat index i
+            int j = 0;                               // wave (region) of flat index i
+#pragma unroll
+            for (int h = kMaxWaves / 2; h >= 1; h >>= 1)
+                if (wfirst[j + h] <= i) j += h;
             const int k = i - wfirst[j];
             if constexpr (WIN) {
                 const uint2 rec = k < kLdsWinHits
@@ -1421,25 +1428,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         flush_stage(S, st);
     }
 
-    // The last block to finish hands the count to the host, once every
-    // block's matches are stored: the barrier waits for this block's stores,
-    // the release fence makes them visible to the device before the block
-    // counts itself done, and the last block's acquire fence pairs with the
-    // other blocks' release fences.
-    if (S.host_count) __syncthreads();
-    if (S.host_count && threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const unsigned long long t = atomicAdd(S.done, 1ull);
-        if (t == S.done_base + gridDim.x - 1) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            const unsigned long long c = atomicAdd(S.count, 0ull);
-            auto *hc = (__attribute__((address_space(1))) unsigned long long *)(S.host_count);
-            hc[0] = c;
-            __threadfence_system();
-            hc[1] = S.host_seq;      // the count is in place
-            __threadfence_system();
-        }
-    }
+    if (S.host_count) report_count(S);
 }
 
 

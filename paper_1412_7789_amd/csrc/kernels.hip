@@ -129,7 +129,6 @@ FilteredGeom filtered_geom(const ac_automaton *a, const uint8_t *text, int64_t n
     F.V = F.mis + n;
     const int64_t CH = int64_t(cfg.segs) * kSegBytes;
     F.n_chunks = (F.V + CH - 1) / CH;
-    F.c_lo = F.mis > 0 ? 1 : 0;
     F.c_hi = F.V >= 16 ? (F.V - 16) / CH : 0;
     F.filter = a->dfilter[stride_set(cfg.stride) * kNumFilterKinds + cfg.filter - 1];
     if (cfg.stride > 1) {
@@ -139,8 +138,7 @@ FilteredGeom filtered_geom(const ac_automaton *a, const uint8_t *text, int64_t n
         F.win_nb = a->host.win[ws].bits - 2;
     }
     const int waves = cfg.block / kWave;
-    const int64_t interior = std::max<int64_t>(0, F.c_hi - F.c_lo);
-    const int64_t want = (std::max<int64_t>(interior, 1) + waves - 1) / waves;
+    const int64_t want = (F.n_chunks + waves - 1) / waves;
     const int64_t cap = int64_t(a->cu_count) * cfg.grid_per_cu;
     G.grid = std::max<int64_t>(1, std::min(want, cap));
     G.waves = G.grid * waves;
@@ -292,8 +290,7 @@ int64_t widest_scan_regions(int cu_count, int64_t lds_per_cu) {
 }
 
 int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &cfg, const HitScratch &hs,
-                hipStream_t stream, std::string &err, const KernelTiming *timing, int64_t *blocks) {
-    if (blocks) *blocks = 0;
+                hipStream_t stream, std::string &err, const KernelTiming *timing) {
     const KernelTiming none;
     const KernelTiming &T = timing ? *timing : none;
     if (S.n <= 0) return AC_OK;
@@ -308,9 +305,8 @@ int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &cfg, 
         }
         F.hits = hs.hits;
         F.hit_cap = hs.cap;
-        const int64_t interior = std::max<int64_t>(0, F.c_hi - F.c_lo);
         // queue entries hold (slot << 12 | position): a block's slots must fit 20 bits
-        if (interior / G.grid + 2 * (cfg.block / kWave) >= (int64_t(1) << 20)) {
+        if (F.n_chunks / G.grid + 2 * (cfg.block / kWave) >= (int64_t(1) << 20)) {
             err = "text too large for one launch";
             return AC_EINVAL;
         }
@@ -322,7 +318,6 @@ int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &cfg, 
         void *fargs[] = {&KA};
         e = launch_timed(reinterpret_cast<const void *>(fn), dim3(unsigned(G.grid)), dim3(unsigned(cfg.block)), fargs, 0,
                          stream, T.scan0, T.scan1);
-        if (blocks && e == hipSuccess) *blocks = G.grid;
         if (e != hipSuccess) { err = std::string("scan launch: ") + hipGetErrorString(e); return AC_EHIP; }
     } else if (cfg.policy == AC_POLICY_DIRECT) {
         if (S.text_off) { err = "direct policy does not scan batches"; return AC_ENOTSUP; }

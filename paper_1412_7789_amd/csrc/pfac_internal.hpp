@@ -50,6 +50,16 @@ inline FilterGeom filter_geom(int kind) {
     }
 }
 constexpr int kNumFilterKinds = 6;
+// The second word of a count report.  It ties the count to the call, so the
+// two words need no order between them: a new tag beside an old count (or the
+// other way round) passes for the call's report only if both counts are equal
+// (or the count is the new one).
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr unsigned long long report_tag(unsigned long long count, unsigned long long seq) {
+    return seq ^ (count * 0x9E3779B97F4A7C15ull);
+}
 constexpr uint32_t kFilterMul2 = 0x7FEB35u;       // hash of the second map of AC_FILTER_DUAL19
 // Filter sets, kNumFilterKinds maps each: stride 1 tests every offset against
 // the keywords' K-byte prefixes; stride 2 tests the windows starting at every
@@ -162,13 +172,12 @@ struct ScanArgs {
     unsigned long long *count;
     unsigned long long count_base; // value of *count before this scan: match i goes to index i - base
     int64_t *per_text;             // batch only, may be null
-    // Optional report of the count to the host: the streaming kernel's last
-    // block to finish (*done reaching done_base + blocks) stores *count into
-    // host_count[0], a pinned host word, and then host_seq into host_count[1],
-    // so the host can wait for the word instead of the stream.
-    // host_count == nullptr: no report.
+    // Optional report of the count to the host: the scan's last block to
+    // finish stores *count and report_tag(*count, host_seq) into the two
+    // pinned words host_count, so the host can wait for them instead of the
+    // stream.  host_count == nullptr: no report.  *done counts the finished
+    // blocks (zero between scans).
     unsigned long long *done;
-    unsigned long long done_base;
     unsigned long long *host_count;
     unsigned long long host_seq;
 };
@@ -232,11 +241,8 @@ int64_t widest_scan_regions(int cu_count, int64_t lds_per_cu);
 struct KernelTiming {
     hipEvent_t scan0 = nullptr, scan1 = nullptr;
 };
-// *blocks (if given) receives the number of blocks of the scan kernel (0
-// when nothing was launched).
 int launch_scan(const ac_automaton *a, const ScanArgs &args, const ac_launch &cfg, const HitScratch &hs,
-                hipStream_t stream, std::string &err, const KernelTiming *timing = nullptr,
-                int64_t *blocks = nullptr);
+                hipStream_t stream, std::string &err, const KernelTiming *timing = nullptr);
 int launch_zero(unsigned long long *count, unsigned long long *done, int64_t *per_text, int32_t n_texts,
                 hipStream_t stream, std::string &err);
 void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &cfg);

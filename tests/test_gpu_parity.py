@@ -498,3 +498,24 @@ def test_windows_shared_nested_and_cut(stride, segs):
         tid, off, pid, per = (x.cpu().numpy() for x in a.match_batch(d, b, launch=cfg, capacity=len(want_key)))
         assert np.array_equal(key(tid, off, pid), want_key), f"batch, filter {f}"
         assert np.array_equal(per, [len(w[0]) for w in want])
+
+
+@pytest.mark.parametrize("kws", [[b"a"], [b"ab", b"bab"], [b"abca", b"bcab"], [b"abcab"], [b"abcabca"],
+                                 [b"abcabcab", b"cabcabcabc"]],
+                         ids=["K1", "K2", "K3", "five", "seven", "eight"])
+def test_text_inside_a_buffer_of_keywords(kws):
+    """A text whose buffer goes on with the keywords' bytes on both sides: the
+    granules that hold its ends are read whole, and nothing that starts before
+    the text or runs past it may be reported.  Every alignment of the start,
+    lengths around the ends of words, segments and chunks, each stride and
+    segment count the keywords allow."""
+    buf = np.frombuffer(b"abc" * 3000, dtype=np.uint8)
+    d = torch.from_numpy(buf.copy()).cuda()
+    a = pf.Automaton(kws)
+    lens = [1, 2, 3, 4, 5, 7, 8, 15, 16, 17, 33, 1008, 1023, 1024, 1040, 2047, 2049, 4095, 4096, 4113]
+    for o in range(16):
+        for n in lens:
+            exp = oracle_match(kws, buf[o:o + n])
+            for stride, segs in ((0, 0), (1, 2), (2, 1), (2, 4), (4, 1), (4, 2)):
+                off, pid = a.match(d[o:o + n], capacity=2 * n, launch=pf.launch_config(policy=1, stride=stride, segs=segs))
+                assert_same((off.cpu().numpy(), pid.cpu().numpy()), exp, f"start {o} n {n} stride {stride} segs {segs}")
