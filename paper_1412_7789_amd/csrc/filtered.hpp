@@ -135,8 +135,15 @@ struct MatchStage {
     unsigned long long base;
 };
 
-__device__ __forceinline__ void emit_staged(const DevAut &A, const ScanArgs &S, MatchStage *st, int64_t off,
-                                            int32_t tid, int32_t s) {
+// One more match of text tid: in the block's LDS counters when it has them,
+// else in global memory.
+__device__ __forceinline__ void count_text(const ScanArgs &S, uint32_t *lcnt, int32_t tid) {
+    if (lcnt) atomicAdd(&lcnt[tid], 1u);
+    else if (S.per_text) atomicAdd(reinterpret_cast<unsigned long long *>(S.per_text + tid), 1ull);
+}
+
+__device__ __forceinline__ void emit_staged(const DevAut &A, const ScanArgs &S, MatchStage *st, uint32_t *lcnt,
+                                            int64_t off, int32_t tid, int32_t s) {
     const int32_t k0 = A.out_off[s], k1 = A.out_off[s + 1];
     for (int32_t k = k0; k < k1; ++k) {
         const int32_t i = atomicAdd(&st->n, 1);
@@ -144,7 +151,6 @@ __device__ __forceinline__ void emit_staged(const DevAut &A, const ScanArgs &S, 
             st->off[i] = off;
             st->pid[i] = A.out_pid[k];
             st->tid[i] = tid;
-            if (S.per_text) atomicAdd(reinterpret_cast<unsigned long long *>(S.per_text + tid), 1ull);
         } else {
             // stage full: this id goes out directly (one atomic)
             const unsigned long long idx = atomicAdd(S.count, 1ull) - S.count_base;
@@ -153,13 +159,14 @@ __device__ __forceinline__ void emit_staged(const DevAut &A, const ScanArgs &S, 
                 S.out_pid[idx] = A.out_pid[k];
                 if (S.out_tid) S.out_tid[idx] = tid;
             }
-            if (S.per_text) atomicAdd(reinterpret_cast<unsigned long long *>(S.per_text + tid), 1ull);
         }
+        count_text(S, lcnt, tid);
     }
 }
 
 // One keyword id `pid` found at `off` (the caller knows it is the state's only one).
-__device__ __forceinline__ void emit_one(const ScanArgs &S, MatchStage *st, int64_t off, int32_t tid, int32_t pid) {
+__device__ __forceinline__ void emit_one(const ScanArgs &S, MatchStage *st, uint32_t *lcnt, int64_t off, int32_t tid,
+                                         int32_t pid) {
     int32_t i = kStageCap;
     if (st) i = atomicAdd(&st->n, 1);
     if (i < kStageCap) {
@@ -174,13 +181,17 @@ __device__ __forceinline__ void emit_one(const ScanArgs &S, MatchStage *st, int6
             if (S.out_tid) S.out_tid[idx] = tid;
         }
     }
-    if (S.per_text) atomicAdd(reinterpret_cast<unsigned long long *>(S.per_text + tid), 1ull);
+    count_text(S, lcnt, tid);
 }
 
 // Called by every thread of the block once all its walks are done.
-__device__ __forceinline__ void flush_stage(const ScanArgs &S, MatchStage *st) {
+__device__ __forceinline__ void flush_stage(const ScanArgs &S, MatchStage *st, const uint32_t *lcnt) {
     __syncthreads();
     const int32_t n = imin(st->n, kStageCap);
+    if (lcnt)
+        for (int32_t i = threadIdx.x; i < S.n_texts; i += blockDim.x)
+            if (const uint32_t c = lcnt[i])
+                atomicAdd(reinterpret_cast<unsigned long long *>(S.per_text + i), static_cast<unsigned long long>(c));
     if (threadIdx.x == 0) st->base = n ? atomicAdd(S.count, static_cast<unsigned long long>(n)) - S.count_base : 0ull;
     __syncthreads();
     for (int32_t i = threadIdx.x; i < n; i += blockDim.x) {
@@ -335,8 +346,8 @@ __device__ __forceinline__ bool equal_bytes(const uint8_t *t, const uint8_t *k, 
     auto text16 = [&](const uint8_t *p) __attribute__((always_inline)) {
         return reinterpret_cast<uintptr_t>(p) + 16u <= tend ? load16_any(p) : load16_clamped(p, tlast);
     };
-    const u32x4 t0 = text16(t), t1 = text16(t + 16);
     const u32x4 k0 = load16_any(k), k1 = load16_any(k + 16);
+    const u32x4 t0 = text16(t), t1 = text16(t + 16);
     uint32_t d = diff16(t0, k0, n) | diff16(t1, k1, n - 16);
     for (int i = 32; d == 0 && i < n; i += 16) d = diff16(text16(t + i), load16_any(k + i), n - i);
     return d == 0;
@@ -491,29 +502,22 @@ __device__ __forceinline__ int window_slot(LoadBucket load, int nb, uint32_t x) 
 }
 
 // Everything the window at offset w (found in `slot` of the window table)
-// belongs to: each of its entries fixes the offset o that the window's path
-// starts from and the bytes to compare there, either a whole keyword or the
-// path down to a state from which a walk goes on.  locate(o, tstart, end,
-// tid) gives the text holding o; ids(o - tstart, tid, state) and one(o -
-// tstart, tid, pid) report.
-template <typename Locate, typename Ids, typename One>
+// belongs to, inside the text [tstart, end) that holds w: each of its entries
+// fixes the offset o = w - position that the window's path starts from and the
+// bytes to compare there, either a whole keyword or the path down to a state
+// from which a walk goes on.  ids(o, state) and one(o, pid) report.
+template <typename Ids, typename One>
 __device__ __forceinline__ void walk_window(const DevAut &A, const ScanArgs &S, const int4 *entries, int slot,
-                                            int64_t w, Locate &&locate, Ids &&ids, One &&one) {
+                                            int64_t w, int64_t tstart, int64_t end, Ids &&ids, One &&one) {
     while (true) {
         const int4 e = entries[slot];
         const int64_t o = w - (e.w & 7);
-        if (o >= 0 && o + e.y <= S.n) {
-            int64_t tstart, end;
-            int32_t tid;
-            locate(o, tstart, end, tid);
-            if (o + e.y <= end && equal_bytes(S.text + o, A.kw_bytes + e.x, e.y, S.text, S.n)) {
-                if (uint32_t(e.w) & kWinGeneral)
-                    walk_below<false>(A, S, o, end, e.z, e.y, make_uint2(0u, 0u),
-                                      [&](int32_t st) { ids(o - tstart, tid, st); },
-                                      [&](int32_t pid) { one(o - tstart, tid, pid); });
-                else
-                    one(o - tstart, tid, e.z);
-            }
+        if (o >= tstart && o + e.y <= end && equal_bytes(S.text + o, A.kw_bytes + e.x, e.y, S.text, S.n)) {
+            if (uint32_t(e.w) & kWinGeneral)
+                walk_below<false>(A, S, o, end, e.z, e.y, make_uint2(0u, 0u), [&](int32_t st) { ids(o, st); },
+                                  [&](int32_t pid) { one(o, pid); });
+            else
+                one(o, e.z);
         }
         const uint32_t next = uint32_t(e.w) >> 4;
         if (next == 0) return;
@@ -1197,7 +1201,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 locate_text(S, nullptr, o, tstart, end, tid);
                 walk_rest<false>(A, S, o, end, kv.y, make_uint2(0u, 0u),
                                  [&](int32_t st) { emit(A, S, o - tstart, tid, st); },
-                                 [&](int32_t pid) { emit_one(S, nullptr, o - tstart, tid, pid); });
+                                 [&](int32_t pid) { emit_one(S, nullptr, nullptr, o - tstart, tid, pid); });
             }
         };
         auto drain_walk_windows = [&](int take) __attribute__((always_inline)) {
@@ -1205,10 +1209,13 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             if (int(lane) >= take) return;
             const int slot = find_window(pt_lds, sptab, F.win_keys, F.win_nb, e.y);
             if (slot < 0) return;
-            walk_window(A, S, F.win_entries, slot, offset_of(e.x) + STRIDE,
-                        [&](int64_t o, int64_t &ts, int64_t &te, int32_t &tid) { locate_text(S, nullptr, o, ts, te, tid); },
-                        [&](int64_t off, int32_t tid, int32_t st) { emit(A, S, off, tid, st); },
-                        [&](int64_t off, int32_t tid, int32_t pid) { emit_one(S, nullptr, off, tid, pid); });
+            const int64_t w = offset_of(e.x) + STRIDE;
+            int64_t tstart, end;
+            int32_t tid;
+            locate_text(S, nullptr, w, tstart, end, tid);
+            walk_window(A, S, F.win_entries, slot, w, tstart, end,
+                        [&](int64_t o, int32_t st) { emit(A, S, o - tstart, tid, st); },
+                        [&](int64_t o, int32_t pid) { emit_one(S, nullptr, nullptr, o - tstart, tid, pid); });
         };
         // What is left of the wave's slots: cur first, with what its queueing
         // left (its text is read again), then its successors.  A queue that
@@ -1283,7 +1290,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 q[2 + 2 * at] = ent;
                 q[3 + 2 * at] = uint32_t(pid);
             } else {
-                emit_one(S, nullptr, o, 0, pid);
+                emit_one(S, nullptr, nullptr, o, 0, pid);
             }
         };
         for (int i = int(lane); WIN && i < hcount; i += kWave) {
@@ -1296,12 +1303,11 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             auto put = [&](int64_t o, int32_t pid) __attribute__((always_inline)) {
                 stage_one(rec.x + uint32_t(o - first), o, pid);
             };
-            walk_window(A, S, F.win_entries, int(rec.y), first + STRIDE,
-                        [&](int64_t, int64_t &ts, int64_t &te, int32_t &tid) { ts = 0; te = S.n; tid = 0; },
-                        [&](int64_t o, int32_t, int32_t st) {
+            walk_window(A, S, F.win_entries, int(rec.y), first + STRIDE, 0, S.n,
+                        [&](int64_t o, int32_t st) {
                             for (int32_t k = A.out_off[st], k1 = A.out_off[st + 1]; k < k1; ++k) put(o, A.out_pid[k]);
                         },
-                        [&](int64_t o, int32_t, int32_t pid) { put(o, pid); });
+                        put);
         }
         for (int i = int(lane); !WIN && i < hcount; i += kWave) {
             uint4 rec;
@@ -1385,6 +1391,14 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         static_assert(kLdsTexts >= 4096, "room for the text starts of a batch of 4096 texts");
         uint32_t *lds_off = FLOG2 >= 17 ? reinterpret_cast<uint32_t *>(sfilt + kStageEnd) : sptab;
         const uint32_t *loff = nullptr;
+        // Per-text counts are added up in LDS behind the starts, when both
+        // fit: the matches of a long text meet in every block, and atomics on
+        // one address pass at about 85 M/s.
+        uint32_t *lcnt = nullptr;
+        if (S.per_text && total > 0 && 2 * int64_t(S.n_texts) + 1 <= kLdsTexts) {
+            lcnt = lds_off + S.n_texts + 1;
+            for (int i = int(threadIdx.x); i < S.n_texts; i += int(blockDim.x)) lcnt[i] = 0u;
+        }
         if (total > 0 && S.n_texts < kLdsTexts && S.n < (int64_t(1) << 32)) {
             if (pre_ok) {
 #pragma unroll
@@ -1397,9 +1411,9 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 for (int i = int(threadIdx.x); i <= S.n_texts; i += int(blockDim.x))
                     lds_off[i] = uint32_t(S.text_off[i] - base0);
             }
-            __syncthreads();
             loff = lds_off;
         }
+        __syncthreads();
         for (int32_t i = int32_t(threadIdx.x); i < total; i += int32_t(blockDim.x)) {
             int j = 0;                               // wave (region) of flat index i
 #pragma unroll
@@ -1410,10 +1424,13 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 const uint2 rec = k < kLdsWinHits
                                       ? swhits[j * kLdsWinHits + k]
                                       : reinterpret_cast<const uint2 *>(F.hits + (r0 + j) * F.hit_cap)[k - kLdsWinHits];
-                walk_window(A, S, F.win_entries, int(rec.y), offset_of(rec.x) + STRIDE,
-                            [&](int64_t o, int64_t &ts, int64_t &te, int32_t &tid) { locate_text(S, loff, o, ts, te, tid); },
-                            [&](int64_t off, int32_t tid, int32_t s2) { emit_staged(A, S, st, off, tid, s2); },
-                            [&](int64_t off, int32_t tid, int32_t pid) { emit_one(S, st, off, tid, pid); });
+                const int64_t w0 = offset_of(rec.x) + STRIDE;
+                int64_t tstart, end;
+                int32_t tid;
+                locate_text(S, loff, w0, tstart, end, tid);
+                walk_window(A, S, F.win_entries, int(rec.y), w0, tstart, end,
+                            [&](int64_t o, int32_t s2) { emit_staged(A, S, st, lcnt, o - tstart, tid, s2); },
+                            [&](int64_t o, int32_t pid) { emit_one(S, st, lcnt, o - tstart, tid, pid); });
                 continue;
             }
             const uint4 rec = k < kLdsHits ? shits[j * kLdsHits + k] : F.hits[(r0 + j) * F.hit_cap + (k - kLdsHits)];
@@ -1422,10 +1439,10 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             int32_t tid;
             locate_text(S, loff, o, tstart, end, tid);
             walk_rest<true>(A, S, o, end, rec.y, make_uint2(rec.z, rec.w),
-                            [&](int32_t s2) { emit_staged(A, S, st, o - tstart, tid, s2); },
-                            [&](int32_t pid) { emit_one(S, st, o - tstart, tid, pid); });
+                            [&](int32_t s2) { emit_staged(A, S, st, lcnt, o - tstart, tid, s2); },
+                            [&](int32_t pid) { emit_one(S, st, lcnt, o - tstart, tid, pid); });
         }
-        flush_stage(S, st);
+        flush_stage(S, st, lcnt);
     }
 
     if (S.host_count) report_count(S);
