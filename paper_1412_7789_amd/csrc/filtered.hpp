@@ -600,6 +600,18 @@ __device__ __forceinline__ void load_chunk(const FilterLaunch &F, int64_t c, uns
     R.tail = __builtin_amdgcn_raw_buffer_load_b32(rsrc, int(CH), 0, 0);
 }
 
+// Segment j of a chunk alone.
+template <int SEGS>
+__device__ __forceinline__ void load_segment(const FilterLaunch &F, int64_t c, int j, unsigned lane, ChunkRegs<1> &R) {
+    constexpr int64_t CH = int64_t(SEGS) * kSegBytes;
+    const int records = c < F.c_hi ? int(CH + 16) : int(((F.V + 3) & ~int64_t(3)) - c * CH);
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(F.base + c * CH), short(0), records, kBufferFlags);
+    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(lane * 16u), j * kSegBytes, 0);
+    R.d[0][0] = q.x; R.d[0][1] = q.y; R.d[0][2] = q.z; R.d[0][3] = q.w;
+    R.tail = __builtin_amdgcn_raw_buffer_load_b32(rsrc, 0, (j + 1) * kSegBytes, 0);
+}
+
 // Candidate mask of one chunk: bit 16 j + s is set when offset s of the
 // lane's 16 bytes in segment j may start a keyword.
 //
@@ -929,25 +941,28 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         qlen -= take;
     };
     // The same for windows (WIN): a queue entry also carries the window's
-    // bytes, so that looking it up reads no text.  Filters and queues a chunk
-    // in groups of at most kGroup segments (more at once spill registers),
-    // from group g0 on; on a refusal `rest` and `rest_g` tell what is left.
-    // `only` (unless all ones) replaces group g0's mask.
-    constexpr int kGroup = SEGS < 2 ? 1 : 2;
+    // bytes, so that looking it up reads no text.  Filters and queues the
+    // segments held in R (of the chunk in slot k, the first of them segment
+    // `seg`) in groups of at most two (more at once spill registers).  On a
+    // refusal `rest` holds what is left of group rest_g; the groups after it
+    // are left whole.
     constexpr int kWin = 16 / STRIDE;    // windows per segment and lane
     uint2 *wq = reinterpret_cast<uint2 *>(q);
     int rest_g = 0;
-    auto queue_group = [&](unsigned m, const ChunkRegs<SEGS> &R, const uint32_t (&d4)[kGroup], auto j0, uint32_t k,
-                           unsigned &left, auto &&drain) __attribute__((always_inline)) {
+    // Queues the positive windows m (those of N segments from J0 on); false,
+    // leaving the rest in m, if `drain` refuses to run.
+    auto queue_windows = [&](unsigned &m, const auto &R, const auto &d4, auto j0, uint32_t at0,
+                             auto &&drain) __attribute__((always_inline)) {
+        constexpr int J0 = decltype(j0)::value;
+        constexpr int N = int(sizeof(d4) / 4);
         if (!uniform(m != 0)) return true;
 #pragma unroll
-        for (int i = 0; i < kGroup; ++i) {
-            constexpr int J0 = decltype(j0)::value;
+        for (int i = 0; i < N; ++i) {
             const uint32_t (&d)[4] = R.d[J0 + i];
             uint32_t mj = __builtin_amdgcn_ubfe(m, uint32_t(kWin * i), uint32_t(kWin));
             while (true) {
                 if (qlen >= kDrain && !drain(kDrain)) {
-                    left = mj << (kWin * i) | (m >> (kWin * (i + 1)) << (kWin * (i + 1)));
+                    m = mj << (kWin * i) | (m >> (kWin * (i + 1)) << (kWin * (i + 1)));
                     return false;
                 }
                 const unsigned long long act = __ballot(mj != 0);
@@ -965,34 +980,31 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                         x = pick(bit_mask(b, 1), hi, __builtin_amdgcn_alignbyte(hi, lo, 2u));
                     }
                     wq[qlen + int(rank_in(act))] =
-                        make_uint2((k << 12) | uint32_t((J0 + i) * kSegBytes + int(lane) * 16 + b), x);
+                        make_uint2(at0 + uint32_t((J0 + i) * kSegBytes + int(lane) * 16 + b), x);
                     mj &= mj - 1;
                 }
                 qlen += __popcll(act);
             }
         }
+        m = 0;
         return true;
     };
-    auto push_windows = [&](const ChunkRegs<SEGS> &R, uint32_t mul, uint32_t k, int g0, unsigned only,
+    auto push_windows = [&](const ChunkRegs<SEGS> &R, uint32_t mul, uint32_t k,
                             auto &&drain) __attribute__((always_inline)) {
+        constexpr int kGroup = SEGS < 2 ? 1 : 2;
         auto group = [&](auto g) __attribute__((always_inline)) {
             constexpr int G = decltype(g)::value;
-            if (G < g0) return true;
             uint32_t d4[kGroup];
             unsigned m = filter_windows<BITMAP, SEGS, FLOG2, STRIDE, DUAL, PAIR, G * kGroup, kGroup>(R, lane, sfilt, mul,
                                                                                                    d4);
-            if (G == g0) m &= only;
-            unsigned left = 0;
-            if (queue_group(m, R, d4, std::integral_constant<int, G * kGroup>{}, k, left, drain)) return true;
-            rest = left;
+            if (queue_windows(m, R, d4, std::integral_constant<int, G * kGroup>{}, k << 12, drain)) return true;
+            rest = m;
             rest_g = G;
             return false;
         };
         if (!group(std::integral_constant<int, 0>{})) return false;
-        if constexpr (SEGS / kGroup > 1)
+        if constexpr (SEGS == 4)
             if (!group(std::integral_constant<int, 1>{})) return false;
-        if constexpr (SEGS / kGroup > 2)
-            if (!group(std::integral_constant<int, 2>{}) || !group(std::integral_constant<int, 3>{})) return false;
         return true;
     };
     auto pop_window = [&](int take) __attribute__((always_inline)) {
@@ -1141,7 +1153,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             if (lane == 0 && nxt_ok) ahead = atomicAdd(&snext, 1u);
             bool pushed;
             if constexpr (WIN) {
-                pushed = push_windows(regs, mul, cur, 0, ~0u, drain_windows);
+                pushed = push_windows(regs, mul, cur, drain_windows);
             } else {
                 rest = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(regs, lane, sfilt, mul);
                 pushed = push(rest, cur, drain_store);
@@ -1218,44 +1230,52 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                         [&](int64_t o, int32_t pid) { emit_one(S, nullptr, nullptr, o - tstart, tid, pid); });
         };
         // What is left of the wave's slots: cur first, with what its queueing
-        // left (its text is read again), then its successors.  A queue that
-        // fills up is walked empty before its chunk goes on, so that the walk
-        // is in the code once.
+        // left (its text is read again), then its successors; with the window
+        // table one segment at a time, since a segment's registers stay live
+        // while the walks of a full queue run.
         auto full = [](int) __attribute__((always_inline)) { return false; };
         uint32_t sl = cur;
         bool ok = cur_ok, first = true;
         while (ok || qlen > 0) {
-            ChunkRegs<SEGS> r;
-            bool queued = !ok;        // nothing (more) of this chunk to queue
-            int g0 = 0;
-            unsigned only = ~0u;
-            unsigned long long m = 0;
-            if (ok) {
-                load_chunk<SEGS>(F, M.chunk(sl), lane, r);
-                if (first) {
-                    g0 = rest_g;
-                    only = unsigned(rest);
-                }
-                if constexpr (!WIN)
-                    m = first ? rest : filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(r, lane, sfilt, mul);
-            }
-            first = false;
-            while (true) {
-                if (!queued) {
+            for (int j = 0; j < (WIN ? SEGS : 1); ++j) {
+                bool queued = !ok;        // nothing (more) to queue
+                unsigned long long m = 0;
+                ChunkRegs<1> r1;
+                uint32_t d4[1];
+                unsigned mw = 0;
+                if (ok) {
                     if constexpr (WIN) {
-                        queued = push_windows(r, mul, sl, g0, only, full);
-                        g0 = rest_g;
-                        only = unsigned(rest);
+                        load_segment<SEGS>(F, M.chunk(sl), j, lane, r1);
+                        mw = filter_windows<BITMAP, 1, FLOG2, STRIDE, DUAL, PAIR, 0, 1>(r1, lane, sfilt, mul, d4);
+                        if (first) {
+                            const int g = SEGS < 2 ? j : j / 2;
+                            if (g < rest_g) mw = 0;
+                            if (g == rest_g) mw &= unsigned(rest) >> (SEGS < 2 ? 0 : kWin * (j & 1));
+                        }
+                    } else if (first) {
+                        m = rest;
                     } else {
-                        queued = push(m, sl, full);
+                        ChunkRegs<SEGS> r;
+                        load_chunk<SEGS>(F, M.chunk(sl), lane, r);
+                        m = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(r, lane, sfilt, mul);
                     }
                 }
-                while (qlen > 0) {
-                    if constexpr (WIN) drain_walk_windows(imin(qlen, kDrain));
-                    else drain_walk(imin(qlen, kDrain));
+                while (true) {
+                    if (!queued) {
+                        if constexpr (WIN)
+                            queued = queue_windows(mw, r1, d4, std::integral_constant<int, 0>{},
+                                                   (sl << 12) + uint32_t(j * kSegBytes), full);
+                        else
+                            queued = push(m, sl, full);
+                    }
+                    while (qlen > 0) {
+                        if constexpr (WIN) drain_walk_windows(imin(qlen, kDrain));
+                        else drain_walk(imin(qlen, kDrain));
+                    }
+                    if (queued) break;
                 }
-                if (queued) break;
             }
+            first = false;
             if (ok) {
                 sl = nxt;
                 ok = M.chunk(sl) < F.n_chunks;
