@@ -153,6 +153,12 @@ hipError_t launch_timed(const void *fn, dim3 grid, dim3 block, void **args, size
     return hipLaunchKernel(fn, grid, block, args, lds, stream);
 }
 
+// Most 4-byte windows for which the launch rules choose stride 4 on any text,
+// on texts under 512 MiB and on texts under 16 MiB, and stride 2 with the
+// 4-byte-window map.
+constexpr int32_t kPair4Keys = 32768, kPair4MidKeys = 100000, kPair4SmallKeys = 262144;
+constexpr int32_t kPair2Keys = 131072;
+
 std::mutex g_attr_mu;
 
 void allow_lds(const void *fn, int64_t bytes) {
@@ -169,49 +175,59 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
     if (batch) cfg.policy = AC_POLICY_FILTERED;
     if (cfg.policy == AC_POLICY_FILTERED) {
         // Sampling stride and map, chosen by the number of keys the map must
-        // hold.  A stride of s divides the probes by s but holds s windows per
-        // keyword and makes s candidates per positive; the dual map spends a
-        // second hash and LDS read per probe to square the false-positive
-        // rate, and the 4-byte-window map sets two bits (three at stride 2)
-        // of one word per key, which cuts false positives without a second
-        // LDS read.
-        // Measured on MI355X (ms per GiB, two segments): 1000 printable
-        // keywords 0.193 with the 4-byte-window map at stride 4, 0.214 with
-        // it at stride 2, 0.217 with one 2^20-bit map at stride 2, 0.269
-        // dual at stride 2; 20000 byte keywords (29958 4-byte windows at
-        // stride 2) 0.275 with the 4-byte-window map at stride 2, 0.284 dual
-        // at stride 2, 0.437 with the 4-byte-window map at stride 4, 0.567
-        // with one 2^20-bit map at stride 2 (the stride-2 map has since
-        // gained its third bit: 0.245).  On 256 MiB of random bytes, 20000
-        // keywords of 8..64 bytes (39999 windows): 0.071 ms with the
-        // 4-byte-window map at stride 2, 0.078 dual at stride 2, 0.099 with
-        // a 2^20-bit map at stride 1; 50000 such keywords (99998 windows):
-        // 0.126 with the 4-byte-window map at stride 2, 0.132 dual at stride
-        // 1, 0.149 dual at stride 2.
+        // hold and the text's length.  A stride of s divides the probes by s
+        // but holds s windows per keyword.  A positive costs one lookup in the
+        // exact window table (keywords of s + 4 bytes), so the longest stride
+        // wins until the map lets too many through.  Measured on MI355X (kernel
+        // us; stride/map/segments, maps by their AC_FILTER number):
+        //   1 GiB     1000 printable keywords (4000 windows at stride 4)
+        //             4/6/2 173, 2/6/4 > 178; 5000 byte keywords (20000)
+        //             4/6/2 163.3, 2/6/4 163.3; 20000 (80000) 4/6/2 218,
+        //             2/6/4 201; 50000 (200000) 4/6/2 427, 2/6/4 279
+        //   256 MiB   5000 47.8 and 51.3, 20000 61.2 and 61.0, 50000 117 and 79
+        //   64 MiB    5000 19.6 and 21.6 (2/6/2), 20000 22.9 and 24.3, 50000
+        //             37 and 28.5
+        //   4 MiB     50000 keywords 4/6/2 10.4, 2/6/2 10.5, stride 1 13.2;
+        //             5000 4/4/2 9.4, 4/6/2 9.6, 2/4/1 10.7; 1000 4/6/2 11.1,
+        //             4/4/2 11.2, 2/4/1 12.4
+        //   64 KiB    50000 keywords 4/6/1 8.1, stride 1 9.7
+        // So stride 4 up to kPair4Keys windows, up to kPair4MidKeys on texts
+        // short enough that fixed costs weigh as much as the stream, and up to
+        // kPair4SmallKeys on small ones, which see few positives in all; else
+        // stride 2 up to kPair2Keys, with the 4-byte-window map.  Small texts
+        // take the 64 KiB bit map while its keys are few: less to stage, and
+        // room for the window keys beside it.
         const bool auto_filter = cfg.filter < AC_FILTER_BYTES17 || cfg.filter > AC_FILTER_PAIR20;
         const bool auto_stride = cfg.stride != 1 && cfg.stride != 2 && cfg.stride != 4;
         const bool small_text = len < (int64_t(16) << 20);
         if (auto_stride) {
-            if (auto_filter && !small_text && P.pair4 && P.n_quads4 <= kPairMaxKeys) {
+            const int32_t most4 = small_text ? kPair4SmallKeys : len < (int64_t(512) << 20) ? kPair4MidKeys : kPair4Keys;
+            if (auto_filter && P.pair4 && P.n_quads4 <= most4) {
                 cfg.stride = 4;
-                cfg.filter = AC_FILTER_PAIR20;
+                cfg.filter = small_text && P.n_quads4 <= kPair4Keys ? AC_FILTER_BITS19 : AC_FILTER_PAIR20;
             } else if (P.sampled && (P.n_windows2 <= 65536 ||
-                                     (auto_filter && !small_text && P.pair2 && P.n_quads2 <= kPair2MaxKeys))) {
+                                     (auto_filter && !small_text && P.pair2 && P.n_quads2 <= kPair2Keys))) {
                 cfg.stride = 2;
-                if (auto_filter && !small_text && P.pair2 && P.n_quads2 <= kPair2MaxKeys) cfg.filter = AC_FILTER_PAIR20;
+                if (auto_filter && !small_text && P.pair2 && P.n_quads2 <= kPair2Keys) cfg.filter = AC_FILTER_PAIR20;
             } else {
                 cfg.stride = 1;
             }
         }
         if (cfg.stride == 4 && !P.sampled4) cfg.stride = P.sampled ? 2 : 1;
         if (cfg.stride == 2 && !P.sampled) cfg.stride = 1;
-        // the 4-byte-window map exists at stride 4 only
+        // the 4-byte-window map needs its stride's windows
         if (cfg.filter == AC_FILTER_PAIR20 && !((cfg.stride == 4 && P.pair4) || (cfg.stride == 2 && P.pair2)))
             cfg.filter = AC_FILTER_AUTO;
         if (cfg.filter < AC_FILTER_BYTES17 || cfg.filter > AC_FILTER_PAIR20) {
             // keys in the filter: prefixes (stride 1) or windows (strides 2, 4)
             const int64_t keys = cfg.stride == 4 ? P.n_windows4 : cfg.stride == 2 ? P.n_windows2 : P.n_prefixes;
-            if (small_text) cfg.filter = keys > 1500 ? AC_FILTER_BITS19 : AC_FILTER_BYTES16;
+            // A few prefixes at stride 1 keep the 64 KiB byte map, with the
+            // prefix table in LDS beside it, up to 128 MiB (200 keywords of 2
+            // to 8 bytes, 64 MiB: 40.0 us against 42.5 with the 128 KiB map;
+            // 64 keywords of 4 to 12 bytes: 64 MiB 32.0 both, 256 MiB 110.7
+            // and 109.4).
+            if (small_text || (cfg.stride == 1 && keys <= 1500 && len < (int64_t(128) << 20)))
+                cfg.filter = keys > 1500 ? AC_FILTER_BITS19 : AC_FILTER_BYTES16;
             else if (keys <= 1500) cfg.filter = AC_FILTER_BYTES17;
             else if (keys <= 8192) cfg.filter = AC_FILTER_BITS20;
             else if (cfg.stride == 2 || keys > 20000) cfg.filter = AC_FILTER_DUAL19;
@@ -226,22 +242,21 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
             g = filter_geom(cfg.filter);
         }
         if (cfg.block != 256 && cfg.block != 512 && cfg.block != 1024) cfg.block = 1024;
-        // Texts under 32 MiB take one segment per wave step, which spreads
-        // them over more waves (measured on MI355X: a 1 MiB scan in 11 us
-        // instead of 19 with four segments).  Above that, two (1 GiB on
-        // MI355X: 1000 keywords, 4-byte-window map at stride 4, 0.192 ms at
-        // two and 0.200 at four; the dual map's four-segment kernel spills
-        // registers), except for the 4-byte-window map at stride 2 with up
-        // to 65,536 windows on texts of 256 MiB and more, where four halve
-        // the per-step work of a filter-bound loop with few drains (20000
-        // byte keywords, 29974 windows: 1 GiB 0.221 ms at four and 0.241 at
-        // two, 256 MiB 0.070 and 0.075; 20000 keywords of 8..64 bytes, 39999
-        // windows: 1 GiB 0.234 and 0.252; 50000 such keywords, 99998
-        // windows, whose many drains favour two: 0.625 and 0.597).
+        // One segment per wave step for the shortest texts, which spreads
+        // them over more waves, two above 3 MiB (2 MiB at stride 1, whose
+        // filter takes longer than a load): 1000 keywords, 4/6 (us): 512 KiB
+        // 9.0 with one, 9.6 with two, 2 MiB 10.2 and 9.9, 3 MiB 10.9 and 10.3,
+        // 4 MiB 12.4 and 11.1; 50000 keywords, 2 MiB 9.2 and 9.7; 200 short
+        // keywords at stride 1, 1 MiB 10.8 and 11.4, 2 MiB 12.6 and 11.9, 4
+        // MiB 15.6 and 13.8.  Four for the 4-byte-window map at stride 2 on
+        // texts of 256 MiB and more, where they halve the per-step work of a
+        // filter-bound loop (20000 byte keywords, 1 GiB: 197 with four, 214
+        // with two; 50000, 256 MiB 79.3 and 80.8, 1 GiB 279 and 293); with the
+        // 4-byte-window map at stride 4 four are slower (1000 keywords, 1 GiB:
+        // 180 and 173).
         if (cfg.segs != 1 && cfg.segs != 2 && cfg.segs != 4) {
-            cfg.segs = len < (int64_t(32) << 20) ? 1 : 2;
-            if (cfg.filter == AC_FILTER_PAIR20 && cfg.stride == 2 && P.n_quads2 <= 65536 && len >= (int64_t(256) << 20))
-                cfg.segs = 4;
+            cfg.segs = len < (int64_t(cfg.stride == 1 ? 2 : 3) << 20) ? 1 : 2;
+            if (cfg.filter == AC_FILTER_PAIR20 && cfg.stride == 2 && len >= (int64_t(256) << 20)) cfg.segs = 4;
         }
         const int64_t fit = std::max<int64_t>(1, a->lds_per_cu / filtered_lds(g));
         if (cfg.grid_per_cu <= 0 || cfg.grid_per_cu > fit) cfg.grid_per_cu = int32_t(fit);
