@@ -159,8 +159,9 @@ int64_t ac_match_ex(const ac_automaton *a, const uint8_t *d_text, int64_t len,
 /*
  * Asynchronous form: enqueues the scan on `stream` and writes the match count
  * to d_count (device int64) without synchronising; returns AC_OK or an error.
- * It clears d_count with a kernel (no memset).  Only the first call on a
- * stream allocates (the stream's scratch, sized for any text); after one
+ * The filtered scan's last block stores the count at its end (the direct policy
+ * and an empty text clear d_count with a kernel first; no memset).  Only the
+ * first call on a stream allocates (the stream's scratch, sized for any text); after one
  * call on the stream it may be captured in a HIP graph.  Replays of captured
  * scans that share a stream's scratch must not overlap.
  */

@@ -177,6 +177,10 @@ struct ScanArgs {
     // pinned words host_count, so the host can wait for them instead of the
     // stream.  host_count == nullptr: no report.  *done counts the finished
     // blocks (zero between scans).
+    // dev_count (asynchronous scans): the last block stores the count there
+    // and leaves *count at zero for the next scan, which then needs no
+    // clearing kernel before it.
+    unsigned long long *dev_count;
     unsigned long long *done;
     unsigned long long *host_count;
     unsigned long long host_seq;
@@ -219,11 +223,13 @@ void prefix_buckets(uint32_t x, uint32_t mul, int bits, uint32_t &b1, uint32_t &
 // Per-stream scratch of the filtered policy: one hit region per streaming
 // wave of the widest launch.
 struct HitScratch {
+    unsigned long long *words = nullptr;   // [kScanWords], zero between scans: finished blocks, [kScanCount] matches
     uint4 *hits = nullptr;         // [regions * cap]
     int64_t regions = 0;
     int32_t cap = 0;
 };
 constexpr int32_t kHitCap = 1024;
+constexpr int kScanCount = 16, kScanWords = 32;   // each word on a 128-byte line of its own
 
 // host_match.cpp: every (offset, keyword id) of text[0, n) found on host
 // threads (n_threads <= 0: chosen by length); writes up to cap of them and
