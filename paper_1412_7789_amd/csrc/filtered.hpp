@@ -104,8 +104,9 @@ __device__ __forceinline__ void write_through(T *p, T v) {
 __device__ __forceinline__ void put_out(const ScanArgs &S, unsigned long long idx, int64_t off, int32_t tid,
                                         int32_t pid) {
     if (idx >= static_cast<unsigned long long>(S.cap)) return;
-    write_through(S.out_off + idx, off);
-    write_through(S.out_pid + idx, pid);
+    const bool near = idx < static_cast<unsigned long long>(S.near_cap);
+    write_through((near ? S.near_off : S.out_off) + idx, off);
+    write_through((near ? S.near_pid : S.out_pid) + idx, pid);
     if (S.out_tid) write_through(S.out_tid + idx, tid);
 }
 

@@ -169,6 +169,11 @@ struct ScanArgs {
     int32_t *out_pid;
     int32_t *out_tid;              // batch only
     int64_t cap;                   // 0 = count only
+    // the first near_cap matches go to these arrays instead (pinned host
+    // memory of a caller that wants them there)
+    int64_t near_cap;
+    int64_t *near_off;
+    int32_t *near_pid;
     unsigned long long *count;
     unsigned long long count_base; // value of *count before this scan: match i goes to index i - base
     int64_t *per_text;             // batch only, may be null
