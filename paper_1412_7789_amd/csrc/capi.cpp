@@ -6,6 +6,7 @@
 #include <chrono>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -213,14 +214,18 @@ int upload(ac_automaton *a) {
         place(wkey[k]); place(went[k]);
     }
     a->dbytes = at;
-    std::vector<uint8_t> staging(size_t(at), 0);
-    auto copy = [&](const Sec &s) { if (s.bytes) std::memcpy(staging.data() + s.at, s.src, size_t(s.bytes)); };
+    std::unique_ptr<uint8_t[]> staging(new (std::nothrow) uint8_t[size_t(at)]);
+    if (!staging) return fail(AC_ENOMEM, "ac_build: out of host memory");
+    auto copy = [&](const Sec &s) {
+        if (s.bytes) std::memcpy(staging.get() + s.at, s.src, size_t(s.bytes));
+        std::memset(staging.get() + s.at + s.bytes, 0, size_t(pad256(std::max<int64_t>(s.bytes, 1)) - s.bytes));
+    };
     copy(cls); for (auto &f : filt) copy(f); copy(dense); copy(node); copy(label); copy(ooff); copy(opid);
     copy(ptab); copy(tail); copy(tinfo); copy(kwb); copy(kwo);
     for (int k = 0; k < 2; ++k) { copy(wkey[k]); copy(went[k]); }
     e = hipMalloc(&a->dmem, size_t(at));
     if (e != hipSuccess) { a->dmem = nullptr; return fail(AC_ENOMEM, std::string("hipMalloc(automaton): ") + hipGetErrorString(e)); }
-    e = hipMemcpy(a->dmem, staging.data(), size_t(at), hipMemcpyHostToDevice);
+    e = hipMemcpy(a->dmem, staging.get(), size_t(at), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail("hipMemcpy(automaton)", e);
     uint8_t *b = static_cast<uint8_t *>(a->dmem);
     DevAut &D = a->dev;

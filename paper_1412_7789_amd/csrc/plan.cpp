@@ -83,6 +83,23 @@ bool build_cuckoo(const std::vector<std::pair<uint32_t, uint32_t>> &items, int b
     return true;
 }
 
+// Sorts (window << 32 | state) pairs, given in the order of their states, by
+// window: a radix sort of three 11-bit digits once there are many.
+void sort_by_window(std::vector<uint64_t> &w) {
+    if (w.size() < (1 << 14)) {
+        std::sort(w.begin(), w.end());
+        return;
+    }
+    std::vector<uint64_t> to(w.size());
+    for (int shift = 32; shift < 64; shift += 11) {
+        uint32_t at[2049] = {};
+        for (uint64_t v : w) ++at[(v >> shift & 2047) + 1];
+        for (int d = 0; d < 2048; ++d) at[d + 1] += at[d];
+        for (uint64_t v : w) to[at[v >> shift & 2047]++] = v;
+        w.swap(to);
+    }
+}
+
 // Builds the exact window table of one stride from (window, state) pairs
 // sorted by window; entry_of(state) gives the state's entry without its link.
 template <typename EntryOf>
@@ -98,32 +115,35 @@ void build_windows(const std::vector<uint64_t> &pairs, EntryOf &&entry_of, Windo
     for (;; ++bits) {
         const int nb = bits - 2;
         slot.assign(size_t(1) << bits, kFree);
+        W.keys.resize(size_t(1) << bits);
         uint32_t rng = 0x2545F491u;
         bool placed = true;
         for (size_t k = 0; k < n && placed; ++k) {
-            uint32_t item = uint32_t(k), from = kFree;
+            uint32_t item = uint32_t(k), key = uint32_t(pairs[first[k]] >> 32), from = kFree;
             placed = false;
             for (int kick = 0; kick < 2000 && !placed; ++kick) {
                 uint32_t b[2];
-                window_buckets(uint32_t(pairs[first[item]] >> 32), nb, b[0], b[1]);
+                window_buckets(key, nb, b[0], b[1]);
                 for (uint32_t c : b)
                     for (uint32_t j = 0; j < 4 && !placed; ++j)
                         if (slot[size_t(c) * 4 + j] == kFree) {
                             slot[size_t(c) * 4 + j] = item;
+                            W.keys[size_t(c) * 4 + j] = key;
                             placed = true;
                         }
                 if (placed) break;
                 // evict from the bucket the item did not come from
                 rng ^= rng << 13; rng ^= rng >> 17; rng ^= rng << 5;
                 from = b[0] == from ? b[1] : b[0];
-                std::swap(item, slot[size_t(from) * 4 + (rng & 3u)]);
+                const size_t at = size_t(from) * 4 + (rng & 3u);
+                std::swap(item, slot[at]);
+                std::swap(key, W.keys[at]);
             }
         }
         if (placed) break;
     }
     W.bits = bits;
     const int nb = bits - 2;
-    W.keys.resize(size_t(1) << bits);
     W.entries.assign(size_t(1) << bits, WindowEntry{0, 0, 0, 0u});
     for (uint32_t at = 0; at < uint32_t(slot.size()); ++at) {
         if (slot[at] == kFree) {
@@ -139,7 +159,6 @@ void build_windows(const std::vector<uint64_t> &pairs, EntryOf &&entry_of, Windo
             continue;
         }
         const size_t i0 = first[slot[at]];
-        W.keys[at] = uint32_t(pairs[i0] >> 32);
         WindowEntry e = entry_of(int32_t(uint32_t(pairs[i0])));
         size_t end = i0 + 1;
         while (end < pairs.size() && (pairs[end] >> 32) == (pairs[i0] >> 32)) ++end;
@@ -321,28 +340,44 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     }
 
     // ---- candidate filters over the first K bytes of every keyword --------
-    std::vector<uint32_t> prefixes(static_cast<size_t>(n));
-    for (int32_t p = 0; p < n; ++p) {
-        uint32_t x = 0;
-        for (int j = 0; j < P.K; ++j) x |= uint32_t(kw(p)[j]) << (8 * j);
-        prefixes[size_t(p)] = x;
+    // tail4[s] = the last four bytes of the path to s (little-endian, zeros
+    // before the root), for every state of depth 8 or less.  States of one
+    // depth are consecutive, and since every keyword has at least K bytes (or
+    // those its stride asks for), the states of a depth are exactly the
+    // distinct keyword prefixes of that length.
+    constexpr int kTailDepth = 8;
+    int32_t at_depth[kTailDepth + 2];         // first state of each depth (S when there is none)
+    std::vector<uint32_t> tail4(1, 0u);
+    at_depth[0] = 0;
+    for (int d = 1; d <= kTailDepth + 1; ++d) {
+        at_depth[d] = int32_t(tail4.size());
+        if (d > kTailDepth) break;
+        for (int32_t s = at_depth[d - 1]; s < at_depth[d]; ++s)
+            for (int32_t k = 0; k < P.n_child[size_t(s)]; ++k)
+                tail4.push_back(tail4[size_t(s)] >> 8 | uint32_t(P.label[size_t(P.first_child[size_t(s)] + k)]) << 24);
     }
-    std::sort(prefixes.begin(), prefixes.end());
-    prefixes.erase(std::unique(prefixes.begin(), prefixes.end()), prefixes.end());
+    std::vector<uint32_t> prefixes;
+    for (int32_t s = at_depth[P.K]; s < at_depth[P.K + 1]; ++s) prefixes.push_back(tail4[size_t(s)] >> (32 - 8 * P.K));
     P.n_prefixes = int32_t(prefixes.size());
     // windows for the sampled filters: bytes [j, j + 3) of each keyword for
     // j = 1, 2 (stride 2, keywords of 5 bytes or more) and j = 1 .. 4 (stride
-    // 4, 7 bytes or more)
+    // 4, 7 bytes or more), each once
     auto windows_of = [&](int count) {
         std::vector<uint32_t> w;
-        w.reserve(size_t(n) * size_t(count));
-        for (int32_t p = 0; p < n; ++p) {
-            const uint8_t *k = kw(p);
-            for (int j = 1; j <= count; ++j)
-                w.push_back(uint32_t(k[j]) | uint32_t(k[j + 1]) << 8 | uint32_t(k[j + 2]) << 16);
+        const int32_t s0 = at_depth[4], s1 = at_depth[count + 4];
+        if (s1 - s0 < (1 << 15)) {
+            for (int32_t s = s0; s < s1; ++s) w.push_back(tail4[size_t(s)] >> 8);
+            std::sort(w.begin(), w.end());
+            w.erase(std::unique(w.begin(), w.end()), w.end());
+            return w;
         }
-        std::sort(w.begin(), w.end());
-        w.erase(std::unique(w.begin(), w.end()), w.end());
+        std::vector<uint64_t> seen(size_t(1) << 18, 0);
+        for (int32_t s = s0; s < s1; ++s) {
+            const uint32_t x = tail4[size_t(s)] >> 8;
+            uint64_t &word = seen[x >> 6];
+            if (!(word >> (x & 63) & 1)) w.push_back(x);
+            word |= uint64_t(1) << (x & 63);
+        }
         return w;
     };
     P.sampled = P.K == 3 && P.min_len >= 5;
@@ -353,33 +388,24 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     P.n_windows4 = int32_t(windows4.size());
     // 4-byte windows at positions 1 .. count (keywords of count + 4 bytes or
     // more), with the states whose paths end with them: (window << 32 | state)
-    // for every state of depth 5 .. count + 4, sorted.  rep[s] = a keyword
-    // whose path passes through s down to a leaf.
-    std::vector<int32_t> rep(size_t(S), -1);
-    for (int32_t s = S - 1; s >= 0; --s)
-        rep[size_t(s)] = P.n_child[size_t(s)] > 0 ? rep[size_t(P.first_child[size_t(s)])]
-                                                  : P.out_pid[size_t(P.out_off[size_t(s)])];
-    auto quads_of = [&](int count) {
-        std::vector<uint64_t> w;
-        for (int32_t s = 0; s < S && P.depth[size_t(s)] <= count + 4; ++s) {
-            const int32_t j = P.depth[size_t(s)] - 4;
-            if (j < 1) continue;
-            const uint8_t *k = kw(rep[size_t(s)]) + j;
-            const uint32_t x = uint32_t(k[0]) | uint32_t(k[1]) << 8 | uint32_t(k[2]) << 16 | uint32_t(k[3]) << 24;
-            w.push_back(uint64_t(x) << 32 | uint32_t(s));
-        }
-        std::sort(w.begin(), w.end());
-        return w;
-    };
+    // for every state of depth 5 .. count + 4, sorted.
+    P.pair2 = P.K == 3 && P.min_len >= 6;
+    P.pair4 = P.K == 3 && P.min_len >= 8;
+    std::vector<uint64_t> quads2, quads4;
+    if (P.pair2) {
+        std::vector<uint64_t> &w = P.pair4 ? quads4 : quads2;
+        for (int32_t s = at_depth[5]; s < at_depth[P.pair4 ? 9 : 7]; ++s)
+            w.push_back(uint64_t(tail4[size_t(s)]) << 32 | uint32_t(s));
+        sort_by_window(w);
+        if (P.pair4)
+            for (uint64_t q : quads4)
+                if (int32_t(uint32_t(q)) < at_depth[7]) quads2.push_back(q);
+    }
     auto distinct = [](const std::vector<uint64_t> &w) {
         int32_t c = 0;
         for (size_t i = 0; i < w.size(); ++i) c += i == 0 || (w[i] >> 32) != (w[i - 1] >> 32);
         return c;
     };
-    P.pair2 = P.K == 3 && P.min_len >= 6;
-    P.pair4 = P.K == 3 && P.min_len >= 8;
-    const std::vector<uint64_t> quads2 = P.pair2 ? quads_of(2) : std::vector<uint64_t>();
-    const std::vector<uint64_t> quads4 = P.pair4 ? quads_of(4) : std::vector<uint64_t>();
     P.n_quads2 = distinct(quads2);
     P.n_quads4 = distinct(quads4);
     // A key x with hash h = x * mul (mod 2^32) owns bit h mod 32 of word (or
@@ -445,22 +471,8 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     {
         std::vector<std::pair<uint32_t, uint32_t>> items;   // (key, value), one per prefix
         items.reserve(size_t(P.n_prefixes));
-        std::vector<uint32_t> seen;
-        for (int32_t p = 0; p < n; ++p) {
-            uint32_t x = 0;
-            for (int j = 0; j < P.K; ++j) x |= uint32_t(kw(p)[j]) << (8 * j);
-            seen.push_back(x);
-        }
-        std::sort(seen.begin(), seen.end());
-        seen.erase(std::unique(seen.begin(), seen.end()), seen.end());
-        for (uint32_t x : seen) {
-            int32_t s = 0;   // follow the trie for K bytes
-            for (int j = 0; j < P.K; ++j) {
-                const uint8_t b = uint8_t(x >> (8 * j));
-                int32_t lo = P.first_child[size_t(s)], hi = lo + P.n_child[size_t(s)];
-                while (lo < hi && P.label[size_t(lo)] != b) ++lo;
-                s = lo;
-            }
+        for (int32_t s = at_depth[P.K]; s < at_depth[P.K + 1]; ++s) {
+            const uint32_t x = tail4[size_t(s)] >> (32 - 8 * P.K);
             uint32_t key = x, val = uint32_t(s) | (is_final(s) ? 0x80000000u : 0u);
             if (P.n_child[size_t(s)] == 1) {
                 key |= uint32_t(P.label[size_t(P.first_child[size_t(s)])]) << 24;
@@ -478,25 +490,26 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     // tail[s] = leaf l when every state from s down to l has one child and no
     // state strictly between s and l ends a keyword; the remaining bytes can
     // then be compared with the leaf's keyword in one pass.  -1 otherwise.
+    // Unary chains that do not end at a leaf: chain[s] = the first state
+    // below s that ends a keyword or has other than one child, when s has
+    // one child (else -1).  rep[s] = a keyword whose path passes through s
+    // down to a leaf.
     P.tail.assign(size_t(S), -1);
+    std::vector<int32_t> chain(size_t(S), -1), rep(size_t(S), -1);
     for (int32_t s = S - 1; s >= 0; --s) {
         const int32_t nc = P.n_child[size_t(s)];
         if (nc == 0) {
             P.tail[size_t(s)] = s;
-        } else if (nc == 1) {
-            const int32_t c = P.first_child[size_t(s)];
-            if (P.n_child[size_t(c)] == 0) P.tail[size_t(s)] = c;
-            else if (!is_final(c)) P.tail[size_t(s)] = P.tail[size_t(c)];
+            rep[size_t(s)] = P.out_pid[size_t(P.out_off[size_t(s)])];
+            continue;
         }
-    }
-    // Unary chains that do not end at a leaf: chain[s] = the first state
-    // below s that ends a keyword or has other than one child, when s has
-    // one child (else -1).
-    std::vector<int32_t> chain(size_t(S), -1);
-    for (int32_t s = S - 1; s >= 0; --s) {
-        if (P.n_child[size_t(s)] == 1) {
-            const int32_t c = P.first_child[size_t(s)];
-            chain[size_t(s)] = (is_final(c) || P.n_child[size_t(c)] != 1) ? c : chain[size_t(c)];
+        const int32_t c = P.first_child[size_t(s)];
+        rep[size_t(s)] = rep[size_t(c)];
+        if (nc == 1) {
+            const bool fin = is_final(c);
+            if (P.n_child[size_t(c)] == 0) P.tail[size_t(s)] = c;
+            else if (!fin) P.tail[size_t(s)] = P.tail[size_t(c)];
+            chain[size_t(s)] = (fin || P.n_child[size_t(c)] != 1) ? c : chain[size_t(c)];
         }
     }
     // per state, everything one step of a walk needs in one 16-byte record:
@@ -540,7 +553,8 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     // stride + 4 bytes), so the path down to it is compared as a whole: with
     // its keyword, when the rest is forced down to a leaf with one keyword
     // (and none ends on the way), else down to the state, where a walk goes on.
-    auto entry_of = [&](int32_t s) {
+    std::vector<WindowEntry> entry;           // of the states from at_depth[5] on, in their order
+    for (int32_t s = at_depth[5]; s < at_depth[P.pair4 ? 9 : 7] && P.pair2; ++s) {
         const int32_t d = P.depth[size_t(s)], l = P.tail[size_t(s)];
         const int32_t p = rep[size_t(s)];
         WindowEntry e{int32_t(offsets[p] - offsets[0]), d, s, uint32_t(d - 4) | kWinGeneral};
@@ -549,8 +563,9 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
             e.what = P.out_pid[size_t(P.out_off[size_t(l)])];
             e.link = uint32_t(d - 4);
         }
-        return e;
-    };
+        entry.push_back(e);
+    }
+    auto entry_of = [&](int32_t s) { return entry[size_t(s - at_depth[5])]; };
     if (P.pair2) build_windows(quads2, entry_of, P.win[window_set(2)]);
     if (P.pair4) build_windows(quads4, entry_of, P.win[window_set(4)]);
     // keyword bytes (for tail comparisons) with int32 offsets
