@@ -20,9 +20,7 @@ constexpr int kQueueCap = 256;   // per-wave candidate queue (entries)
 // global region.  Global stores in the streaming loop stall it (a later wait
 // for the next chunk's loads also waits for them, and the data registers a
 // store reads cannot be reused until it is done), so records stay on chip.
-constexpr int kLdsHits = 64;
-// the same with the window table, whose records are half as large
-constexpr int kLdsWinHits = 2 * kLdsHits;
+constexpr int kLdsHits = 128;
 constexpr int kDrain = 64;       // candidates taken per drain (1 per lane; 128 and 192 measured slower)
 // A queue holds fewer than kDrain entries before a push round and gains at
 // most one per lane in it, so its last entries are never used by the queue:
@@ -372,16 +370,14 @@ __device__ __forceinline__ int find_byte16(u32x4 v, int n, uint32_t b) {
 // transition row, with the byte's class loaded beside the record; a compact
 // state's children are consecutive states with sorted edge labels, found
 // among up to 16 labels read in one load.  The walk never compares or steps
-// past `end` (the end of o's text).  With REC, rb holds the 8 text bytes
-// after depth d0 (as captured by the streaming kernel), which pick
-// the first transitions without waiting for a load; the 32 bytes after it
+// past `end` (the end of o's text).  The 32 text bytes after depth d0
 // are loaded at the start, beside the first record, and serve the
-// first compare and the next transitions.  Every keyword starting at o and
+// first compare and the first transitions.  Every keyword starting at o and
 // ending at s or below is reported, through ids(state) for all keyword ids of
 // a final state or one(pid) for a single id.
-template <bool REC, typename Ids, typename One>
+template <typename Ids, typename One>
 __device__ __forceinline__ void walk_below(const DevAut &A, const ScanArgs &S, int64_t o, int64_t end, int32_t s,
-                                           int d0, uint2 rb, Ids &&ids, One &&one) {
+                                           int d0, Ids &&ids, One &&one) {
     if (o + d0 > end) return;         // the path ran into the next text of a batch
     // The 32 text bytes after the path, loaded beside the first walk
     // record: most walks compare them with a forced path's keyword and read
@@ -399,7 +395,6 @@ __device__ __forceinline__ void walk_below(const DevAut &A, const ScanArgs &S, i
     }
     auto byte_at = [&](int64_t j) -> uint32_t {   // text byte j (o + d0 <= j < end)
         const int64_t r = j - o - d0;
-        if (REC && r < 8) return r < 4 ? (rb.x >> (8 * r)) & 0xFFu : (rb.y >> (8 * (r - 4))) & 0xFFu;
         if (r < 32) {
             const u32x4 t = r < 16 ? t0 : t1;
             const int q = int(r & 15);
@@ -470,14 +465,6 @@ __device__ __forceinline__ void walk_below(const DevAut &A, const ScanArgs &S, i
     }
 }
 
-// The rest of the walk from offset o once the exact prefix table gave e =
-// {state at depth K | final bit}.
-template <bool REC, typename Ids, typename One>
-__device__ __forceinline__ void walk_rest(const DevAut &A, const ScanArgs &S, int64_t o, int64_t end, uint32_t e,
-                                          uint2 rb, Ids &&ids, One &&one) {
-    walk_below<REC>(A, S, o, end, int32_t(e & kStateMask), A.K, rb, ids, one);
-}
-
 // Slot of the 4-byte window x in the exact window table (2^nb buckets of four
 // keys), or -1.  Both buckets, 16 bytes each, are read at once.
 template <typename LoadBucket>
@@ -507,8 +494,8 @@ __device__ __forceinline__ void walk_window(const DevAut &A, const ScanArgs &S, 
         const int64_t o = w - (e.w & 7);
         if (o >= tstart && o + e.y <= end && equal_bytes(S.text + o, A.kw_bytes + e.x, e.y, S.text, S.n)) {
             if (uint32_t(e.w) & kWinGeneral)
-                walk_below<false>(A, S, o, end, e.z, e.y, make_uint2(0u, 0u), [&](int32_t st) { ids(o, st); },
-                                  [&](int32_t pid) { one(o, pid); });
+                walk_below(A, S, o, end, e.z, e.y, [&](int32_t st) { ids(o, st); },
+                           [&](int32_t pid) { one(o, pid); });
             else
                 one(o, e.z);
         }
@@ -525,10 +512,9 @@ struct FilterLaunch {
     int64_t n_chunks;        // ceil(V / chunk bytes)
     int64_t c_hi;            // chunks from c_hi on (two at most) reach past the text's last 16 bytes
     const uint8_t *filter;   // the filter map this launch stages in LDS
-    int32_t hit_cap;         // entries per wave region
-    uint4 *hits;             // [waves * hit_cap]: {slot << 12 | position, prefix-table value,
-                             //  the 8 text bytes after the prefix}; with the window
-                             //  table two {slot << 12 | position, table slot} in each
+    int32_t hit_cap;         // 16-byte entries per wave region
+    uint4 *hits;             // [waves * hit_cap]: two records in each, {slot << 12 | position,
+                             //  window-table slot or prefix-table value}
     const uint32_t *win_keys;   // exact window table (4 << win_nb keys)
     const int4 *win_entries;
     int32_t win_nb;             // log2(buckets)
@@ -605,8 +591,9 @@ __device__ __forceinline__ void load_segment(const FilterLaunch &F, int64_t c, i
     R.tail = __builtin_amdgcn_raw_buffer_load_b32(rsrc, 0, (j + 1) * kSegBytes, 0);
 }
 
-// Candidate mask of one chunk: bit 16 j + s is set when offset s of the
-// lane's 16 bytes in segment j may start a keyword.
+// Candidate mask of the N segments from J0 on: bit 16 i + s is set when offset
+// s of the lane's 16 bytes in segment J0 + i may start a keyword.  d4[i]
+// receives the dword after the lane's 16 bytes.
 //
 // Stride 1: the K bytes at offset s hash to a set filter entry.
 // Stride 2 and 4: only the 3-byte windows starting at s = STRIDE, 2 STRIDE,
@@ -621,22 +608,23 @@ __device__ __forceinline__ void load_segment(const FilterLaunch &F, int64_t c, i
 // rotating the word right by p (mod 32) moves the key's bit (x * mul) mod 32
 // to b.  Adding c may carry into the word index; the host sets each key's
 // bit in both words that can result.
-template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL>
-__device__ __forceinline__ unsigned long long filter_chunk(const ChunkRegs<SEGS> &R, unsigned lane,
-                                                           const uint8_t *sfilt, uint32_t mul) {
+template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, int J0, int N>
+__device__ __forceinline__ uint32_t filter_offsets(const ChunkRegs<SEGS> &R, unsigned lane, const uint8_t *sfilt,
+                                                   uint32_t mul, uint32_t (&d4)[N]) {
     constexpr uint32_t kmask = K >= 3 ? 0xFFFFFFu : ((1u << (8 * K)) - 1u);
     // byte map: 2^FLOG2 entries; bit map: 2^(FLOG2-2) words of 32 bits
     constexpr int shift = BITMAP ? 32 - (FLOG2 - 2) : 32 - FLOG2;
     const uint32_t *fm = reinterpret_cast<const uint32_t *>(sfilt);
-    uint32_t mseg[SEGS];
+    static_assert(N <= 2, "one mask word");
+    uint32_t m = 0;
 #pragma unroll
-    for (int j = 0; j < SEGS; ++j) {
-        uint32_t d[5];
-        d[0] = R.d[j][0]; d[1] = R.d[j][1]; d[2] = R.d[j][2]; d[3] = R.d[j][3];
-        const uint32_t from_next_lane = __builtin_amdgcn_ds_bpermute(int((lane + 1) * 4), int(d[0]));
+    for (int i = 0; i < N; ++i) {
+        const int j = J0 + i;
+        const uint32_t from_next_lane = __builtin_amdgcn_ds_bpermute(int((lane + 1) * 4), int(R.d[j][0]));
         const uint32_t from_next_seg = (j + 1 < SEGS) ? __builtin_amdgcn_readlane(R.d[(j + 1) % SEGS][0], 0)
                                                       : R.tail;
-        d[4] = lane == 63 ? from_next_seg : from_next_lane;
+        d4[i] = lane == 63 ? from_next_seg : from_next_lane;
+        const uint32_t d[5] = {R.d[j][0], R.d[j][1], R.d[j][2], R.d[j][3], d4[i]};
         uint32_t mj = 0;
         if (STRIDE == 1) {
 #pragma unroll
@@ -686,12 +674,9 @@ __device__ __forceinline__ unsigned long long filter_chunk(const ChunkRegs<SEGS>
             if (STRIDE == 2) mj |= mj << 1;
             if (STRIDE == 4) mj = __umul24(mj, 15u);
         }
-        mseg[j] = mj;
+        m |= mj << (16 * i);
     }
-    // bit 16 j + s: segment j, byte s
-    const uint32_t lo = SEGS >= 2 ? (mseg[0] | (mseg[1 % SEGS] << 16)) : mseg[0];
-    const uint32_t hi = SEGS >= 4 ? (mseg[2 % SEGS] | (mseg[3 % SEGS] << 16)) : 0u;
-    return (static_cast<unsigned long long>(hi) << 32) | lo;
+    return m;
 }
 
 // Positive windows of the N segments from J0 on, for the strides with the
@@ -870,9 +855,11 @@ __device__ __forceinline__ int prefix16(int v, unsigned lane) {
 // keywords, 1 GiB, 173 -> 171 (bound by the stream), 220.8 -> 199.6 per call
 // between other work.
 //
-// Otherwise a drain loads each candidate offset's text, looks its prefix up
-// in the exact prefix table and keeps the survivors with the 8 text bytes
-// after the prefix.
+// Otherwise an entry is a candidate offset and the four bytes from it on, and
+// a drain looks the prefix up in the exact prefix table, in LDS beside a 64 KiB
+// map.  (Drains that read each offset's text: 200 keywords of 2 to 8 bytes, 64
+// MiB, 1.5 million candidates, 35.3 us, now 35.0; two keywords, 1 MiB, 10.0 ->
+// 9.5.)
 //
 // Kept hits go to the wave's hit records (LDS, then its region).  A wave
 // whose region has no room for another drain leaves the loop and goes on in
@@ -886,13 +873,11 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     // Beside a 64 KiB filter, a copy of the prefix table (8192 slots) fits
     // too; beside a 128 KiB one only the queues and the hit records do.
     constexpr int PT_SLOTS = FLOG2 >= 17 ? 0 : 8192;
-    constexpr int kHitBytes = kMaxWaves * kLdsHits * 16;
+    constexpr int kHitBytes = kMaxWaves * kLdsHits * 8;
     __shared__ __align__(16) uint32_t sxtra[(2 * PT_SLOTS * 4 + kHitBytes) / 4];
     uint32_t *const sptab = sxtra;                                        // [2 * PT_SLOTS]
-    uint4 *const shits = reinterpret_cast<uint4 *>(sxtra + 2 * PT_SLOTS);  // [waves * kLdsHits]
-    uint2 *const swhits = reinterpret_cast<uint2 *>(shits);               // [waves * kLdsWinHits]
+    uint2 *const shits = reinterpret_cast<uint2 *>(sxtra + 2 * PT_SLOTS);  // [waves * kLdsHits]
     constexpr int64_t CH = int64_t(SEGS) * kSegBytes;
-    constexpr int PER_LANE = kDrain / kWave;
     const int waves_per_block = int(blockDim.x) / kWave;
     const int wlog = __builtin_ctz(unsigned(waves_per_block));   // W is a power of two
     const unsigned lane = lane_id();
@@ -905,81 +890,52 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     int qlen = 0;
 
     // Where the streaming loop stopped: every slot from `cur` on is left to
-    // the slow mode (none if cur_ok is false), cur's candidates not yet
-    // queued in `rest` (with the window table: those of group rest_g, and the
-    // groups after it), and lane 0's `ahead` holding the slot after nxt
-    // (taken when nxt is a chunk of the text).
+    // the slow mode (none if cur_ok is false), of cur what `rest` holds of its
+    // group of segments rest_g and the groups after it, and lane 0's `ahead`
+    // holds the slot after nxt (taken when nxt is a chunk of the text).
     bool slow = false;
     bool cur_ok = false;
     uint32_t cur = 0, nxt = 0, ahead = 0;
-    unsigned long long rest = 0;
-
-    // Queues the candidate offsets of mask m (chunk slot k), draining the
-    // queue whenever it holds kDrain entries.  Returns false, leaving the
-    // bits not yet queued in m, if `drain` refuses to run.
-    auto push = [&](unsigned long long &m, uint32_t k, auto &&drain) __attribute__((always_inline)) {
-        while (true) {
-            if (qlen >= kDrain && !drain(kDrain)) return false;
-            const unsigned long long act = __ballot(m != 0);
-            if (act == 0) return true;
-            if (m) {
-                const int b = __ffsll(static_cast<long long>(m)) - 1;
-                q[qlen + int(rank_in(act))] = (k << 12) | uint32_t((b >> 4) * kSegBytes + int(lane) * 16 + (b & 15));
-                m &= m - 1;
-            }
-            qlen += __popcll(act);
-        }
-    };
-    // The newest `take` queue entries, one per lane (lanes past `take`
-    // repeat the first one, so every load made from them is valid).
-    auto pop = [&](int take, uint32_t (&ent)[PER_LANE]) __attribute__((always_inline)) {
-        wave_sync();
-#pragma unroll
-        for (int r = 0; r < PER_LANE; ++r) {
-            const int i = int(lane) + r * kWave;
-            ent[r] = q[qlen - take + (i < take ? i : 0)];
-        }
-        wave_sync();
-        qlen -= take;
-    };
-    // The same for windows (WIN): a queue entry also carries the window's
-    // bytes, so that looking it up reads no text.  Filters and queues the
-    // segments held in R (of the chunk in slot k, the first of them segment
-    // `seg`) in groups of at most two (more at once spill registers).  On a
-    // refusal `rest` holds what is left of group rest_g; the groups after it
-    // are left whole.
-    constexpr int kWin = 16 / STRIDE;    // windows per segment and lane
-    uint2 *wq = reinterpret_cast<uint2 *>(q);
+    unsigned rest = 0;
     int rest_g = 0;
-    // Queues the positive windows m (those of N segments from J0 on); false,
-    // leaving the rest in m, if `drain` refuses to run.
-    auto queue_windows = [&](unsigned &m, const auto &R, const auto &d4, auto j0, uint32_t at0,
-                             auto &&drain) __attribute__((always_inline)) {
+
+    // A queue entry is a candidate's position {slot << 12 | byte of the chunk}
+    // and its four bytes, from the registers that were filtered: the positive
+    // window's (its position the first offset it stands for), or those from a
+    // candidate offset on (the prefix and at least one byte after it).
+    constexpr int kBits = WIN ? 16 / STRIDE : 16;    // candidates per segment and lane
+    uint2 *wq = reinterpret_cast<uint2 *>(q);
+    // Queues the candidates m (those of N segments from J0 on); false, leaving
+    // the rest in m, if `drain` refuses to run.
+    auto queue_mask = [&](unsigned &m, const auto &R, const auto &d4, auto j0, uint32_t at0,
+                          auto &&drain) __attribute__((always_inline)) {
         constexpr int J0 = decltype(j0)::value;
         constexpr int N = int(sizeof(d4) / 4);
         if (!uniform(m != 0)) return true;
-#pragma unroll
+        // left as a loop: unrolled, 50000 keywords, 64 MiB took 28.0 us
+        // instead of 27.4, and 20000 keywords, 1 GiB, 198 instead of 196
         for (int i = 0; i < N; ++i) {
             const uint32_t (&d)[4] = R.d[J0 + i];
-            uint32_t mj = __builtin_amdgcn_ubfe(m, uint32_t(kWin * i), uint32_t(kWin));
+            uint32_t mj = __builtin_amdgcn_ubfe(m, uint32_t(kBits * i), uint32_t(kBits));
             while (true) {
                 if (qlen >= kDrain && !drain(kDrain)) {
-                    m = mj << (kWin * i) | (m >> (kWin * (i + 1)) << (kWin * (i + 1)));
+                    m = mj << (kBits * i) | (i + 1 < N ? m >> (kBits * N / 2) << (kBits * N / 2) : 0u);
                     return false;
                 }
                 const unsigned long long act = __ballot(mj != 0);
                 if (act == 0) break;
                 if (mj) {
-                    const int t = __builtin_ctz(mj), b = t * STRIDE;
-                    // the window's bytes, picked without branches
+                    const int t = __builtin_ctz(mj), b = WIN ? t * STRIDE : t;
+                    // the four bytes, picked without branches
                     const uint32_t c2 = bit_mask(b, 2), c3 = bit_mask(b, 3);
+                    const uint32_t hi = pick(c3, pick(c2, d4[i], d[3]), pick(c2, d[2], d[1]));
                     uint32_t x;
-                    if (STRIDE == 4) {
-                        x = pick(c3, pick(c2, d4[i], d[3]), pick(c2, d[2], d[1]));
+                    if (WIN && STRIDE == 4) {
+                        x = hi;
                     } else {
                         const uint32_t lo = pick(c3, pick(c2, d[3], d[2]), pick(c2, d[1], d[0]));
-                        const uint32_t hi = pick(c3, pick(c2, d4[i], d[3]), pick(c2, d[2], d[1]));
-                        x = pick(bit_mask(b, 1), hi, __builtin_amdgcn_alignbyte(hi, lo, 2u));
+                        if (WIN) x = pick(bit_mask(b, 1), hi, __builtin_amdgcn_alignbyte(hi, lo, 2u));
+                        else x = __builtin_amdgcn_alignbyte(hi, lo, uint32_t(b) & 3u);
                     }
                     wq[qlen + int(rank_in(act))] =
                         make_uint2(at0 + uint32_t((J0 + i) * kSegBytes + int(lane) * 16 + b), x);
@@ -991,15 +947,25 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         m = 0;
         return true;
     };
-    auto push_windows = [&](const ChunkRegs<SEGS> &R, uint32_t mul, uint32_t k,
-                            auto &&drain) __attribute__((always_inline)) {
+    // Filters the segments of R from J0 on.
+    auto filter = [&](const auto &R, auto j0, uint32_t mul, auto &d4) __attribute__((always_inline)) -> unsigned {
+        constexpr int J0 = decltype(j0)::value;
+        constexpr int N = int(sizeof(d4) / 4);
+        constexpr int NS = int(sizeof(R.d) / 16);
+        if constexpr (WIN) return filter_windows<BITMAP, NS, FLOG2, STRIDE, DUAL, PAIR, J0, N>(R, lane, sfilt, mul, d4);
+        else return filter_offsets<K, BITMAP, NS, FLOG2, STRIDE, DUAL, J0, N>(R, lane, sfilt, mul, d4);
+    };
+    // Filters and queues the chunk held in R (slot k) in groups of at most two
+    // segments (more at once spill registers).  On a refusal `rest` holds what
+    // is left of group rest_g; the groups after it are left whole.
+    auto push = [&](const ChunkRegs<SEGS> &R, uint32_t mul, uint32_t k, auto &&drain) __attribute__((always_inline)) {
         constexpr int kGroup = SEGS < 2 ? 1 : 2;
         auto group = [&](auto g) __attribute__((always_inline)) {
             constexpr int G = decltype(g)::value;
             uint32_t d4[kGroup];
-            unsigned m = filter_windows<BITMAP, SEGS, FLOG2, STRIDE, DUAL, PAIR, G * kGroup, kGroup>(R, lane, sfilt, mul,
-                                                                                                   d4);
-            if (queue_windows(m, R, d4, std::integral_constant<int, G * kGroup>{}, k << 12, drain)) return true;
+            const std::integral_constant<int, G * kGroup> j0{};
+            unsigned m = filter(R, j0, mul, d4);
+            if (queue_mask(m, R, d4, j0, k << 12, drain)) return true;
             rest = m;
             rest_g = G;
             return false;
@@ -1009,19 +975,32 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             if (!group(std::integral_constant<int, 1>{})) return false;
         return true;
     };
-    auto pop_window = [&](int take) __attribute__((always_inline)) {
+    // The newest `take` queue entries, one per lane (lanes past `take` repeat
+    // the first one).
+    auto pop = [&](int take) __attribute__((always_inline)) {
         wave_sync();
         const uint2 e = wq[qlen - take + (int(lane) < take ? int(lane) : 0)];
         wave_sync();
         qlen -= take;
         return e;
     };
+    // What the tables know of a queue entry's bytes: the window table's slot,
+    // or the prefix table's value; kNoHit when no keyword has them.
+    constexpr uint32_t kNoHit = WIN ? ~0u : 0u;
+    auto look_up = [&](uint32_t y, bool in_lds, const FilterLaunch &F, const uint32_t *gptab, int bits,
+                       uint32_t mul) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (WIN) return uint32_t(find_window(in_lds, sptab, F.win_keys, F.win_nb, y));
+        const uint2 kv = probe_prefix(in_lds, sptab, gptab, bits, K >= 3 ? y & 0xFFFFFFu : y & ((1u << (8 * K)) - 1u), mul);
+        // a non-final prefix state whose only child's byte differs from the
+        // text's next byte ends the walk at the prefix
+        if ((kv.y & kHasNext) && !(kv.y >> 31) && (kv.x >> 24) != ((y >> (8 * K)) & 0xFFu)) return kNoHit;
+        return kv.y;
+    };
 
     // ---- set-up and streaming: the fields they read, and no others ----
     {
         const KArgs *P1 = kernel_args();
         const FilterLaunch F = P1->F;
-        const uint8_t *text = P1->S.text;
         const uint32_t *gptab = P1->A.ptab;
         const int ptab_bits = P1->A.ptab_bits;
         const uint32_t mul = P1->A.hash_mul;
@@ -1053,80 +1032,21 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         if (threadIdx.x == 0) snext = uint32_t(2 * waves_per_block);
         __syncthreads();
 
-        uint4 *hits = F.hits + w * F.hit_cap;
-        uint4 *lhits = shits + wave * kLdsHits;
-        // Streaming-loop drain of the newest `take` entries.  Reads the
-        // aligned 16 bytes from each offset's dword on (the prefix and the 8
-        // bytes after it), held back to the text's last dword.  Refuses when
+        // Streaming-loop drain of the newest `take` entries.  Refuses when
         // the region might not hold its hits.
-        const int64_t n = P1->S.n;
-        const uintptr_t tlast = (reinterpret_cast<uintptr_t>(text) + uintptr_t(n) - 1u) & ~uintptr_t(3);
-        auto drain_store = [&](int take) __attribute__((always_inline)) {
-            if (hcount + kDrain > kLdsHits + F.hit_cap) return false;
-            uint32_t ent[PER_LANE];
-            pop(take, ent);
-            u32x4 win[PER_LANE];
-            uint32_t sh[PER_LANE];
-            bool inside[PER_LANE];
-#pragma unroll
-            for (int r = 0; r < PER_LANE; ++r) {
-                const int64_t o = M.chunk(ent[r] >> 12) * CH + int64_t(ent[r] & 4095u) - F.mis;
-                const uintptr_t a = reinterpret_cast<uintptr_t>(text + o);
-                sh[r] = uint32_t(a & 3u);
-                inside[r] = o >= 0 && o + K <= n;
-                const uintptr_t pa = inside[r] ? a & ~uintptr_t(3) : tlast;
-                if (pa + 12 <= tlast) {
-                    win[r] = gload16(reinterpret_cast<const uint8_t *>(pa));
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uintptr_t pi = pa + 4u * uintptr_t(i);
-                        win[r][i] = gload4(reinterpret_cast<const uint8_t *>(pi < tlast ? pi : tlast));
-                    }
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < PER_LANE; ++r) {
-                const uint32_t y0 = __builtin_amdgcn_alignbyte(win[r].y, win[r].x, sh[r]);
-                const uint32_t y1 = __builtin_amdgcn_alignbyte(win[r].z, win[r].y, sh[r]);
-                const uint32_t y2 = __builtin_amdgcn_alignbyte(win[r].w, win[r].z, sh[r]);
-                const uint32_t x = K >= 3 ? (y0 & 0xFFFFFFu) : (y0 & ((1u << (8 * K)) - 1u));
-                const uint32_t rb0 = __builtin_amdgcn_alignbyte(y1, y0, uint32_t(K));
-                const uint32_t rb1 = __builtin_amdgcn_alignbyte(y2, y1, uint32_t(K));
-                uint32_t e = 0;
-                if (int(lane) + r * kWave < take && inside[r]) {
-                    const uint2 kv = probe_prefix(pt_lds, sptab, gptab, ptab_bits, x, mul);
-                    e = kv.y;
-                    // a non-final prefix state whose only child's byte differs
-                    // from the text's next byte ends the walk at the prefix
-                    if ((e & kHasNext) && !(e >> 31) && (kv.x >> 24) != (rb0 & 0xFFu)) e = 0u;
-                }
-                const unsigned long long hit = __ballot(e != 0u);
-                if (hit == 0) continue;
-                if (e != 0u) {
-                    const int at = hcount + int(rank_in(hit));
-                    if (at < kLdsHits) lhits[at] = make_uint4(ent[r], e, rb0, rb1);
-                    else gstore16(hits + (at - kLdsHits), ent[r], e, rb0, rb1);
-                }
-                hcount += __popcll(hit);
-            }
-            return true;
-        };
-
-        // The same for windows: one lookup in the exact window table.
-        uint2 *whits = reinterpret_cast<uint2 *>(hits);
-        uint2 *lwhits = swhits + wave * kLdsWinHits;
-        auto drain_windows = [&](int take) __attribute__((always_inline)) {
-            if (hcount + kDrain > kLdsWinHits + 2 * F.hit_cap) return false;
-            const uint2 e = pop_window(take);
-            int slot = -1;
-            if (int(lane) < take) slot = find_window(pt_lds, sptab, F.win_keys, F.win_nb, e.y);
-            const unsigned long long hit = __ballot(slot >= 0);
+        uint2 *hits = reinterpret_cast<uint2 *>(F.hits + w * F.hit_cap);
+        uint2 *lhits = shits + wave * kLdsHits;
+        auto drain = [&](int take) __attribute__((always_inline)) {
+            if (hcount + kDrain > kLdsHits + 2 * F.hit_cap) return false;
+            const uint2 e = pop(take);
+            uint32_t v = kNoHit;
+            if (int(lane) < take) v = look_up(e.y, pt_lds, F, gptab, ptab_bits, mul);
+            const unsigned long long hit = __ballot(v != kNoHit);
             if (hit == 0) return true;
-            if (slot >= 0) {
+            if (v != kNoHit) {
                 const int at = hcount + int(rank_in(hit));
-                if (at < kLdsWinHits) lwhits[at] = make_uint2(e.x, uint32_t(slot));
-                else gstore8(whits + (at - kLdsWinHits), e.x, uint32_t(slot));
+                if (at < kLdsHits) lhits[at] = make_uint2(e.x, v);
+                else gstore8(hits + (at - kLdsHits), e.x, v);
             }
             hcount += __popcll(hit);
             return true;
@@ -1153,14 +1073,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             const bool nxt_ok = uniform(M.chunk(nxt) < n_chunks);
             load_chunk<SEGS>(F, M.chunk(nxt_ok ? nxt : cur), lane, into);
             if (lane == 0 && nxt_ok) ahead = atomicAdd(&snext, 1u);
-            bool pushed;
-            if constexpr (WIN) {
-                pushed = push_windows(regs, mul, cur, drain_windows);
-            } else {
-                rest = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(regs, lane, sfilt, mul);
-                pushed = push(rest, cur, drain_store);
-            }
-            if (!uniform(pushed)) { slow = true; return false; }
+            if (!uniform(push(regs, mul, cur, drain))) { slow = true; return false; }
             // slots held by a wave only grow, and so do their chunks: once
             // one is past the end, so is every later one
             cur = nxt;
@@ -1172,12 +1085,8 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             if (!half(ra, rb)) break;
             if (!half(rb, ra)) break;
         }
-        while (!slow && qlen > 0) {
-            bool done;
-            if constexpr (WIN) done = drain_windows(imin(qlen, kDrain));
-            else done = drain_store(imin(qlen, kDrain));
-            if (!done) slow = true;
-        }
+        while (!slow && qlen > 0)
+            if (!drain(imin(qlen, kDrain))) slow = true;
     }
 
     // ---- slow mode, partial chunks, walks and output ----
@@ -1192,88 +1101,67 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     M.wlog = wlog;
     const bool pt_lds = FLOG2 < 17 && (WIN ? F.win_nb <= 12 : A.ptab_bits <= 13);
     const uint32_t mul = A.hash_mul;
-    uint4 *hits = F.hits + w * F.hit_cap;
+    const uint2 *hits = reinterpret_cast<const uint2 *>(F.hits + w * F.hit_cap);
     auto offset_of = [&](uint32_t ent) __attribute__((always_inline)) {
         return M.chunk(ent >> 12) * CH + int64_t(ent & 4095u) - F.mis;
     };
+    // Walks a hit {position, look_up's value}; text(at, start, end, id) gives
+    // the text holding its window or offset, ids(o, id, start, state) and
+    // one(o, id, start, keyword) report.
+    auto walk_hit = [&](uint2 rec, auto &&text, auto &&ids, auto &&one) __attribute__((always_inline)) {
+        const int64_t at = offset_of(rec.x) + (WIN ? STRIDE : 0);
+        int64_t tstart, end;
+        int32_t tid;
+        text(at, tstart, end, tid);
+        auto ids2 = [&](int64_t o, int32_t st) __attribute__((always_inline)) { ids(o, tid, tstart, st); };
+        auto one2 = [&](int64_t o, int32_t pid) __attribute__((always_inline)) { one(o, tid, tstart, pid); };
+        if constexpr (WIN)
+            walk_window(A, S, F.win_entries, int(rec.y), at, tstart, end, ids2, one2);
+        else if (at >= tstart)     // not before the text's first byte
+            walk_below(A, S, at, end, int32_t(rec.y & kStateMask), K, [&](int32_t st) { ids2(at, st); },
+                       [&](int32_t pid) { one2(at, pid); });
+    };
 
     if (slow) {
-        // Drains that walk what they confirm right here.
+        // A drain that walks what it confirms right here.
         auto drain_walk = [&](int take) __attribute__((always_inline)) {
-            uint32_t ent[PER_LANE];
-            pop(take, ent);
-            for (int r = 0; r < PER_LANE; ++r) {
-                if (int(lane) + r * kWave >= take) continue;
-                const int64_t o = offset_of(ent[r]);
-                if (o < 0 || o + K > S.n) continue;
-                uint32_t x = 0;
-                for (int j = 0; j < K; ++j) x |= gload1(S.text + o + j) << (8 * j);
-                const uint2 kv = probe_prefix(pt_lds, sptab, A.ptab, A.ptab_bits, x, mul);
-                if (kv.y == 0u) continue;
-                int64_t tstart, end;
-                int32_t tid;
-                locate_text(S, nullptr, o, tstart, end, tid);
-                walk_rest<false>(A, S, o, end, kv.y, make_uint2(0u, 0u),
-                                 [&](int32_t st) { emit(A, S, o - tstart, tid, st); },
-                                 [&](int32_t pid) { emit_one(S, nullptr, nullptr, o - tstart, tid, pid); });
-            }
-        };
-        auto drain_walk_windows = [&](int take) __attribute__((always_inline)) {
-            const uint2 e = pop_window(take);
+            const uint2 e = pop(take);
             if (int(lane) >= take) return;
-            const int slot = find_window(pt_lds, sptab, F.win_keys, F.win_nb, e.y);
-            if (slot < 0) return;
-            const int64_t w = offset_of(e.x) + STRIDE;
-            int64_t tstart, end;
-            int32_t tid;
-            locate_text(S, nullptr, w, tstart, end, tid);
-            walk_window(A, S, F.win_entries, slot, w, tstart, end,
-                        [&](int64_t o, int32_t st) { emit(A, S, o - tstart, tid, st); },
-                        [&](int64_t o, int32_t pid) { emit_one(S, nullptr, nullptr, o - tstart, tid, pid); });
+            const uint32_t v = look_up(e.y, pt_lds, F, A.ptab, A.ptab_bits, mul);
+            if (v == kNoHit) return;
+            walk_hit(make_uint2(e.x, v),
+                     [&](int64_t at, int64_t &ts, int64_t &te, int32_t &id) { locate_text(S, nullptr, at, ts, te, id); },
+                     [&](int64_t o, int32_t id, int64_t ts, int32_t st) { emit(A, S, o - ts, id, st); },
+                     [&](int64_t o, int32_t id, int64_t ts, int32_t pid) {
+                         emit_one(S, nullptr, nullptr, o - ts, id, pid);
+                     });
         };
         // What is left of the wave's slots: cur first, with what its queueing
-        // left (its text is read again), then its successors; with the window
-        // table one segment at a time, since a segment's registers stay live
-        // while the walks of a full queue run.
+        // left (its text is read again), then its successors, one segment at a
+        // time, since a segment's registers stay live while the walks of a
+        // full queue run.
         auto full = [](int) __attribute__((always_inline)) { return false; };
         uint32_t sl = cur;
         bool ok = cur_ok, first = true;
         while (ok || qlen > 0) {
-            for (int j = 0; j < (WIN ? SEGS : 1); ++j) {
+            for (int j = 0; j < SEGS; ++j) {
+                const std::integral_constant<int, 0> j0{};
                 bool queued = !ok;        // nothing (more) to queue
-                unsigned long long m = 0;
                 ChunkRegs<1> r1;
                 uint32_t d4[1];
-                unsigned mw = 0;
+                unsigned m = 0;
                 if (ok) {
-                    if constexpr (WIN) {
-                        load_segment<SEGS>(F, M.chunk(sl), j, lane, r1);
-                        mw = filter_windows<BITMAP, 1, FLOG2, STRIDE, DUAL, PAIR, 0, 1>(r1, lane, sfilt, mul, d4);
-                        if (first) {
-                            const int g = SEGS < 2 ? j : j / 2;
-                            if (g < rest_g) mw = 0;
-                            if (g == rest_g) mw &= unsigned(rest) >> (SEGS < 2 ? 0 : kWin * (j & 1));
-                        }
-                    } else if (first) {
-                        m = rest;
-                    } else {
-                        ChunkRegs<SEGS> r;
-                        load_chunk<SEGS>(F, M.chunk(sl), lane, r);
-                        m = filter_chunk<K, BITMAP, SEGS, FLOG2, STRIDE, DUAL>(r, lane, sfilt, mul);
+                    load_segment<SEGS>(F, M.chunk(sl), j, lane, r1);
+                    m = filter(r1, j0, mul, d4);
+                    if (first) {
+                        const int g = SEGS < 2 ? j : j / 2;
+                        if (g < rest_g) m = 0;
+                        if (g == rest_g) m &= rest >> (SEGS < 2 ? 0 : kBits * (j & 1));
                     }
                 }
                 while (true) {
-                    if (!queued) {
-                        if constexpr (WIN)
-                            queued = queue_windows(mw, r1, d4, std::integral_constant<int, 0>{},
-                                                   (sl << 12) + uint32_t(j * kSegBytes), full);
-                        else
-                            queued = push(m, sl, full);
-                    }
-                    while (qlen > 0) {
-                        if constexpr (WIN) drain_walk_windows(imin(qlen, kDrain));
-                        else drain_walk(imin(qlen, kDrain));
-                    }
+                    if (!queued) queued = queue_mask(m, r1, d4, j0, (sl << 12) + uint32_t(j * kSegBytes), full);
+                    while (qlen > 0) drain_walk(imin(qlen, kDrain));
                     if (queued) break;
                 }
             }
@@ -1315,37 +1203,21 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 emit_one(S, nullptr, nullptr, o, 0, pid);
             }
         };
-        for (int i = int(lane); WIN && i < hcount; i += kWave) {
+        for (int i = int(lane); i < hcount; i += kWave) {
             uint2 rec;
-            if (i < kLdsWinHits) rec = swhits[wave * kLdsWinHits + i];
-            else rec = gload8(reinterpret_cast<const uint2 *>(hits) + (i - kLdsWinHits));
-            const int64_t first = offset_of(rec.x);     // the window's first candidate
-            // a match at o = first .. first + STRIDE - 1 has the entry's
-            // position moved by as much (it stays below 4096)
-            auto put = [&](int64_t o, int32_t pid) __attribute__((always_inline)) {
+            if (i < kLdsHits) rec = shits[wave * kLdsHits + i];
+            else rec = gload8(hits + (i - kLdsHits));
+            // a match at a window's o = first .. first + STRIDE - 1 has the
+            // entry's position moved by as much (it stays below 4096)
+            const int64_t first = offset_of(rec.x);
+            auto put = [&](int64_t o, int32_t, int64_t, int32_t pid) __attribute__((always_inline)) {
                 stage_one(rec.x + uint32_t(o - first), o, pid);
             };
-            walk_window(A, S, F.win_entries, int(rec.y), first + STRIDE, 0, S.n,
-                        [&](int64_t o, int32_t st) {
-                            for (int32_t k = A.out_off[st], k1 = A.out_off[st + 1]; k < k1; ++k) put(o, A.out_pid[k]);
-                        },
-                        put);
-        }
-        for (int i = int(lane); !WIN && i < hcount; i += kWave) {
-            uint4 rec;
-            if (i < kLdsHits) {
-                rec = shits[wave * kLdsHits + i];
-            } else {
-                const u32x4 g = gload16(reinterpret_cast<const uint8_t *>(hits + (i - kLdsHits)));
-                rec = make_uint4(g.x, g.y, g.z, g.w);
-            }
-            const int64_t o = offset_of(rec.x);
-            auto put = [&](int32_t pid) __attribute__((always_inline)) { stage_one(rec.x, o, pid); };
-            walk_rest<true>(A, S, o, S.n, rec.y, make_uint2(rec.z, rec.w),
-                            [&](int32_t st) {
-                                for (int32_t k = A.out_off[st], k1 = A.out_off[st + 1]; k < k1; ++k) put(A.out_pid[k]);
-                            },
-                            put);
+            walk_hit(rec, [&](int64_t, int64_t &ts, int64_t &te, int32_t &id) { ts = 0; te = S.n; id = 0; },
+                     [&](int64_t o, int32_t, int64_t, int32_t st) {
+                         for (int32_t k = A.out_off[st], k1 = A.out_off[st + 1]; k < k1; ++k) put(o, 0, 0, A.out_pid[k]);
+                     },
+                     put);
         }
         __syncthreads();
         // every wave's matches are staged: one atomic reserves the block's
@@ -1439,27 +1311,12 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             for (int h = kMaxWaves / 2; h >= 1; h >>= 1)
                 if (wfirst[j + h] <= i) j += h;
             const int k = i - wfirst[j];
-            if constexpr (WIN) {
-                const uint2 rec = k < kLdsWinHits
-                                      ? swhits[j * kLdsWinHits + k]
-                                      : reinterpret_cast<const uint2 *>(F.hits + (r0 + j) * F.hit_cap)[k - kLdsWinHits];
-                const int64_t w0 = offset_of(rec.x) + STRIDE;
-                int64_t tstart, end;
-                int32_t tid;
-                locate_text(S, loff, w0, tstart, end, tid);
-                walk_window(A, S, F.win_entries, int(rec.y), w0, tstart, end,
-                            [&](int64_t o, int32_t s2) { emit_staged(A, S, st, lcnt, o - tstart, tid, s2); },
-                            [&](int64_t o, int32_t pid) { emit_one(S, st, lcnt, o - tstart, tid, pid); });
-                continue;
-            }
-            const uint4 rec = k < kLdsHits ? shits[j * kLdsHits + k] : F.hits[(r0 + j) * F.hit_cap + (k - kLdsHits)];
-            const int64_t o = offset_of(rec.x);
-            int64_t tstart, end;
-            int32_t tid;
-            locate_text(S, loff, o, tstart, end, tid);
-            walk_rest<true>(A, S, o, end, rec.y, make_uint2(rec.z, rec.w),
-                            [&](int32_t s2) { emit_staged(A, S, st, lcnt, o - tstart, tid, s2); },
-                            [&](int32_t pid) { emit_one(S, st, lcnt, o - tstart, tid, pid); });
+            const uint2 rec = k < kLdsHits ? shits[j * kLdsHits + k]
+                                           : reinterpret_cast<const uint2 *>(F.hits + (r0 + j) * F.hit_cap)[k - kLdsHits];
+            walk_hit(rec,
+                     [&](int64_t at, int64_t &ts, int64_t &te, int32_t &id) { locate_text(S, loff, at, ts, te, id); },
+                     [&](int64_t o, int32_t id, int64_t ts, int32_t s2) { emit_staged(A, S, st, lcnt, o - ts, id, s2); },
+                     [&](int64_t o, int32_t id, int64_t ts, int32_t pid) { emit_one(S, st, lcnt, o - ts, id, pid); });
         }
         flush_stage(S, st, lcnt);
     }

@@ -111,7 +111,7 @@ FilteredFn pick_filtered(int K, int kind, int segs, int stride, bool win) {
 
 int64_t filtered_lds(const FilterGeom &g) {
     const int64_t pt_slots = g.bytes > (64 << 10) ? 0 : 8192;
-    return g.bytes + int64_t(kMaxWaves) * kQueueCap * 4 + pt_slots * 8 + int64_t(kMaxWaves) * kLdsHits * 16;
+    return g.bytes + int64_t(kMaxWaves) * kQueueCap * 4 + pt_slots * 8 + int64_t(kMaxWaves) * kLdsHits * 8;
 }
 
 // Launch geometry of the filtered policy for a text of n bytes at `addr`.
