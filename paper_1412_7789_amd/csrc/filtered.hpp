@@ -904,48 +904,52 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
     // window's (its position the first offset it stands for), or those from a
     // candidate offset on (the prefix and at least one byte after it).
     constexpr int kBits = WIN ? 16 / STRIDE : 16;    // candidates per segment and lane
+    constexpr int kBitsLog = __builtin_ctz(unsigned(kBits));
     uint2 *wq = reinterpret_cast<uint2 *>(q);
-    // Queues the candidates m (those of N segments from J0 on); false, leaving
-    // the rest in m, if `drain` refuses to run.
+    // Queues the candidates m (those of N segments from J0 on), one per lane
+    // and round; false, leaving the rest in m, if `drain` refuses to run.
+    // Bound by VALU issue: a round costs some 30 instructions however few of
+    // its lanes have a candidate, and there are as many as the fullest lane
+    // has bits.  So both segments of a group share the rounds, which costs 6
+    // more instructions to pick a lane's registers; kernel, a loop per segment
+    // -> this: 20000 keywords, 1 GiB, 193 -> 182 us; 200 short keywords, 64
+    // MiB, 35.1 -> 33.1; 50000 keywords, 64 MiB, 27.4 -> 26.5.  Four segments
+    // at once need three times the picks: 1 GiB 203.
     auto queue_mask = [&](unsigned &m, const auto &R, const auto &d4, auto j0, uint32_t at0,
                           auto &&drain) __attribute__((always_inline)) {
         constexpr int J0 = decltype(j0)::value;
         constexpr int N = int(sizeof(d4) / 4);
-        if (!uniform(m != 0)) return true;
-        // left as a loop: unrolled, 50000 keywords, 64 MiB took 28.0 us
-        // instead of 27.4, and 20000 keywords, 1 GiB, 198 instead of 196
-        for (int i = 0; i < N; ++i) {
-            const uint32_t (&d)[4] = R.d[J0 + i];
-            uint32_t mj = __builtin_amdgcn_ubfe(m, uint32_t(kBits * i), uint32_t(kBits));
-            while (true) {
-                if (qlen >= kDrain && !drain(kDrain)) {
-                    m = mj << (kBits * i) | (i + 1 < N ? m >> (kBits * N / 2) << (kBits * N / 2) : 0u);
-                    return false;
+        while (true) {
+            if (qlen >= kDrain && !drain(kDrain)) return false;
+            const unsigned long long act = __ballot(m != 0);
+            if (act == 0) return true;
+            if (m) {
+                const int t = __builtin_ctz(m);
+                // of two segments' registers, the one's that bit t lies in
+                const uint32_t c1 = N == 2 ? bit_mask(t, kBitsLog) : 0u;
+                auto reg = [&](int k) __attribute__((always_inline)) -> uint32_t {
+                    const uint32_t r0 = k < 4 ? R.d[J0][k] : d4[0];
+                    return N == 2 ? pick(c1, k < 4 ? R.d[J0 + N - 1][k] : d4[N - 1], r0) : r0;
+                };
+                const int b = WIN ? (t * STRIDE) & 15 : t & 15;
+                // the four bytes, picked without branches
+                const uint32_t c2 = bit_mask(b, 2), c3 = bit_mask(b, 3);
+                const uint32_t w2 = reg(2), w3 = reg(3), w1 = reg(1);
+                const uint32_t hi = pick(c3, pick(c2, reg(4), w3), pick(c2, w2, w1));
+                uint32_t x;
+                if (WIN && STRIDE == 4) {
+                    x = hi;
+                } else {
+                    const uint32_t lo = pick(c3, pick(c2, w3, w2), pick(c2, w1, reg(0)));
+                    if (WIN) x = pick(bit_mask(b, 1), hi, __builtin_amdgcn_alignbyte(hi, lo, 2u));
+                    else x = __builtin_amdgcn_alignbyte(hi, lo, uint32_t(b) & 3u);
                 }
-                const unsigned long long act = __ballot(mj != 0);
-                if (act == 0) break;
-                if (mj) {
-                    const int t = __builtin_ctz(mj), b = WIN ? t * STRIDE : t;
-                    // the four bytes, picked without branches
-                    const uint32_t c2 = bit_mask(b, 2), c3 = bit_mask(b, 3);
-                    const uint32_t hi = pick(c3, pick(c2, d4[i], d[3]), pick(c2, d[2], d[1]));
-                    uint32_t x;
-                    if (WIN && STRIDE == 4) {
-                        x = hi;
-                    } else {
-                        const uint32_t lo = pick(c3, pick(c2, d[3], d[2]), pick(c2, d[1], d[0]));
-                        if (WIN) x = pick(bit_mask(b, 1), hi, __builtin_amdgcn_alignbyte(hi, lo, 2u));
-                        else x = __builtin_amdgcn_alignbyte(hi, lo, uint32_t(b) & 3u);
-                    }
-                    wq[qlen + int(rank_in(act))] =
-                        make_uint2(at0 + uint32_t((J0 + i) * kSegBytes + int(lane) * 16 + b), x);
-                    mj &= mj - 1;
-                }
-                qlen += __popcll(act);
+                const uint32_t at = at0 + uint32_t(J0 * kSegBytes + int(lane) * 16 + b);
+                wq[qlen + int(rank_in(act))] = make_uint2(N == 2 ? at + (c1 & kSegBytes) : at, x);
+                m &= m - 1;
             }
+            qlen += __popcll(act);
         }
-        m = 0;
-        return true;
     };
     // Filters the segments of R from J0 on.
     auto filter = [&](const auto &R, auto j0, uint32_t mul, auto &d4) __attribute__((always_inline)) -> unsigned {
