@@ -15,17 +15,17 @@
 namespace pfac {
 namespace dev {
 
-constexpr int kQueueCap = 256;   // per-wave candidate queue (entries)
+constexpr int kQueueCap = 256;   // per-wave candidate queue (dwords, two per entry)
 // Hit records a wave keeps in LDS before it spills further ones to its
 // global region.  Global stores in the streaming loop stall it (a later wait
 // for the next chunk's loads also waits for them, and the data registers a
 // store reads cannot be reused until it is done), so records stay on chip.
 constexpr int kLdsHits = 128;
 constexpr int kDrain = 64;       // candidates taken per drain (1 per lane; 128 and 192 measured slower)
-// A queue holds fewer than kDrain entries before a push round and gains at
-// most one per lane in it, so its last entries are never used by the queue:
-// the last dword of the first wave's queue holds the block's slot counter.
-static_assert(2 * kDrain <= kQueueCap - 4, "queue room");
+// A queue holds fewer than kDrain entries before a round and gains at most
+// one per lane in it, so its last dwords are never used by the queue: the last
+// one of the first wave's queue holds the block's slot counter.
+static_assert(2 * (2 * kDrain - 1) < kQueueCap, "queue room");
 constexpr int kMaxWaves = 16;    // waves per block at most (1024 threads)
 // (queue entry, keyword id) pairs a wave's queue holds as its match stage,
 // after its count and before the slot counter

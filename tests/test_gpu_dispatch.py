@@ -77,3 +77,20 @@ def test_host_matcher_on_a_built_automaton_and_capacity():
     # a capacity below the count: the call grows its arrays once
     off, pid, ran = a.match_dispatch(w.text, capacity=3)
     assert_same((off, pid), exp, "dispatch, small capacity")
+
+
+@pytest.mark.parametrize("n", [65535, 65536, 65537, 200_001])
+def test_more_matches_than_the_pinned_arrays_hold(n):
+    """The first 65536 matches of a dispatched scan go straight to pinned
+    memory and the rest through device memory, with the caller's first capacity
+    below, at and above the count (a short one is grown to the count reported)."""
+    kws = [b"a", b"xyz"]
+    a = pf.Automaton(kws)
+    a.dispatch_threshold = 0
+    text = np.full(n, ord("a"), dtype=np.uint8)
+    for cap in (None, n, n + 7, n - 1, 65536, 65537):
+        off, pid, ran = a.match_dispatch(text, capacity=cap)
+        assert ran == pf.AC_RAN_GPU
+        assert len(off) == n and (pid == 0).all()
+        off = np.sort(off)
+        assert off[0] >= 0 and off[-1] < n and (np.diff(off) > 0).all()

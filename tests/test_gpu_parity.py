@@ -519,3 +519,27 @@ def test_text_inside_a_buffer_of_keywords(kws):
             for stride, segs in ((0, 0), (1, 2), (2, 1), (2, 4), (4, 1), (4, 2)):
                 off, pid = a.match(d[o:o + n], capacity=2 * n, launch=pf.launch_config(policy=1, stride=stride, segs=segs))
                 assert_same((off.cpu().numpy(), pid.cpu().numpy()), exp, f"start {o} n {n} stride {stride} segs {segs}")
+
+
+@pytest.mark.parametrize("stride,segs", [(1, 1), (1, 2), (2, 2), (2, 4), (4, 2), (4, 4)])
+def test_one_lane_with_candidates_in_every_segment(stride, segs):
+    """The segments of a group share their queueing rounds: keywords at the
+    same place of a lane's 16 bytes in one, some or all segments of a chunk,
+    at every place, in the first, middle and last lanes, with and without
+    others in the same 16 bytes."""
+    kws = [b"0123456789", b"wxyz0123", b"89wxyz01234567"]
+    text = np.full(96 << 10, ord("."), dtype=np.uint8)
+    for chunk in range(24):
+        for seg in range(4):
+            if not (chunk + 1 >> seg) & 1 and chunk < 16:
+                continue
+            for lane in (0, 1, 17, 31, 62, 63):
+                at = chunk * 4096 + seg * 1024 + lane * 16 + (chunk + (lane if chunk & 1 else 0)) % 16
+                k = np.frombuffer(kws[(chunk + seg) % 3] + (b"wxyz01234567" if chunk % 3 == 0 else b""), dtype=np.uint8)
+                text[at:at + len(k)] = k[:len(text) - at]
+    a = pf.Automaton(kws)
+    for n in (len(text), len(text) - 4099):
+        exp = oracle_match(kws, text[:n])
+        for f in range(1, 7):
+            cfg = pf.launch_config(policy=1, filter=f, segs=segs, stride=stride)
+            assert_same(gpu_match(kws, text[:n], launch=cfg, automaton=a), exp, f"n {n} filter {f}")

@@ -207,3 +207,23 @@ def test_submit_errors():
             srv.submit(0, np.zeros(1 << 20, np.uint8))       # larger than the whole budget
         off, pid, _ = srv.wait(srv.submit(0, np.frombuffer(b"xabcx", np.uint8)))
         assert off.tolist() == [1]
+
+
+@pytest.mark.parametrize("limit", [1, 31, 32, 33])
+def test_batches_around_the_pinned_text_starts(limit):
+    """Batches of up to 32 texts are scanned with their starts read from pinned
+    memory, larger ones with a device copy of them."""
+    kws = [b"ab", b"abc", b"bca", b"cabcab"]
+    rng = np.random.default_rng(limit)
+    texts = [rng.integers(97, 100, size=4 * MIB, dtype=np.uint8)]
+    texts += [rng.integers(97, 100, size=int(k), dtype=np.uint8) for k in rng.integers(0, 3000, size=150)]
+    o = Oracle(kws)
+    a = pf.Automaton(kws)
+    with pf.Server(pf.server_opts(n_streams=1, max_batch_texts=limit)) as srv:
+        srv.add_automaton(a)
+        reqs = [srv.submit(0, t) for t in texts]
+        res = [srv.wait(r) for r in reqs]
+    assert max(r[2]["batch_requests"] for r in res) <= limit
+    say("batch sizes", sorted({r[2]["batch_requests"] for r in res}))
+    for i, (off, pid, _) in enumerate(res):
+        assert_same((off, pid), o.match(texts[i]), f"request {i}")
