@@ -154,7 +154,7 @@ hipError_t launch_timed(const void *fn, dim3 grid, dim3 block, void **args, size
 }
 
 // Most 4-byte windows for which the launch rules choose stride 4 on any text,
-// on texts under 512 MiB and on texts under 16 MiB, and stride 2 with the
+// on texts under 256 MiB and on texts under 16 MiB, and stride 2 with the
 // 4-byte-window map.
 constexpr int32_t kPair4Keys = 32768, kPair4MidKeys = 100000, kPair4SmallKeys = 262144;
 constexpr int32_t kPair2Keys = 131072;
@@ -181,16 +181,18 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
         // wins until the map lets too many through.  Measured on MI355X (kernel
         // us; stride/map/segments, maps by their AC_FILTER number):
         //   1 GiB     1000 printable keywords (4000 windows at stride 4)
-        //             4/6/2 173, 2/6/4 > 178; 5000 byte keywords (20000)
-        //             4/6/2 163.3, 2/6/4 163.3; 20000 (80000) 4/6/2 218,
-        //             2/6/4 201; 50000 (200000) 4/6/2 427, 2/6/4 279
-        //   256 MiB   5000 47.8 and 51.3, 20000 61.2 and 61.0, 50000 117 and 79
-        //   64 MiB    5000 19.6 and 21.6 (2/6/2), 20000 22.9 and 24.3, 50000
-        //             37 and 28.5
-        //   4 MiB     50000 keywords 4/6/2 10.4, 2/6/2 10.5, stride 1 13.2;
-        //             5000 4/4/2 9.4, 4/6/2 9.6, 2/4/1 10.7; 1000 4/6/2 11.1,
-        //             4/4/2 11.2, 2/4/1 12.4
-        //   64 KiB    50000 keywords 4/6/1 8.1, stride 1 9.7
+        //             4/6/2 166, 2/6/4 170; 5000 byte keywords (20000)
+        //             4/6/2 158, 2/6/4 163; 20000 (80000) 4/6/2 213,
+        //             2/6/4 184; 50000 (200000) 4/6/2 421, 2/6/4 277
+        //   256 MiB   5000 46.9 and 49.5, 20000 58.8 and 55.2 (57.4 both when a
+        //             third share prefixes), 50000 113 and 77
+        //   200 MiB   20000 47.2 and 46.4, with shared prefixes 46.0 and 48.0
+        //   64 MiB    5000 18.4 and 21.6 (2/6/2), 20000 22.0 and 23.4, 50000
+        //             34.5 and 27.8
+        //   4 MiB     50000 keywords 4/6/2 9.8, 2/6/2 9.9, stride 1 11.8;
+        //             5000 4/4/2 8.6, 4/6/2 8.8, 2/4/1 9.6; 1000 4/4/2 10.2,
+        //             4/6/2 10.3, 2/4/1 11.6
+        //   64 KiB    50000 keywords 4/6/1 7.2, stride 1 8.3
         // So stride 4 up to kPair4Keys windows, up to kPair4MidKeys on texts
         // short enough that fixed costs weigh as much as the stream, and up to
         // kPair4SmallKeys on small ones, which see few positives in all; else
@@ -201,7 +203,7 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
         const bool auto_stride = cfg.stride != 1 && cfg.stride != 2 && cfg.stride != 4;
         const bool small_text = len < (int64_t(16) << 20);
         if (auto_stride) {
-            const int32_t most4 = small_text ? kPair4SmallKeys : len < (int64_t(512) << 20) ? kPair4MidKeys : kPair4Keys;
+            const int32_t most4 = small_text ? kPair4SmallKeys : len < (int64_t(256) << 20) ? kPair4MidKeys : kPair4Keys;
             if (auto_filter && P.pair4 && P.n_quads4 <= most4) {
                 cfg.stride = 4;
                 cfg.filter = small_text && P.n_quads4 <= kPair4Keys ? AC_FILTER_BITS19 : AC_FILTER_PAIR20;
@@ -223,9 +225,9 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
             const int64_t keys = cfg.stride == 4 ? P.n_windows4 : cfg.stride == 2 ? P.n_windows2 : P.n_prefixes;
             // A few prefixes at stride 1 keep the 64 KiB byte map, with the
             // prefix table in LDS beside it, up to 128 MiB (200 keywords of 2
-            // to 8 bytes, 64 MiB: 40.0 us against 42.5 with the 128 KiB map;
-            // 64 keywords of 4 to 12 bytes: 64 MiB 32.0 both, 256 MiB 110.7
-            // and 109.4).
+            // to 8 bytes, 64 MiB: 33.1 us against 35.6 with the 128 KiB map;
+            // 64 keywords of 4 to 12 bytes: 64 MiB 26.8 and 28.0, 256 MiB
+            // 112.0 and 107.1).
             if (small_text || (cfg.stride == 1 && keys <= 1500 && len < (int64_t(128) << 20)))
                 cfg.filter = keys > 1500 ? AC_FILTER_BITS19 : AC_FILTER_BYTES16;
             else if (keys <= 1500) cfg.filter = AC_FILTER_BYTES17;
@@ -243,19 +245,18 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
         }
         if (cfg.block != 256 && cfg.block != 512 && cfg.block != 1024) cfg.block = 1024;
         // One segment per wave step for the shortest texts, which spreads
-        // them over more waves, two above 3 MiB (2 MiB at stride 1, whose
-        // filter takes longer than a load): 1000 keywords, 4/6 (us): 512 KiB
-        // 9.0 with one, 9.6 with two, 2 MiB 10.2 and 9.9, 3 MiB 10.9 and 10.3,
-        // 4 MiB 12.4 and 11.1; 50000 keywords, 2 MiB 9.2 and 9.7; 200 short
-        // keywords at stride 1, 1 MiB 10.8 and 11.4, 2 MiB 12.6 and 11.9, 4
-        // MiB 15.6 and 13.8.  Four for the 4-byte-window map at stride 2 on
-        // texts of 256 MiB and more, where they halve the per-step work of a
-        // filter-bound loop (20000 byte keywords, 1 GiB: 197 with four, 214
-        // with two; 50000, 256 MiB 79.3 and 80.8, 1 GiB 279 and 293); with the
-        // 4-byte-window map at stride 4 four are slower (1000 keywords, 1 GiB:
-        // 180 and 173).
+        // them over more waves, two from 3 MiB on: 1000 keywords, 4/4 (us): 512
+        // KiB 8.8 with one, 9.6 with two, 2 MiB 9.7 and 9.5, 3 MiB 10.6 and
+        // 9.8, 4 MiB 11.5 and 10.2; 50000 keywords, 2 MiB 8.9 and 9.5; 200 short
+        // keywords at stride 1, 1 MiB 10.2 and 11.6, 2 MiB 10.6 and 11.4, 3 MiB
+        // 11.4 and 11.6, 4 MiB 12.3 and 11.9.  Four for the 4-byte-window map at
+        // stride 2 on texts of 256 MiB and more, where they halve the per-step
+        // work of a filter-bound loop (20000 byte keywords: 256 MiB 55.2 with
+        // four, 57.0 with two, 1 GiB 184 and 193; 50000: 192 MiB 60.4 and 60.2,
+        // 256 MiB 77.4 both, 1 GiB 277 and 285); with the 4-byte-window map at
+        // stride 4 four are slower (1000 keywords, 1 GiB: 171 and 166).
         if (cfg.segs != 1 && cfg.segs != 2 && cfg.segs != 4) {
-            cfg.segs = len < (int64_t(cfg.stride == 1 ? 2 : 3) << 20) ? 1 : 2;
+            cfg.segs = len < (int64_t(3) << 20) ? 1 : 2;
             if (cfg.filter == AC_FILTER_PAIR20 && cfg.stride == 2 && len >= (int64_t(256) << 20)) cfg.segs = 4;
         }
         const int64_t fit = std::max<int64_t>(1, a->lds_per_cu / filtered_lds(g));
