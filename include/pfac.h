@@ -176,9 +176,9 @@ int ac_match_async(const ac_automaton *a, const uint8_t *d_text, int64_t len,
  * fixed array in the library's device code instead of per-stream scratch.
  * The call makes no hipMalloc, hipFree or other allocating call, on any call,
  * including the first on a device (which only looks up the array's address
- * there).  The array holds 16 MiB per GPU for the life of the process: 256
- * records of 16 bytes for each of the 4096 waves of the widest launch on a
- * 256-CU MI355X; a launch whose waves would get fewer than 128 records each
+ * there).  The array holds 16 MiB per GPU for the life of the process: 4
+ * KiB (512 records of 8 bytes) for each of the 4096 waves of the widest launch
+ * on a 256-CU MI355X; a launch whose waves would get less than 2 KiB each
  * is rejected with AC_EINVAL (a wave whose records run out finishes its
  * share walking hits as it finds them, which is slower, never wrong).  Every
  * call on one GPU uses that GPU's one array, so two such calls must not

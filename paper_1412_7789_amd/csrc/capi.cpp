@@ -676,12 +676,12 @@ namespace {
 
 // ---- the allocation-free scan's scratch ----------------------------------
 // Hit regions of ac_match_async_noalloc: a fixed device array that each GPU
-// holds for the life of the process (16 MiB: 4096 waves x 256 records of
-// 16 bytes, the widest launch on a 256-CU MI355X).  In host code `scratch`
+// holds for the life of the process (16 MiB: 4096 waves x 512 records of 8
+// bytes, the widest launch on a 256-CU MI355X).  In host code `scratch`
 // only names the array; its device address, one per GPU, comes from
 // hipGetSymbolAddress with that GPU current.
 constexpr int64_t kStaticScratchBytes = int64_t(16) << 20;
-// fewest records per region the scan accepts: two drains' worth
+// smallest region the scan accepts, in pairs of records: four drains' worth
 constexpr int64_t kNoallocMinCap = 128;
 static __device__ __align__(256) uint4 scratch[kStaticScratchBytes / sizeof(uint4)];
 static __device__ __align__(256) unsigned long long scratch_words[kScanWords];   // zero between scans

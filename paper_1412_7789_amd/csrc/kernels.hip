@@ -7,22 +7,23 @@
 //
 // filtered_kernel (default).  A wave owns a 1-4 KiB chunk of text per step:
 //   each lane holds 16 contiguous bytes per 1 KiB segment in VGPRs (one
-//   coalesced 16-byte load; the 2-byte halo comes from the next lane), and
-//   for each of its 16 offsets tests the first K = min(3, shortest keyword)
-//   bytes against a hashed filter of the keywords' K-byte prefixes held in
-//   LDS.  An offset whose prefix is not in the filter cannot start a keyword
-//   (its walk dies within K steps without reaching a final state), so only
-//   the rare candidate offsets are queued (wave ballot + prefix count into a
-//   per-wave LDS queue) and walked, 64 at a time, through the transition
-//   table in global memory (L2-resident rows; dense rows for shallow states,
-//   compact child lists for deep ones).
+//   coalesced 16-byte load; the halo comes from the next lane), and tests them
+//   against a hashed filter in LDS: at stride 1 the first K = min(3, shortest
+//   keyword) bytes of every offset, at strides 2 and 4 every second or fourth
+//   window against the keywords' windows.  What is not in the filter cannot
+//   start a keyword (its walk dies without reaching a final state), so only
+//   the rare candidates are queued (wave ballot + prefix count into a per-wave
+//   LDS queue), looked up in an exact table, 64 at a time, and walked through
+//   the transition table in global memory (L2-resident rows; dense rows for
+//   shallow states, compact child lists for deep ones) or compared with the
+//   one keyword their window belongs to.
 //
 // direct_kernel (plain PFAC).  A block stages its text tile plus a halo of
 //   (longest keyword - 1) bytes in LDS and walks every offset from the root
 //   through the dense table, itself in LDS when it fits.
 //
-// Both emit matches with a wave ballot: one atomic per wave reserves output
-// slots, each lane writes at its rank.  The returned count is exact even when
+// The filtered kernel stages matches in LDS, and one atomic per block reserves
+// their output slots; the direct kernel reserves a slot per match.  The count is exact even when
 // the output buffer is too small (only `cap` entries are written).
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>

@@ -229,7 +229,7 @@ void prefix_buckets(uint32_t x, uint32_t mul, int bits, uint32_t &b1, uint32_t &
 // wave of the widest launch.
 struct HitScratch {
     unsigned long long *words = nullptr;   // [kScanWords], zero between scans: finished blocks, [kScanCount] matches
-    uint4 *hits = nullptr;         // [regions * cap]
+    uint4 *hits = nullptr;         // [regions * cap], each two 8-byte records
     int64_t regions = 0;
     int32_t cap = 0;
 };
