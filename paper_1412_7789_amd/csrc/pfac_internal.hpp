@@ -89,6 +89,8 @@ struct WindowTable {
     std::vector<WindowEntry> entries;    // [1 << bits] and the links' targets
 };
 constexpr uint32_t kWinGeneral = 8u;
+// Entries a window table may have: a link holds an entry's index + 1 in 28 bits.
+constexpr size_t kMaxWindowEntries = (size_t(1) << 28) - 1;
 constexpr uint32_t kWinMul1 = 0x9E3779B1u, kWinMul2 = 0x85EBCA77u;
 // The two buckets (of 4 slots) of window x among 2^nb (nb >= 1).
 #ifdef __HIPCC__

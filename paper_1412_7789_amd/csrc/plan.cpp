@@ -102,8 +102,10 @@ void sort_by_window(std::vector<uint64_t> &w) {
 
 // Builds the exact window table of one stride from (window, state) pairs
 // sorted by window; entry_of(state) gives the state's entry without its link.
+// A table that would need more than max_entries entries is left empty: false.
 template <typename EntryOf>
-void build_windows(const std::vector<uint64_t> &pairs, EntryOf &&entry_of, WindowTable &W) {
+bool build_windows(const std::vector<uint64_t> &pairs, EntryOf &&entry_of, WindowTable &W,
+                   size_t max_entries = kMaxWindowEntries) {
     std::vector<uint32_t> first;              // index of each distinct window's first pair
     for (size_t i = 0; i < pairs.size(); ++i)
         if (i == 0 || (pairs[i] >> 32) != (pairs[i - 1] >> 32)) first.push_back(uint32_t(i));
@@ -113,6 +115,10 @@ void build_windows(const std::vector<uint64_t> &pairs, EntryOf &&entry_of, Windo
     constexpr uint32_t kFree = ~0u;
     std::vector<uint32_t> slot;               // the window in each slot, by its rank
     for (;; ++bits) {
+        if ((size_t(1) << bits) + (pairs.size() - n) > max_entries) {
+            W = WindowTable();
+            return false;
+        }
         const int nb = bits - 2;
         slot.assign(size_t(1) << bits, kFree);
         W.keys.resize(size_t(1) << bits);
@@ -170,6 +176,7 @@ void build_windows(const std::vector<uint64_t> &pairs, EntryOf &&entry_of, Windo
             W.entries.push_back(e);
         }
     }
+    return true;
 }
 
 }  // namespace
@@ -566,8 +573,15 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
         entry.push_back(e);
     }
     auto entry_of = [&](int32_t s) { return entry[size_t(s - at_depth[5])]; };
-    if (P.pair2) build_windows(quads2, entry_of, P.win[window_set(2)]);
-    if (P.pair4) build_windows(quads4, entry_of, P.win[window_set(4)]);
+    // without its table a stride has no 4-byte-window map either
+    if (P.pair2 && !build_windows(quads2, entry_of, P.win[window_set(2)])) {
+        P.pair2 = false;
+        P.filter[stride_set(2) * kNumFilterKinds + AC_FILTER_PAIR20 - 1].clear();
+    }
+    if (P.pair4 && !build_windows(quads4, entry_of, P.win[window_set(4)])) {
+        P.pair4 = false;
+        P.filter[stride_set(4) * kNumFilterKinds + AC_FILTER_PAIR20 - 1].clear();
+    }
     // keyword bytes (for tail comparisons) with int32 offsets
     P.kw_bytes.assign(bytes + offsets[0], bytes + offsets[0] + total);
     P.kw_off.resize(size_t(n) + 1);
