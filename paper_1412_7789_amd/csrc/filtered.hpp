@@ -579,16 +579,18 @@ __device__ __forceinline__ void load_chunk(const FilterLaunch &F, int64_t c, uns
     R.tail = __builtin_amdgcn_raw_buffer_load_b32(rsrc, int(CH), 0, 0);
 }
 
-// Segment j of a chunk alone.
+// Segment j of a chunk alone.  The segment's offset is part of the vector
+// offset, as in load_chunk: the scalar one takes no part in the check against
+// `records`, which is what ends a last chunk's loads at the text's end.
 template <int SEGS>
 __device__ __forceinline__ void load_segment(const FilterLaunch &F, int64_t c, int j, unsigned lane, ChunkRegs<1> &R) {
     constexpr int64_t CH = int64_t(SEGS) * kSegBytes;
     const int records = c < F.c_hi ? int(CH + 16) : int(((F.V + 3) & ~int64_t(3)) - c * CH);
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(F.base + c * CH), short(0), records, kBufferFlags);
-    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(lane * 16u), j * kSegBytes, 0);
+    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc, int(lane * 16u) + j * kSegBytes, 0, 0);
     R.d[0][0] = q.x; R.d[0][1] = q.y; R.d[0][2] = q.z; R.d[0][3] = q.w;
-    R.tail = __builtin_amdgcn_raw_buffer_load_b32(rsrc, 0, (j + 1) * kSegBytes, 0);
+    R.tail = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (j + 1) * kSegBytes, 0, 0);
 }
 
 // Candidate mask of the N segments from J0 on: bit 16 i + s is set when offset
