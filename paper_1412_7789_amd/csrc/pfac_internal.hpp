@@ -171,8 +171,8 @@ struct ScanArgs {
     int32_t *out_pid;
     int32_t *out_tid;              // batch only
     int64_t cap;                   // 0 = count only
-    // the first near_cap matches go to these arrays instead (pinned host
-    // memory of a caller that wants them there)
+    // the first near_cap matches of a single text go to these arrays instead
+    // (pinned host memory of a caller that reads them when the count arrives)
     int64_t near_cap;
     int64_t *near_off;
     int32_t *near_pid;

@@ -13,14 +13,15 @@ from paper_1412_7789_amd import build as lib_build
 HIPCC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
 
 
-def instructions(tmp_path, source):
-    """The instructions of the kernels in `source`, which may use filtered.hpp."""
+def instructions(tmp_path, source, also="buffer_"):
+    """The memory instructions of the kernels in `source`, which may use
+    filtered.hpp, and those that start with `also`."""
     src, asm = tmp_path / "snippet.hip", tmp_path / "snippet.s"
     src.write_text('#include "filtered.hpp"\nusing namespace pfac;\nusing namespace pfac::dev;\n' + source)
     subprocess.run([HIPCC, *lib_build.HIPCC_FLAGS, f"-I{lib_build.INCLUDE}", f"-I{lib_build.CSRC}", "-x", "hip",
                     "--cuda-device-only", "-S", str(src), "-o", str(asm)], check=True, capture_output=True, text=True)
     lines = (line.split(";")[0].strip() for line in asm.read_text().splitlines())
-    return [line for line in lines if re.match(r"(buffer|global|flat)_", line)]
+    return [line for line in lines if re.match(r"(buffer|global|flat)_|" + also, line)]
 
 
 @pytest.mark.parametrize("segs", [1, 2, 4])
@@ -50,3 +51,17 @@ __global__ void one(FilterLaunch F, int64_t c, int j, uint32_t *out) {{
         assert m, i
         assert m.group(2) == "0", i
         assert m.group(1) == "off" or "offen" in m.group(3), i
+
+
+def test_matches_for_the_host_are_released_before_the_count(tmp_path):
+    """The host reads a dispatched call's pinned match arrays as soon as the
+    count is reported, before the kernel's end: every block releases its matches
+    to the system (a cache writeback at system scope) before it counts itself
+    done, only where there are such arrays."""
+    code = instructions(tmp_path, """
+__global__ void report(ScanArgs S) { report_count(S); }
+""", also="s_cbranch")
+    release = code.index("buffer_wbl2 sc0 sc1")
+    done = next(i for i, line in enumerate(code) if "atomic_add" in line)
+    assert release < done
+    assert code[release - 1].startswith("s_cbranch"), "a scan without pinned arrays needs no writeback"
