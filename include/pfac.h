@@ -163,7 +163,10 @@ int64_t ac_match_ex(const ac_automaton *a, const uint8_t *d_text, int64_t len,
  * and an empty text clear d_count with a kernel first; no memset).  Only the
  * first call on a stream allocates (the stream's scratch, sized for any text); after one
  * call on the stream it may be captured in a HIP graph.  Replays of captured
- * scans that share a stream's scratch must not overlap.
+ * scans that share a stream's scratch must not overlap: the results of those
+ * that do are undefined, and so are those of later asynchronous scans with that
+ * scratch until a call with len = 0 on the stream (or ac_release_stream) has
+ * put it in order again.
  */
 int ac_match_async(const ac_automaton *a, const uint8_t *d_text, int64_t len,
                    const ac_matches *matches, const ac_launch *launch,
@@ -183,7 +186,9 @@ int ac_match_async(const ac_automaton *a, const uint8_t *d_text, int64_t len,
  * share walking hits as it finds them, which is slower, never wrong).  Every
  * call on one GPU uses that GPU's one array, so two such calls must not
  * overlap on a GPU (serialise them on one stream, or wait between them);
- * overlapping calls race on the array and their results are undefined.
+ * overlapping calls race on the array and their results are undefined, and so
+ * are those of later calls until one with len = 0, overlapping no other, has
+ * put the array in order again.
  * Matches, count, launch choices and errors are those of ac_match_async.
  */
 int ac_match_async_noalloc(const ac_automaton *a, const uint8_t *d_text, int64_t len,

@@ -303,7 +303,7 @@ int device_matches(const ac_automaton *a) {
     return AC_OK;
 }
 
-// Enqueue zero + scan for one text or a batch.
+// floor(log4 n)
 int length_bucket(int64_t n) {
     int b = 0;
     while (n >= 4) { n >>= 2; ++b; }
@@ -335,9 +335,9 @@ ac_launch resolved(const ac_automaton *a, const ScanArgs &S, const ac_launch *la
     return cfg;
 }
 
-// Enqueue the scan of one text or a batch.  `clear` first zeroes *d_count
-// (and the batch's per-text counts); otherwise matches are numbered from
-// S.count_base.
+// Enqueue the scan of one text or a batch.  `clear` first zeroes *d_count, the
+// scratch's words (S.done points at the first) and the batch's per-text
+// counts; otherwise matches are numbered from S.count_base.
 int enqueue(const ac_automaton *a, ScanArgs S, const ac_launch &cfg, bool batch, bool clear,
             unsigned long long *d_count, const HitScratch &hs, hipStream_t stream,
             const KernelTiming *timing = nullptr) {
@@ -356,13 +356,14 @@ int enqueue(const ac_automaton *a, ScanArgs S, const ac_launch &cfg, bool batch,
 // counts in its scratch and its last block stores the sum, so it is one launch
 // (enqueueing takes 5.1 us instead of 7.8; a 4 MiB text 9.4 us in a graph
 // instead of 10.0); per-text counts, other policies and empty texts clear the
-// words with a kernel first.
+// count with a kernel first, and the scratch's words with it, should scans that
+// overlapped against the rules have left something in them.
 int enqueue_async(const ac_automaton *a, ScanArgs S, const ac_launch &cfg, bool batch, int64_t *d_count,
                   const HitScratch &hs, hipStream_t stream) {
     auto *count = reinterpret_cast<unsigned long long *>(d_count);
+    S.done = hs.words;
     if (cfg.policy != AC_POLICY_FILTERED || S.n <= 0 || S.per_text)
         return enqueue(a, S, cfg, batch, true, count, hs, stream);
-    S.done = hs.words;
     S.dev_count = count;
     return enqueue(a, S, cfg, batch, false, hs.words + kScanCount, hs, stream);
 }
@@ -724,6 +725,7 @@ int ac_match_async_noalloc(const ac_automaton *a, const uint8_t *d_text, int64_t
     const ScanArgs S = single_args(d_text, len, matches);
     const ac_launch cfg = resolved(a, S, launch, false);
     HitScratch hs;
+    if (cfg.policy == AC_POLICY_FILTERED && (rc = static_scratch(a->device, &hs))) return rc;
     if (cfg.policy == AC_POLICY_FILTERED && len > 0) {
         const int64_t regions = scan_regions(a, S.text, S.n, cfg);
         const int64_t cap = std::min<int64_t>(kHitCap, kStaticScratchBytes / int64_t(sizeof(uint4)) / regions);
@@ -732,7 +734,6 @@ int ac_match_async_noalloc(const ac_automaton *a, const uint8_t *d_text, int64_t
                                        " hit regions of at least " + std::to_string(kNoallocMinCap) +
                                        " records; the static scratch holds " +
                                        std::to_string(kStaticScratchBytes) + " bytes");
-        if ((rc = static_scratch(a->device, &hs))) return rc;
         hs.regions = regions;
         hs.cap = int32_t(cap);
     }

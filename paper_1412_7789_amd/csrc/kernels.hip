@@ -79,10 +79,11 @@ __global__ __launch_bounds__(1024) void direct_kernel(const DevAut A, const Scan
     }
 }
 
-__global__ void zero_kernel(unsigned long long *count, unsigned long long *done, int64_t *per_text, int32_t n_texts) {
+// Clears a count, the scratch's words (if given) and the per-text counts.
+__global__ void zero_kernel(unsigned long long *count, unsigned long long *words, int64_t *per_text, int32_t n_texts) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i == 0) *count = 0ull;
-    if (i == 0 && done) *done = 0ull;
+    if (i == 0 && words) words[0] = words[kScanCount] = 0ull;
     if (per_text && i < n_texts) per_text[i] = 0;
 }
 
@@ -284,11 +285,11 @@ int launch_probe_read(const uint8_t *buf, int64_t n, uint32_t *out, hipStream_t 
     return AC_OK;
 }
 
-int launch_zero(unsigned long long *count, unsigned long long *done, int64_t *per_text, int32_t n_texts,
+int launch_zero(unsigned long long *count, unsigned long long *words, int64_t *per_text, int32_t n_texts,
                 hipStream_t stream, std::string &err) {
     const int32_t threads = 256;
     const int32_t blocks = std::max<int32_t>(1, (std::max<int32_t>(n_texts, 1) + threads - 1) / threads);
-    zero_kernel<<<blocks, threads, 0, stream>>>(count, done, per_text, n_texts);
+    zero_kernel<<<blocks, threads, 0, stream>>>(count, words, per_text, n_texts);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { err = std::string("zero_kernel launch: ") + hipGetErrorString(e); return AC_EHIP; }
     return AC_OK;

@@ -256,7 +256,7 @@ struct KernelTiming {
 };
 int launch_scan(const ac_automaton *a, const ScanArgs &args, const ac_launch &cfg, const HitScratch &hs,
                 hipStream_t stream, std::string &err, const KernelTiming *timing = nullptr);
-int launch_zero(unsigned long long *count, unsigned long long *done, int64_t *per_text, int32_t n_texts,
+int launch_zero(unsigned long long *count, unsigned long long *words, int64_t *per_text, int32_t n_texts,
                 hipStream_t stream, std::string &err);
 void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &cfg);
 

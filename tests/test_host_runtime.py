@@ -1,0 +1,97 @@
+"""Host code of the GPU entry points on a HIP runtime made of host memory
+(CPU only): small programs include the library's host sources and stand in for
+the kernel launches, so what a call leaves behind can be set up and read."""
+
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+# stands in for kernels.hip: a scan counts with the CPU matcher the way the
+# kernel does, adding to the count word and handing it out at the end
+PRELUDE = r"""
+#include "fake_hip.hpp"
+#include "plan.cpp"
+#include "host_match.cpp"
+#include "capi.cpp"
+#include <cstdio>
+
+namespace pfac {
+void resolve_launch(const ac_automaton *, int64_t, bool, ac_launch &cfg) {
+    if (!cfg.policy) cfg.policy = AC_POLICY_FILTERED;
+}
+int64_t scan_regions(const ac_automaton *, const uint8_t *, int64_t, const ac_launch &) { return 32; }
+int64_t widest_scan_regions(int, int64_t) { return 32; }
+int launch_probe_read(const uint8_t *, int64_t, uint32_t *, hipStream_t, std::string &) { return AC_OK; }
+int launch_zero(unsigned long long *count, unsigned long long *words, int64_t *per_text, int32_t n_texts, hipStream_t,
+                std::string &) {
+    *count = 0;
+    if (words) words[0] = words[kScanCount] = 0;
+    for (int32_t t = 0; per_text && t < n_texts; ++t) per_text[t] = 0;
+    return AC_OK;
+}
+int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &, const HitScratch &, hipStream_t,
+                std::string &, const KernelTiming *) {
+    if (S.n <= 0) return AC_OK;
+    const int64_t n = host_match(a->host, S.text, S.n, nullptr, nullptr, 0, 1);
+    *S.count += uint64_t(n);
+    if (S.done && S.done[0] != 0) return AC_OK;      // counts of another scan: no block is the last
+    if (S.dev_count) { *S.dev_count = *S.count; *S.count = 0; }
+    if (S.host_count) { S.host_count[0] = *S.count; S.host_count[1] = report_tag(*S.count, S.host_seq); }
+    return AC_OK;
+}
+}  // namespace pfac
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s (%s)\n", __LINE__, #c, ac_last_error()); return 1; } } while (0)
+const uint8_t *kText = reinterpret_cast<const uint8_t *>("abcdefgh-abcdefgh-abcdefgh");
+const int64_t kLen = 26;
+ac_automaton *make() {
+    const int64_t offs[2] = {0, 8};
+    ac_automaton *a = nullptr;
+    return ac_build_csr(kText, offs, 1, nullptr, &a) == AC_OK ? a : nullptr;
+}
+"""
+
+
+def run(tmp_path, source, prelude=PRELUDE):
+    (tmp_path / "main.cpp").write_text(prelude + source)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include",
+                    f"-I{ROOT}/include", f"-I{ROOT}/paper_1412_7789_amd/csrc", f"-I{ROOT}/tests",
+                    str(tmp_path / "main.cpp"), "-o", str(tmp_path / "main"), "-lpthread"], check=True)
+    res = subprocess.run([str(tmp_path / "main")], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_counts_left_by_overlapping_scans_are_cleared(tmp_path):
+    """Asynchronous scans count in words of their scratch that are zero between
+    scans.  Scans that overlapped against the rules may leave something
+    there; an asynchronous call of an empty text puts the words back to
+    zero, the array's of ac_match_async_noalloc and a stream's, and a
+    synchronous call that clears its count does so for its stream's."""
+    run(tmp_path, r"""
+int main() {
+    ac_automaton *a = make();
+    CHECK(a);
+    int64_t count = -1;
+    CHECK(ac_match_async_noalloc(a, kText, kLen, nullptr, nullptr, &count, nullptr) == AC_OK && count == 3);
+    scratch_words[0] = 5;
+    scratch_words[kScanCount] = 7;
+    CHECK(ac_match_async_noalloc(a, kText, 0, nullptr, nullptr, &count, nullptr) == AC_OK && count == 0);
+    CHECK(ac_match_async_noalloc(a, kText, kLen, nullptr, nullptr, &count, nullptr) == AC_OK && count == 3);
+
+    CHECK(ac_match_async(a, kText, kLen, nullptr, nullptr, &count, nullptr) == AC_OK && count == 3);
+    CountSlot &slot = g_slots.begin()->second;
+    auto poison = [&] { slot.hs.words[0] = 5; slot.hs.words[kScanCount] = 7; };
+    poison();
+    CHECK(ac_match_async(a, kText, 0, nullptr, nullptr, &count, nullptr) == AC_OK && count == 0);
+    CHECK(ac_match_async(a, kText, kLen, nullptr, nullptr, &count, nullptr) == AC_OK && count == 3);
+
+    poison();
+    slot.stale = true;
+    CHECK(ac_match(a, kText, kLen, nullptr, nullptr) == 3);
+    CHECK(ac_match_async(a, kText, kLen, nullptr, nullptr, &count, nullptr) == AC_OK && count == 3);
+    CHECK(ac_match(a, kText, kLen, nullptr, nullptr) == 3);
+    ac_free(a);
+    return 0;
+}
+""")
