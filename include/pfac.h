@@ -383,7 +383,9 @@ int ac_probe_read(const uint8_t *d_buf, int64_t n, uint32_t *d_out, hipStream_t 
  *   AC_TABLE_WINDOW2_KEYS, AC_TABLE_WINDOW4_KEYS  uint32[slots], slots a power of two:
  *                          exact table of the 4-byte windows (little-endian) at
  *                          keyword positions 1 .. 2 and 1 .. 4 in buckets of 4
- *                          (empty when a keyword has fewer than stride + 4 bytes);
+ *                          (empty when a keyword has fewer than stride + 4 bytes,
+ *                          or for sets so large that default launches never use
+ *                          the stride);
  *                          window x lies in bucket b1 = x * 0x9E3779B1 >> (32 - nb)
  *                          or b2 = (x ^ x >> 15) * 0x85EBCA77 >> (32 - nb), nb =
  *                          log2(slots) - 2 (b1 ^ 1 if both agree)

@@ -610,7 +610,8 @@ __device__ __forceinline__ void load_segment(const FilterLaunch &F, int64_t c, i
 // rotating the word right by p (mod 32) moves the key's bit (x * mul) mod 32
 // to b.  Adding c may carry into the word index; the host sets each key's
 // bit in both words that can result.
-template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, int J0, int N>
+// PAIR (strides 2 and 4): the 4-byte windows' map, tested as in filter_windows.
+template <int K, bool BITMAP, int SEGS, int FLOG2, int STRIDE, bool DUAL, bool PAIR, int J0, int N>
 __device__ __forceinline__ uint32_t filter_offsets(const ChunkRegs<SEGS> &R, unsigned lane, const uint8_t *sfilt,
                                                    uint32_t mul, uint32_t (&d4)[N]) {
     constexpr uint32_t kmask = K >= 3 ? 0xFFFFFFu : ((1u << (8 * K)) - 1u);
@@ -655,7 +656,13 @@ __device__ __forceinline__ uint32_t filter_offsets(const ChunkRegs<SEGS> &R, uns
                 const int b = s - STRIDE;                 // destination bit
                 const uint32_t c = uint32_t(32 - b) & 31u;
                 const uint32_t p = hash24(x, mul) + c;
-                if (BITMAP) {
+                if (PAIR) {
+                    const uint32_t p1 = hash24(x, mul);
+                    const uint32_t w1 = fm[p1 >> shift];
+                    uint32_t v = (w1 >> (p1 & 31u)) & (w1 >> ((x >> 24) & 31u));
+                    if (STRIDE == 2) v &= w1 >> ((x >> 16) & 31u);
+                    mj |= (v & 1u) << b;
+                } else if (BITMAP) {
                     uint32_t v;
                     if (DUAL) {
                         // two maps of 2^(FLOG2 - 3) words, independent hashes: both bits must be set
@@ -850,8 +857,7 @@ __device__ __forceinline__ int prefix16(int v, unsigned lane) {
 // once.  The chunk loop has no walk, atomic in global memory, call or other
 // dependent global access apart from drains.
 //
-// WIN (strides 2 and 4, when every keyword has stride + 4 bytes): a queue
-// entry is a positive window and its four bytes, taken from the registers
+// WIN (strides 2 and 4, with the stride's window table): a queue entry is a positive window and its four bytes, taken from the registers
 // that were filtered.  A drain looks the bytes up in the exact window table
 // (two 16-byte loads per lane) and keeps {position, table slot} of those that
 // are a keyword's window.  It reads no text, and a positive is one entry
@@ -967,7 +973,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         constexpr int N = int(sizeof(d4) / 4);
         constexpr int NS = int(sizeof(R.d) / 16);
         if constexpr (WIN) return filter_windows<BITMAP, NS, FLOG2, STRIDE, DUAL, PAIR, J0, N>(R, lane, sfilt, mul, d4);
-        else return filter_offsets<K, BITMAP, NS, FLOG2, STRIDE, DUAL, J0, N>(R, lane, sfilt, mul, d4);
+        else return filter_offsets<K, BITMAP, NS, FLOG2, STRIDE, DUAL, PAIR, J0, N>(R, lane, sfilt, mul, d4);
     };
     // Filters and queues the chunk held in R (slot k) in groups of at most two
     // segments (more at once spill registers).  On a refusal `rest` holds what
@@ -1358,8 +1364,8 @@ FilteredFn pick_filter(int kind, int segs) {
         case AC_FILTER_BYTES16: return pick_segs<K, false, 16, STRIDE, false, false, WIN>(segs);
         case AC_FILTER_DUAL19: return pick_segs<K, true, 17, STRIDE, true, false, WIN>(segs);
         case AC_FILTER_PAIR20:
-            // its keys are the window table's, so it always has one (strides 2 and 4)
-            if constexpr (WIN) return pick_segs<K, true, 17, STRIDE, false, true, true>(segs);
+            // strides 2 and 4 only
+            if constexpr (STRIDE > 1) return pick_segs<K, true, 17, STRIDE, false, true, WIN>(segs);
             else return nullptr;
         default: return pick_segs<K, true, 16, STRIDE, false, false, WIN>(segs);
     }

@@ -155,12 +155,6 @@ hipError_t launch_timed(const void *fn, dim3 grid, dim3 block, void **args, size
     return hipLaunchKernel(fn, grid, block, args, lds, stream);
 }
 
-// Most 4-byte windows for which the launch rules choose stride 4 on any text,
-// on texts under 256 MiB and on texts under 16 MiB, and stride 2 with the
-// 4-byte-window map.
-constexpr int32_t kPair4Keys = 32768, kPair4MidKeys = 100000, kPair4SmallKeys = 262144;
-constexpr int32_t kPair2Keys = 131072;
-
 std::mutex g_attr_mu;
 
 void allow_lds(const void *fn, int64_t bytes) {
@@ -198,7 +192,8 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
         // So stride 4 up to kPair4Keys windows, up to kPair4MidKeys on texts
         // short enough that fixed costs weigh as much as the stream, and up to
         // kPair4SmallKeys on small ones, which see few positives in all; else
-        // stride 2 up to kPair2Keys, with the 4-byte-window map.  Small texts
+        // stride 2 up to kPair2Keys, with the 4-byte-window map.  The window
+        // tables exist where these rules choose their stride.  Small texts
         // take the 64 KiB bit map while its keys are few: less to stage, and
         // room for the window keys beside it.
         const bool auto_filter = cfg.filter < AC_FILTER_BYTES17 || cfg.filter > AC_FILTER_PAIR20;
@@ -209,7 +204,7 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
             if (auto_filter && P.pair4 && P.n_quads4 <= most4) {
                 cfg.stride = 4;
                 cfg.filter = small_text && P.n_quads4 <= kPair4Keys ? AC_FILTER_BITS19 : AC_FILTER_PAIR20;
-            } else if (P.sampled && (P.n_windows2 <= 65536 ||
+            } else if (P.sampled && (P.n_windows2 <= kStride2Keys ||
                                      (auto_filter && !small_text && P.pair2 && P.n_quads2 <= kPair2Keys))) {
                 cfg.stride = 2;
                 if (auto_filter && !small_text && P.pair2 && P.n_quads2 <= kPair2Keys) cfg.filter = AC_FILTER_PAIR20;
@@ -328,7 +323,6 @@ int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &cfg, 
             err = "text too large for one launch";
             return AC_EINVAL;
         }
-        // the window table exists for keywords of stride + 4 bytes and more
         const bool win = F.win_keys != nullptr;
         FilteredFn fn = pick_filtered(P.K, cfg.filter, cfg.segs, cfg.stride, win);
         if (!fn) { err = "no kernel for this filter and stride"; return AC_EINVAL; }

@@ -72,6 +72,16 @@ constexpr int kNumFilters = 3 * kNumFilterKinds;   // strides 1, 2 and 4
 // Filter set of a sampling stride: 0 (stride 1), 1 (stride 2), 2 (stride 4).
 constexpr int stride_set(int stride) { return stride == 4 ? 2 : stride - 1; }
 
+// Most 4-byte windows for which the launch rules choose stride 4 on any text,
+// on texts under 256 MiB and on texts under 16 MiB, and stride 2 with the
+// 4-byte-window map; most 3-byte windows for which they choose stride 2 with
+// any map.  A stride that they never choose for a set has no window table,
+// which would take 20 bytes of device memory per slot (about 250 MB for a
+// million keywords of 8 bytes) for explicit and tuned launches alone; those
+// look candidates up in the prefix table.
+constexpr int32_t kPair4Keys = 32768, kPair4MidKeys = 100000, kPair4SmallKeys = 262144;
+constexpr int32_t kPair2Keys = 131072, kStride2Keys = 65536;
+
 // Exact table of the 4-byte windows x at keyword positions 1 .. stride: every
 // window leads to the keyword paths it lies on.  A two-choice cuckoo table of
 // 4-key buckets (16 bytes, one load) holds the windows; the entry of slot i
@@ -131,7 +141,8 @@ struct Plan {
     int32_t n_quads2 = 0;          // distinct 4-byte windows at keyword positions 1 and 2
     bool pair2 = false;            // the stride-2 AC_FILTER_PAIR20 map exists
     std::vector<uint8_t> filter[kNumFilters];   // indexed by stride_set(stride) * kNumFilterKinds + kind - 1
-    // exact window tables of strides 2 and 4 (empty without the 4-byte windows)
+    // exact window tables of strides 2 and 4 (empty without the 4-byte windows,
+    // or where the launch rules never choose the stride)
     WindowTable win[2];
     int32_t ptab_bits = 0;
     std::vector<uint32_t> ptab;    // [2 << ptab_bits]: buckets of 4 {key, value} slots

@@ -560,8 +560,10 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     // stride + 4 bytes), so the path down to it is compared as a whole: with
     // its keyword, when the rest is forced down to a leaf with one keyword
     // (and none ends on the way), else down to the state, where a walk goes on.
+    const bool table2 = P.pair2 && (P.n_quads2 <= kPair2Keys || P.n_windows2 <= kStride2Keys);
+    const bool table4 = P.pair4 && P.n_quads4 <= kPair4SmallKeys;
     std::vector<WindowEntry> entry;           // of the states from at_depth[5] on, in their order
-    for (int32_t s = at_depth[5]; s < at_depth[P.pair4 ? 9 : 7] && P.pair2; ++s) {
+    for (int32_t s = at_depth[5]; s < at_depth[table4 ? 9 : 7] && (table2 || table4); ++s) {
         const int32_t d = P.depth[size_t(s)], l = P.tail[size_t(s)];
         const int32_t p = rep[size_t(s)];
         WindowEntry e{int32_t(offsets[p] - offsets[0]), d, s, uint32_t(d - 4) | kWinGeneral};
@@ -573,15 +575,8 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
         entry.push_back(e);
     }
     auto entry_of = [&](int32_t s) { return entry[size_t(s - at_depth[5])]; };
-    // without its table a stride has no 4-byte-window map either
-    if (P.pair2 && !build_windows(quads2, entry_of, P.win[window_set(2)])) {
-        P.pair2 = false;
-        P.filter[stride_set(2) * kNumFilterKinds + AC_FILTER_PAIR20 - 1].clear();
-    }
-    if (P.pair4 && !build_windows(quads4, entry_of, P.win[window_set(4)])) {
-        P.pair4 = false;
-        P.filter[stride_set(4) * kNumFilterKinds + AC_FILTER_PAIR20 - 1].clear();
-    }
+    if (table2) build_windows(quads2, entry_of, P.win[window_set(2)]);
+    if (table4) build_windows(quads4, entry_of, P.win[window_set(4)]);
     // keyword bytes (for tail comparisons) with int32 offsets
     P.kw_bytes.assign(bytes + offsets[0], bytes + offsets[0] + total);
     P.kw_off.resize(size_t(n) + 1);

@@ -68,3 +68,30 @@ def test_the_limit_is_what_a_link_can_hold(lines):
     last = limit - 1                     # the last entry's index
     assert ((last + 1) << 4) & 0xFFFFFFFF == (last + 1) << 4
     assert ((last + 2) << 4) & 0xFFFFFFFF != (last + 2) << 4
+
+
+@pytest.mark.parametrize("n,alphabet,tables", [
+    (60_000, 256, (True, True)),      # 120,000 windows at stride 2, 240,000 at stride 4
+    (66_000, 256, (False, False)),    # 132,000 and 264,000
+    (100_000, 40, (True, False)),     # at most 64,000 3-byte windows: stride 2 is a default
+], ids=["both", "neither", "stride 2"])
+def test_tables_exist_where_default_launches_use_them(n, alphabet, tables):
+    """Both tables would take 20 bytes of device memory per slot; the 4-byte
+    windows' maps and counts are there either way."""
+    import numpy as np
+
+    import paper_1412_7789_amd as pf
+    from paper_1412_7789_amd import _lib as L
+
+    rng = np.random.default_rng(n)
+    kws = [bytes(k) for k in rng.integers(0, alphabet, size=(n, 8), dtype=np.uint8)]
+    plan = pf.Plan(kws)
+    info = plan.info()
+    for stride, (keys, entries), wanted, windows in (
+            (2, (L.AC_TABLE_WINDOW2_KEYS, L.AC_TABLE_WINDOW2_ENTRIES), tables[0], info["n_quads2"]),
+            (4, (L.AC_TABLE_WINDOW4_KEYS, L.AC_TABLE_WINDOW4_ENTRIES), tables[1], info["n_quads4"])):
+        assert windows == len({k[j:j + 4] for k in kws for j in range(1, stride + 1)})
+        assert (len(plan.export(keys, np.uint32)) > windows) == wanted
+        assert (len(plan.export(entries, np.int32)) > 0) == wanted
+        pair = plan.export(L.AC_TABLE_FILTER_BASE + 6 * (stride // 2) + L.AC_FILTER_PAIR20, np.uint8)
+        assert len(pair) == 1 << 17
