@@ -384,8 +384,8 @@ int ac_probe_read(const uint8_t *d_buf, int64_t n, uint32_t *d_out, hipStream_t 
  *                          exact table of the 4-byte windows (little-endian) at
  *                          keyword positions 1 .. 2 and 1 .. 4 in buckets of 4
  *                          (empty when a keyword has fewer than stride + 4 bytes,
- *                          or for sets so large that default launches never use
- *                          the stride);
+ *                          for sets so large that default launches never use
+ *                          the stride, and where windows lie on many paths);
  *                          window x lies in bucket b1 = x * 0x9E3779B1 >> (32 - nb)
  *                          or b2 = (x ^ x >> 15) * 0x85EBCA77 >> (32 - nb), nb =
  *                          log2(slots) - 2 (b1 ^ 1 if both agree)
@@ -394,8 +394,10 @@ int ac_probe_read(const uint8_t *d_buf, int64_t n, uint32_t *d_out, hipStream_t 
  *                          {keyword-byte position of the path's start, bytes to
  *                          compare from there, keyword id or state, window position
  *                          | general << 3 | (next entry + 1) << 4}; general: the
- *                          compared path ends at that state and the walk goes on,
- *                          else it is that whole keyword (length 0: empty slot)
+ *                          compared path ends at that state and the walk goes on
+ *                          (with length 0 from the root, for a window on many
+ *                          paths), else it is that whole keyword (length 0: empty
+ *                          slot)
  *   AC_TABLE_FILTER_BASE + k   filter map of kind k = AC_FILTER_* (stride 1),
  *                              k = 6 + AC_FILTER_* (stride 2, may be empty),
  *                              k = 12 + AC_FILTER_* (stride 4, may be empty);

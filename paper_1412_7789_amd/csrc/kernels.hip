@@ -193,14 +193,21 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
         // short enough that fixed costs weigh as much as the stream, and up to
         // kPair4SmallKeys on small ones, which see few positives in all; else
         // stride 2 up to kPair2Keys, with the 4-byte-window map.  The window
-        // tables exist where these rules choose their stride.  Small texts
+        // tables exist where these rules choose their stride.  Without one
+        // (windows on many paths) a positive costs a prefix lookup for each of
+        // its offsets, and stride 4 is left to texts of 16 MiB and more and sets
+        // of up to kPair4PrefixKeys windows (32 MiB of prose-like words, 2000 of
+        // them, 4500 windows: 4/6/2 294, 2/6/2 284, stride 1 464).  Small texts
         // take the 64 KiB bit map while its keys are few: less to stage, and
         // room for the window keys beside it.
         const bool auto_filter = cfg.filter < AC_FILTER_BYTES17 || cfg.filter > AC_FILTER_PAIR20;
         const bool auto_stride = cfg.stride != 1 && cfg.stride != 2 && cfg.stride != 4;
         const bool small_text = len < (int64_t(16) << 20);
         if (auto_stride) {
-            const int32_t most4 = small_text ? kPair4SmallKeys : len < (int64_t(256) << 20) ? kPair4MidKeys : kPair4Keys;
+            const int32_t most4 = P.win[window_set(4)].bits == 0 ? (small_text ? 0 : kPair4PrefixKeys)
+                                  : small_text                   ? kPair4SmallKeys
+                                  : len < (int64_t(256) << 20)   ? kPair4MidKeys
+                                                                 : kPair4Keys;
             if (auto_filter && P.pair4 && P.n_quads4 <= most4) {
                 cfg.stride = 4;
                 cfg.filter = small_text && P.n_quads4 <= kPair4Keys ? AC_FILTER_BITS19 : AC_FILTER_PAIR20;

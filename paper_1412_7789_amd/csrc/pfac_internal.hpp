@@ -75,12 +75,13 @@ constexpr int stride_set(int stride) { return stride == 4 ? 2 : stride - 1; }
 // Most 4-byte windows for which the launch rules choose stride 4 on any text,
 // on texts under 256 MiB and on texts under 16 MiB, and stride 2 with the
 // 4-byte-window map; most 3-byte windows for which they choose stride 2 with
-// any map.  A stride that they never choose for a set has no window table,
+// any map (kPair4PrefixKeys: stride 4 on texts of 16 MiB and more for sets without
+// a window table).  A stride that they never choose for a set has no window table,
 // which would take 20 bytes of device memory per slot (about 250 MB for a
 // million keywords of 8 bytes) for explicit and tuned launches alone; those
 // look candidates up in the prefix table.
 constexpr int32_t kPair4Keys = 32768, kPair4MidKeys = 100000, kPair4SmallKeys = 262144;
-constexpr int32_t kPair2Keys = 131072, kStride2Keys = 65536;
+constexpr int32_t kPair2Keys = 131072, kStride2Keys = 65536, kPair4PrefixKeys = 12000;
 
 // Exact table of the 4-byte windows x at keyword positions 1 .. stride: every
 // window leads to the keyword paths it lies on.  A two-choice cuckoo table of
@@ -92,6 +93,7 @@ struct WindowEntry {
     int32_t len;       // bytes to compare with the text from the path's start
     int32_t what;      // general: the state at depth len; else the keyword id
     uint32_t link;     // window position (bits 0..2) | general << 3 | (next entry + 1) << 4
+    // general with len 0 (and the root): a position of a window on many paths
 };
 struct WindowTable {
     int32_t bits = 0;                    // log2(slots)

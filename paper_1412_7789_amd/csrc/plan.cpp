@@ -100,6 +100,59 @@ void sort_by_window(std::vector<uint64_t> &w) {
     }
 }
 
+// The most paths a window keeps in its table (share_windows replaces more), or 0
+// for a set that is better without the table.
+//
+// A lane follows the entries of its window one by one, and the wave waits for
+// its longest chain, where the prefix table's drains spread a window's `stride`
+// offsets over lanes.  So the table pays while windows mostly lie on few paths.
+// It does not once half of all paths lie on windows of stride + 2 or more
+// (calls, 32 MiB of digits, keywords of 8 to 12: 10,000 of them, typically 5
+// paths a window, 692 us with the table and 890 without; 15,000, 6 paths, 941
+// and 860; 32 MiB of ACGT, 20,000 keywords, 16,260 and 1360), nor with more than
+// 1 of 100 paths on windows that are far more crowded than that (32 MiB of
+// prose-like words: 2000 words 848 and 299, 200 words 135 and 120).  With
+// fewer, those windows alone are shared (32 MiB of log lines, 5000 keywords and
+// 40 more with one middle: 77 us with chains, 39 shared).  Sets of a few
+// keywords have too few paths to tell.
+int32_t most_paths(const std::vector<uint64_t> &pairs, int stride) {
+    if (pairs.size() < 16) return 2 * stride;
+    constexpr size_t kCounts = 256;
+    size_t on[kCounts + 1] = {};              // paths whose window is on i paths (the last: or more)
+    for (size_t i = 0, end; i < pairs.size(); i = end) {
+        for (end = i + 1; end < pairs.size() && (pairs[end] >> 32) == (pairs[i] >> 32); ++end) {
+        }
+        on[std::min(end - i, kCounts)] += end - i;
+    }
+    size_t typical = 0, below = 0;            // half of all paths are on windows of at most this many
+    while (2 * below < pairs.size()) below += on[++typical];
+    size_t crowded = 0;
+    for (size_t c = std::max<size_t>(size_t(stride), 3 * typical) + 1; c <= kCounts; ++c) crowded += on[c];
+    if (typical >= size_t(stride + 2) || 100 * crowded > pairs.size()) return 0;
+    return int32_t(std::max<size_t>(2 * size_t(stride), 3 * typical));
+}
+
+// Replaces the pairs of every window on more than `most` paths by one for each of
+// its positions, kSharedWindow and the position in the state's place: the walk
+// from there starts at the root.
+constexpr uint32_t kSharedWindow = 0x80000000u;
+void share_windows(std::vector<uint64_t> &pairs, int32_t most, const std::vector<int32_t> &depth) {
+    size_t to = 0;
+    for (size_t i = 0, end; i < pairs.size(); i = end) {
+        uint32_t positions = 0;
+        for (end = i; end < pairs.size() && (pairs[end] >> 32) == (pairs[i] >> 32); ++end)
+            positions |= 1u << (depth[size_t(uint32_t(pairs[end]))] - 4);
+        const uint64_t window = pairs[i] >> 32 << 32;
+        if (end - i > size_t(most)) {
+            for (uint32_t j = 1; j <= 4; ++j)
+                if (positions >> j & 1) pairs[to++] = window | kSharedWindow | j;
+        } else {
+            for (size_t k = i; k < end; ++k) pairs[to++] = pairs[k];
+        }
+    }
+    pairs.resize(to);
+}
+
 // Builds the exact window table of one stride from (window, state) pairs
 // sorted by window; entry_of(state) gives the state's entry without its link.
 // A table that would need more than max_entries entries is left empty: false.
@@ -560,8 +613,9 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
     // stride + 4 bytes), so the path down to it is compared as a whole: with
     // its keyword, when the rest is forced down to a leaf with one keyword
     // (and none ends on the way), else down to the state, where a walk goes on.
-    const bool table2 = P.pair2 && (P.n_quads2 <= kPair2Keys || P.n_windows2 <= kStride2Keys);
-    const bool table4 = P.pair4 && P.n_quads4 <= kPair4SmallKeys;
+    const int32_t most2 = most_paths(quads2, 2), most4 = most_paths(quads4, 4);
+    const bool table2 = P.pair2 && (P.n_quads2 <= kPair2Keys || P.n_windows2 <= kStride2Keys) && most2 > 0;
+    const bool table4 = P.pair4 && P.n_quads4 <= kPair4SmallKeys && most4 > 0;
     std::vector<WindowEntry> entry;           // of the states from at_depth[5] on, in their order
     for (int32_t s = at_depth[5]; s < at_depth[table4 ? 9 : 7] && (table2 || table4); ++s) {
         const int32_t d = P.depth[size_t(s)], l = P.tail[size_t(s)];
@@ -574,9 +628,18 @@ int compile_plan(const uint8_t *bytes, const int64_t *offsets, int32_t n,
         }
         entry.push_back(e);
     }
-    auto entry_of = [&](int32_t s) { return entry[size_t(s - at_depth[5])]; };
-    if (table2) build_windows(quads2, entry_of, P.win[window_set(2)]);
-    if (table4) build_windows(quads4, entry_of, P.win[window_set(4)]);
+    auto entry_of = [&](int32_t s) {
+        if (s < 0) return WindowEntry{0, 0, 0, (uint32_t(s) & ~kSharedWindow) | kWinGeneral};
+        return entry[size_t(s - at_depth[5])];
+    };
+    if (table2) {
+        share_windows(quads2, most2, P.depth);
+        build_windows(quads2, entry_of, P.win[window_set(2)]);
+    }
+    if (table4) {
+        share_windows(quads4, most4, P.depth);
+        build_windows(quads4, entry_of, P.win[window_set(4)]);
+    }
     // keyword bytes (for tail comparisons) with int32 offsets
     P.kw_bytes.assign(bytes + offsets[0], bytes + offsets[0] + total);
     P.kw_off.resize(size_t(n) + 1);
