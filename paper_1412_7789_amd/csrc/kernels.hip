@@ -253,14 +253,20 @@ void resolve_launch(const ac_automaton *a, int64_t len, bool batch, ac_launch &c
         // KiB 8.8 with one, 9.6 with two, 2 MiB 9.7 and 9.5, 3 MiB 10.6 and
         // 9.8, 4 MiB 11.5 and 10.2; 50000 keywords, 2 MiB 8.9 and 9.5; 200 short
         // keywords at stride 1, 1 MiB 10.2 and 11.6, 2 MiB 10.6 and 11.4, 3 MiB
-        // 11.4 and 11.6, 4 MiB 12.3 and 11.9.  Four for the 4-byte-window map at
+        // 11.4 and 11.6, 4 MiB 12.3 and 11.9.  Without a window table two only
+        // from 8 MiB, where every wave has a step with either: many candidates
+        // keep a wave busy and fill its records, so half of the waves cannot be
+        // left idle (calls, 63 keywords of 4 to 6 letters of ACGT, 4 MiB 73 and
+        // 507, 6 MiB 515 and 730, 8 MiB 956 and 953; 500 short words in prose, 4
+        // MiB 47 and 66, 6 MiB 66 both).  Four for the 4-byte-window map at
         // stride 2 on texts of 256 MiB and more, where they halve the per-step
         // work of a filter-bound loop (20000 byte keywords: 256 MiB 55.2 with
         // four, 57.0 with two, 1 GiB 184 and 193; 50000: 192 MiB 60.4 and 60.2,
         // 256 MiB 77.4 both, 1 GiB 277 and 285); with the 4-byte-window map at
         // stride 4 four are slower (1000 keywords, 1 GiB: 171 and 166).
         if (cfg.segs != 1 && cfg.segs != 2 && cfg.segs != 4) {
-            cfg.segs = len < (int64_t(3) << 20) ? 1 : 2;
+            const bool win = cfg.stride > 1 && P.win[window_set(cfg.stride)].bits > 0;
+            cfg.segs = len < (int64_t(win ? 3 : 8) << 20) ? 1 : 2;
             if (cfg.filter == AC_FILTER_PAIR20 && cfg.stride == 2 && len >= (int64_t(256) << 20)) cfg.segs = 4;
         }
         const int64_t fit = std::max<int64_t>(1, a->lds_per_cu / filtered_lds(g));

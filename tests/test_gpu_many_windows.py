@@ -53,3 +53,22 @@ def test_large_sets_at_every_stride_and_map(shortest, strides):
             cfg = pf.launch_config(policy=1, filter=6, stride=stride, segs=segs, block=256)
             off, pid = a.match(d, launch=cfg, capacity=len(exp[0]) + 8)
             assert_same((off.cpu().numpy(), pid.cpu().numpy()), exp, f"run, stride {stride} segs {segs}")
+
+
+def test_two_segments_need_eight_mebibytes_without_a_window_table():
+    """Two segments per step from 3 MiB on leave waves without one; where every
+    offset may be a candidate (no window table) they wait for 8 MiB."""
+    import paper_1412_7789_amd as pf
+    assert torch.cuda.is_available()
+    rng = np.random.default_rng(5)
+    acgt = np.frombuffer(b"ACGT", dtype=np.uint8)
+    text = acgt[rng.integers(0, 4, size=(8 << 20) + 5)]
+    short = sorted({bytes(acgt[rng.integers(0, 4, size=int(n))]) for n in rng.integers(4, 7, size=20)})
+    long = sorted({bytes(rng.integers(0, 256, size=12, dtype=np.uint8)) for _ in range(500)})
+    for kws, at in ((long, 3 << 20), (short, 8 << 20)):
+        a = pf.Automaton(kws)
+        assert [a.default_launch(n)["segs"] for n in (1 << 20, at - 1, at, 64 << 20)] == [1, 1, 2, 2]
+    d, o = torch.from_numpy(text).cuda(), Oracle(short)
+    for n in ((3 << 20) + 1, (8 << 20) - 1, len(text)):
+        off, pid = a.match(d[:n])
+        assert_same((off.cpu().numpy(), pid.cpu().numpy()), o.match(text[:n]), f"{n} bytes")
