@@ -1159,7 +1159,10 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
         // What is left of the wave's slots: cur first, with what its queueing
         // left (its text is read again), then its successors, one segment at a
         // time, since a segment's registers stay live while the walks of a
-        // full queue run.
+        // full queue run.  A queue is drained when it is full and at the very
+        // end, so that a wave's matches share their atomics (18 keywords of 3
+        // letters, 128 MiB of ACGT, 37.8 million matches: 7129 us a call; drained
+        // at every segment's end 8734).
         auto full = [](int) __attribute__((always_inline)) { return false; };
         uint32_t sl = cur;
         bool ok = cur_ok, first = true;
@@ -1181,7 +1184,7 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 }
                 while (true) {
                     if (!queued) queued = queue_mask(m, r1, d4, j0, (sl << 12) + uint32_t(j * kSegBytes), full);
-                    while (qlen > 0) drain_walk(imin(qlen, kDrain));
+                    while (qlen >= kDrain || (!ok && qlen > 0)) drain_walk(imin(qlen, kDrain));
                     if (queued) break;
                 }
             }
