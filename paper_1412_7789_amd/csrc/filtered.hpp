@@ -179,6 +179,23 @@ __device__ __forceinline__ void emit_one(const ScanArgs &S, MatchStage *st, uint
     count_text(S, lcnt, tid);
 }
 
+// Called by every thread of the block: writes the staged matches out with one
+// atomic, and empties the stage.
+__device__ __forceinline__ void write_stage(const ScanArgs &S, MatchStage *st) {
+    __syncthreads();
+    const int32_t n = imin(st->n, kStageCap);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        st->base = n ? atomicAdd(S.count, static_cast<unsigned long long>(n)) - S.count_base : 0ull;
+        st->n = 0;
+    }
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < n; i += blockDim.x) {
+        const unsigned long long idx = st->base + unsigned(i);
+        put_out(S, idx, st->off[i], st->tid[i], st->pid[i]);
+    }
+}
+
 // Called by every thread of the block once all its walks are done.
 __device__ __forceinline__ void flush_stage(const ScanArgs &S, MatchStage *st, const uint32_t *lcnt) {
     __syncthreads();
@@ -1226,7 +1243,29 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
                 emit_one(S, nullptr, nullptr, o, 0, pid);
             }
         };
-        for (int i = int(lane); i < hcount; i += kWave) {
+        // Writes the staged matches out with one atomic, when there may be no room
+        // for one of each of the next `left` records.  Called by the whole wave.
+        // (A match past the stage's room takes an atomic with the lanes that
+        // reach theirs in the same step, few of them where windows lie at
+        // different positions: 1.28 million matches in 128 MiB of log lines, 850
+        // us a call without this, 211 with it.  More would not pay: atomics on
+        // one address pass at about 85 M/s.)
+        auto flush = [&](int left) __attribute__((always_inline)) {
+            wave_sync();
+            const int n = imin(__builtin_amdgcn_readfirstlane(int(q[0])), kWaveStageCap);
+            if (left <= 0 || n + imin(left, kWave) <= kWaveStageCap) return;
+            unsigned long long base = 0;
+            if (lane == 0) base = atomicAdd(S.count, static_cast<unsigned long long>(n)) - S.count_base;
+            base = readlane64(base, 0);
+            for (int i = int(lane); i < n; i += kWave)
+                put_out(S, base + unsigned(i), offset_of(q[2 + 2 * i]), 0, int32_t(q[3 + 2 * i]));
+            wave_sync();
+            if (lane == 0) q[0] = 0u;
+            wave_sync();
+        };
+        for (int i0 = 0; i0 < hcount; i0 += kWave, flush(hcount - i0)) {
+            const int i = i0 + int(lane);
+            if (i >= hcount) continue;
             uint2 rec;
             if (i < kLdsHits) rec = shits[wave * kLdsHits + i];
             else rec = gload8(hits + (i - kLdsHits));
@@ -1328,7 +1367,17 @@ __global__ __launch_bounds__(1024) void filtered_kernel(const KArgs) {
             loff = lds_off;
         }
         __syncthreads();
-        for (int32_t i = int32_t(threadIdx.x); i < total; i += int32_t(blockDim.x)) {
+        // With more hits than the stage has room for, it is written out whenever
+        // there may be no room for another of each thread (the log lines above
+        // as a batch of 32 texts: 540 -> 147 us).
+        for (int32_t i0 = 0; i0 < total; i0 += int32_t(blockDim.x)) {
+            if (total > kStageCap) {
+                __syncthreads();
+                if (st->n > kStageCap - int32_t(blockDim.x)) write_stage(S, st);
+                __syncthreads();
+            }
+            const int32_t i = i0 + int32_t(threadIdx.x);
+            if (i >= total) continue;
             int j = 0;                               // wave (region) of flat index i
 #pragma unroll
             for (int h = kMaxWaves / 2; h >= 1; h >>= 1)
