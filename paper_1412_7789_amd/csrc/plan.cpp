@@ -114,15 +114,19 @@ void sort_by_window(std::vector<uint64_t> &w) {
 // prose-like words: 2000 words 848 and 299, 200 words 135 and 120).  With
 // fewer, those windows alone are shared (32 MiB of log lines, 5000 keywords and
 // 40 more with one middle: 77 us with chains, 39 shared).  Sets of a few
-// keywords have too few paths to tell.
+// keywords have too few paths to tell: their windows may be on 2 * stride.
 int32_t most_paths(const std::vector<uint64_t> &pairs, int stride) {
-    if (pairs.size() < 16) return 2 * stride;
     constexpr size_t kCounts = 256;
     size_t on[kCounts + 1] = {};              // paths whose window is on i paths (the last: or more)
     for (size_t i = 0, end; i < pairs.size(); i = end) {
         for (end = i + 1; end < pairs.size() && (pairs[end] >> 32) == (pairs[i] >> 32); ++end) {
         }
         on[std::min(end - i, kCounts)] += end - i;
+    }
+    if (pairs.size() < 16) {
+        for (size_t c = 2 * size_t(stride) + 1; c < 16; ++c)
+            if (on[c]) return 0;
+        return 2 * stride;
     }
     size_t typical = 0, below = 0;            // half of all paths are on windows of at most this many
     while (2 * below < pairs.size()) below += on[++typical];

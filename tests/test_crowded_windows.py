@@ -118,3 +118,11 @@ def test_matches_with_crowded_windows(kind):
                 part = text[start:start + n]
                 off, pid = a.match(buf[16 + start:16 + start + n], launch=launch, capacity=8 * n)
                 assert_same((off.cpu().numpy(), pid.cpu().numpy()), o.match(part), f"{kind} {cfg} {start}+{n}")
+
+
+def test_a_few_keywords_in_one_window():
+    """Sets of under 16 paths keep their tables while no window lies on more than
+    2 * stride of them."""
+    few = [b"aaaaaaaa", b"aaaaaaaab", b"baaaaaaaa"]                       # "aaaa": 8 paths, 4 at stride 2
+    assert [len(k) > 0 for k, _ in tables(few)] == [True, True]
+    assert [len(k) > 0 for k, _ in tables(few + [b"aaabaaaa"])] == [True, False]   # 9 paths at stride 4

@@ -119,3 +119,26 @@ def test_text_ending_in_each_segment():
             off, pid = a.match(t[:n], launch=cfg, capacity=len(off_all))
             keep = end_all <= n
             assert_same((off.cpu().numpy(), pid.cpu().numpy()), (off_all[keep], pid_all[keep]), f"{n} segs {segs}")
+
+
+@pytest.mark.parametrize("stride,segs", [(4, 1), (4, 2), (4, 4), (2, 2)])
+def test_more_hits_than_records_with_chained_windows(stride, segs):
+    """The same with windows that lie on several keywords' paths, which keep one
+    entry for each."""
+    from paper_1412_7789_amd import _lib as L
+    kws = [b"aaaaaaab", b"aaaaaaaaaab", b"aaaaaaaaab", b"baaaaaaab"]
+    table = L.AC_TABLE_WINDOW4_KEYS if stride == 4 else L.AC_TABLE_WINDOW2_KEYS
+    assert len(pf.Plan(kws).export(table, np.uint32)) > 0
+    waves = WAVES * torch.cuda.get_device_properties(0).multi_processor_count
+    n = 2 * waves * RECORDS * stride + 1533
+    text = make_text(n, segs)
+    exp = oracle_match(kws, text)
+    cuts = np.array([0, n // 3, n // 3 + 1, n // 2, n], dtype=np.int64)
+    want = [oracle_match(kws, text[s:e]) for s, e in zip(cuts[:-1], cuts[1:])]
+    a, t = pf.Automaton(kws), torch.from_numpy(text).cuda()
+    cfg = pf.launch_config(policy=1, filter=6, stride=stride, segs=segs, block=256)
+    off, pid = a.match(t, launch=cfg, capacity=len(exp[0]))
+    assert_same((off.cpu().numpy(), pid.cpu().numpy()), exp, "single")
+    tid, off, pid, per = (x.cpu().numpy() for x in a.match_batch(t, torch.from_numpy(cuts).cuda(), launch=cfg))
+    for k, w in enumerate(want):
+        assert_same((off[tid == k], pid[tid == k]), w, f"text {k}")
