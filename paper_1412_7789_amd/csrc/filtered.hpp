@@ -139,17 +139,29 @@ struct MatchStage {
 };
 
 // One more match of text tid: in the block's LDS counters when it has them,
-// else in global memory.
+// else in global memory.  A counter that wraps hands its 2^32 on.
 __device__ __forceinline__ void count_text(const ScanArgs &S, uint32_t *lcnt, int32_t tid) {
-    if (lcnt) atomicAdd(&lcnt[tid], 1u);
-    else if (S.per_text) atomicAdd(reinterpret_cast<unsigned long long *>(S.per_text + tid), 1ull);
+    if (!S.per_text) return;
+    unsigned long long more = 1ull;
+    if (lcnt) {
+        if (atomicAdd(&lcnt[tid], 1u) != ~0u) return;
+        more = 1ull << 32;
+    }
+    atomicAdd(reinterpret_cast<unsigned long long *>(S.per_text + tid), more);
+}
+
+// A place in the block's stage for one match, kStageCap or more when it is full.
+// A full stage's count is left alone: states may have any number of ids.
+__device__ __forceinline__ int32_t stage_place(MatchStage *st) {
+    if (__hip_atomic_load(&st->n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= kStageCap) return kStageCap;
+    return atomicAdd(&st->n, 1);
 }
 
 __device__ __forceinline__ void emit_staged(const DevAut &A, const ScanArgs &S, MatchStage *st, uint32_t *lcnt,
                                             int64_t off, int32_t tid, int32_t s) {
     const int32_t k0 = A.out_off[s], k1 = A.out_off[s + 1];
     for (int32_t k = k0; k < k1; ++k) {
-        const int32_t i = atomicAdd(&st->n, 1);
+        const int32_t i = stage_place(st);
         if (i < kStageCap) {
             st->off[i] = off;
             st->pid[i] = A.out_pid[k];
@@ -167,7 +179,7 @@ __device__ __forceinline__ void emit_staged(const DevAut &A, const ScanArgs &S, 
 __device__ __forceinline__ void emit_one(const ScanArgs &S, MatchStage *st, uint32_t *lcnt, int64_t off, int32_t tid,
                                          int32_t pid) {
     int32_t i = kStageCap;
-    if (st) i = atomicAdd(&st->n, 1);
+    if (st) i = stage_place(st);
     if (i < kStageCap) {
         st->off[i] = off;
         st->pid[i] = pid;

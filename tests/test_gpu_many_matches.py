@@ -77,3 +77,17 @@ def test_around_the_blocks_stage(pf, kind, per_text):
         tid, off, pid = (x[:total].cpu().numpy() for x in (tid, off, pid))
         for k, w in enumerate(want):
             assert_same((off[tid == k], pid[tid == k]), w, f"{kind} {m} text {k}")
+
+
+def test_more_matches_of_one_text_than_32_bits_count(pf):
+    """A million keyword ids at each of 4400 offsets, all in one block: the
+    text's count is exact past 2^32 (the other texts have none)."""
+    n_ids, n = 1_000_000, 4400
+    a = pf.Automaton([b"a"] * n_ids)
+    t = torch.full((n,), ord("a"), dtype=torch.uint8, device="cuda")
+    c = torch.tensor([0, 0, n, n], dtype=torch.int64, device="cuda")
+    none32 = torch.empty(0, dtype=torch.int32, device="cuda")
+    none64 = torch.empty(0, dtype=torch.int64, device="cuda")
+    per = torch.full((3,), -1, dtype=torch.int64, device="cuda")
+    assert a.match_batch_into(t, c, none32, none64, none32, per_text=per) == n * n_ids
+    assert per.tolist() == [0, n * n_ids, 0]
