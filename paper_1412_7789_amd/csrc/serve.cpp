@@ -146,17 +146,21 @@ int host_alloc(T **p, int64_t n) {
                            : report_error(AC_ENOMEM, std::string("server hipHostMalloc: ") + hipGetErrorString(e));
 }
 
+// A buffer whose allocation fails is gone, and so is its capacity.
 int grow(Slot &s, int64_t text_bytes, int64_t texts, int64_t matches) {
     int rc = AC_OK;
     if (text_bytes > s.text_cap) {
+        s.text_cap = 0;
         if ((rc = dev_alloc(&s.d_text, text_bytes))) return rc;
         s.text_cap = text_bytes;
     }
     if (texts > s.texts_cap) {
+        s.texts_cap = 0;
         if ((rc = dev_alloc(&s.d_offs, texts + 1)) || (rc = host_alloc(&s.h_offs, texts + 1))) return rc;
         s.texts_cap = texts;
     }
     if (matches > s.match_cap) {
+        s.match_cap = 0;
         if ((rc = host_alloc(&s.h_tid, matches)) || (rc = host_alloc(&s.h_off, matches)) ||
             (rc = host_alloc(&s.h_pid, matches)))
             return rc;

@@ -15,6 +15,7 @@ PRELUDE = r"""
 #include "plan.cpp"
 #include "host_match.cpp"
 #include "capi.cpp"
+#include "serve.cpp"
 #include <cstdio>
 
 namespace pfac {
@@ -34,7 +35,14 @@ int launch_zero(unsigned long long *count, unsigned long long *words, int64_t *p
 int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &, const HitScratch &, hipStream_t,
                 std::string &, const KernelTiming *) {
     if (S.n <= 0) return AC_OK;
-    const int64_t n = host_match(a->host, S.text, S.n, nullptr, nullptr, 0, 1);
+    int64_t n = 0;
+    for (int32_t t = 0; t < (S.text_off ? S.n_texts : 1); ++t) {
+        const int64_t at = S.text_off ? S.text_off[t] : 0, end = S.text_off ? S.text_off[t + 1] : S.n;
+        const int64_t room = std::max<int64_t>(0, S.cap - n);
+        const int64_t m = host_match(a->host, S.text + at, end - at, S.out_off + n, S.out_pid + n, room, 1);
+        for (int64_t i = n; S.out_tid && i < std::min(n + m, S.cap); ++i) S.out_tid[i] = t;
+        n += m;
+    }
     *S.count += uint64_t(n);
     if (S.done && S.done[0] != 0) return AC_OK;      // counts of another scan: no block is the last
     if (S.dev_count) { *S.dev_count = *S.count; *S.count = 0; }
@@ -91,6 +99,49 @@ int main() {
     CHECK(ac_match(a, kText, kLen, nullptr, nullptr) == 3);
     CHECK(ac_match_async(a, kText, kLen, nullptr, nullptr, &count, nullptr) == AC_OK && count == 3);
     CHECK(ac_match(a, kText, kLen, nullptr, nullptr) == 3);
+    ac_free(a);
+    return 0;
+}
+""")
+
+
+def test_server_goes_on_after_a_failed_allocation(tmp_path):
+    """A request whose buffers cannot be allocated fails with AC_ENOMEM; the
+    stream's buffers that were given up for it are allocated again for the next
+    one: the text's, and each of the match arrays' (a re-scan that needs more)."""
+    run(tmp_path, r"""
+int main() {
+    ac_automaton *a = make();
+    CHECK(a);
+    ac_server_opts o{};
+    o.n_streams = 1;
+    o.max_batch_bytes = 4096;
+    o.max_batch_texts = 4;
+    o.matches_per_kib = 1;
+    ac_server *s = nullptr;
+    CHECK(ac_server_create(&o, &s) == AC_OK);
+    CHECK(ac_server_add_automaton(s, a) == 0);
+    std::vector<uint8_t> text;
+    ac_request_result r{};
+    auto serve = [&](int64_t len) {
+        const int64_t id = ac_server_submit(s, 0, text.data(), len);
+        return id < 0 ? int(id) : ac_server_wait(s, id, &r);
+    };
+    text.assign(1 << 20, '.');
+    std::memcpy(text.data(), "abcdefgh", 8);
+    fake::fail_in = 0;
+    CHECK(serve(1 << 20) == AC_ENOMEM);
+    CHECK(serve(1000) == AC_OK && r.count == 1 && r.offset[0] == 0);
+    CHECK(serve(1 << 20) == AC_OK && r.count == 1);
+    for (size_t at = 0; at < text.size(); at += 8) std::memcpy(text.data() + at, "abcdefgh", 8);
+    for (int array = 0; array < 3; ++array) {
+        const int64_t len = int64_t(1) << (15 + array);
+        fake::fail_in = array;
+        CHECK(serve(len) == AC_ENOMEM);
+        CHECK(serve(800) == AC_OK && r.count == 100 && r.pattern_id[99] == 0);
+        CHECK(serve(len) == AC_OK && r.count == len / 8);
+    }
+    ac_server_destroy(s);
     ac_free(a);
     return 0;
 }
