@@ -14,12 +14,15 @@
  *   AC_SERVE_FIFO     the plain way: one stream, one launch per request, in
  *                     arrival order.
  *
- * Admission: every request is charged its text bytes plus its match buffer
- * (16 bytes per reserved match) against hbm_budget_bytes, after the
- * registered automata's device bytes and the server's own device buffers
- * (per stream: the scan's scratch and text and match buffers sized for
- * max_batch_bytes; they grow, and are charged more, if a single request is
- * larger; ac_server_stats.resident_bytes reports them).  The oldest waiting
+ * Admission: every request is charged its text bytes plus 16 bytes per
+ * reserved match against hbm_budget_bytes, after the registered automata's
+ * device bytes and the server's own device buffers (per stream: the scan's
+ * scratch and a text buffer sized for max_batch_bytes; they grow, and are
+ * charged more, if a single request is larger; ac_server_stats.resident_bytes
+ * reports them).  The matches themselves are written to pinned host memory, 16
+ * bytes for each match slot of a full batch per stream (about 32 MB by
+ * default, more after a re-scan), which the budget does not count; their charge
+ * bounds the matches in flight.  The oldest waiting
  * request is always served first (no overtaking across automata); when its
  * charge does not fit the budget left by the batches in flight it waits
  * ("admission wait").

@@ -247,7 +247,6 @@ int upload(ac_automaton *a) {
     D.ptab_bits = P.ptab_bits;
     D.C = P.C;
     D.S_dense = P.S_dense;
-    D.K = P.K;
     D.hash_mul = P.hash_mul;
     return AC_OK;
 }
@@ -731,8 +730,9 @@ int ac_match_async_noalloc(const ac_automaton *a, const uint8_t *d_text, int64_t
         const int64_t cap = std::min<int64_t>(kHitCap, kStaticScratchBytes / int64_t(sizeof(uint4)) / regions);
         if (cap < kNoallocMinCap)
             return fail(AC_EINVAL, "ac_match_async_noalloc: the launch needs " + std::to_string(regions) +
-                                       " hit regions of at least " + std::to_string(kNoallocMinCap) +
-                                       " records; the static scratch holds " +
+                                       " hit regions of at least " +
+                                       std::to_string(kNoallocMinCap * int64_t(sizeof(uint4))) +
+                                       " bytes; the static scratch holds " +
                                        std::to_string(kStaticScratchBytes) + " bytes");
         hs.regions = regions;
         hs.cap = int32_t(cap);

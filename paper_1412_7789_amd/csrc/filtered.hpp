@@ -34,7 +34,6 @@ constexpr int kWaveStageCap = (kQueueCap - 4) / 2;
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 
 __device__ __forceinline__ int64_t lmin(int64_t a, int64_t b) { return a < b ? a : b; }
-__device__ __forceinline__ int64_t lmax(int64_t a, int64_t b) { return a > b ? a : b; }
 
 __device__ __forceinline__ unsigned lane_id() {
     return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
@@ -352,13 +351,13 @@ __device__ __forceinline__ uint32_t diff16(u32x4 a, u32x4 b, int n) {
     return d;
 }
 
-// Whether text t[0 .. n) equals keyword bytes k[0 .. n) (n <= 64; text[0 ..
-// text_n) is the scanned buffer, which holds t[0 .. n)).  The first 32 bytes
-// of both are loaded in one round trip, as 16-byte loads of any alignment;
-// longer tails take more.  Text bytes within 16 of the buffer's end come
-// from clamped dword loads instead.  Keyword bytes may be read up to 79
-// bytes past a keyword: the keyword section is followed by at least 256
-// bytes of the same allocation.
+// Whether text t[0 .. n) equals keyword bytes k[0 .. n) (text[0 .. text_n) is
+// the scanned buffer, which holds t[0 .. n)).  The first 32 bytes of both are
+// loaded in one round trip, as 16-byte loads of any alignment; longer tails take
+// more.  Text bytes within 16 of the buffer's end come from clamped dword loads
+// instead.  Keyword bytes may be read up to 32 bytes past a keyword's compared
+// part: the keyword section is followed by at least 256 bytes of the same
+// allocation.
 __device__ __forceinline__ bool equal_bytes(const uint8_t *t, const uint8_t *k, int n, const uint8_t *text,
                                             int64_t text_n) {
     const uintptr_t tend = reinterpret_cast<uintptr_t>(text) + uintptr_t(text_n);

@@ -169,7 +169,7 @@ struct DevAut {
     const uint32_t *ptab;          // exact prefix table (global copy)
     const int4 *tailinfo;
     const uint8_t *kw_bytes;
-    int32_t C, S_dense, K;
+    int32_t C, S_dense;
     int32_t ptab_bits;
     uint32_t hash_mul;
 };
