@@ -126,3 +126,31 @@ def test_a_few_keywords_in_one_window():
     few = [b"aaaaaaaa", b"aaaaaaaab", b"baaaaaaaa"]                       # "aaaa": 8 paths, 4 at stride 2
     assert [len(k) > 0 for k, _ in tables(few)] == [True, True]
     assert [len(k) > 0 for k, _ in tables(few + [b"aaabaaaa"])] == [True, False]   # 9 paths at stride 4
+
+
+@pytest.mark.gpu
+def test_crowded_windows_of_zeros_at_the_texts_end():
+    """What lies past a text's end reads as zeros: keywords crowded in a window of
+    zeros, in texts that end before, inside and after one."""
+    import torch
+    assert torch.cuda.is_available()
+    rng = np.random.default_rng(23)
+    kws = [bytes(rng.integers(1, 256, size=int(n), dtype=np.uint8)) for n in rng.integers(8, 40, size=5000)]
+    kws += [bytes([c]) + bytes(7) + bytes([d]) for c in range(1, 21) for d in (0, 1)]
+    assert all(len(keys) for keys, _ in tables(kws))
+    a, o = pf.Automaton(kws), Oracle(kws)
+    text = np.concatenate([rng.integers(0, 21, size=2000, dtype=np.uint8)] +
+                          [np.frombuffer(kws[5000 + i] + bytes(i % 5), dtype=np.uint8) for i in range(40)])
+    buf = torch.zeros(len(text) + 64, dtype=torch.uint8, device="cuda")
+    buf[16:16 + len(text)] = torch.from_numpy(text).cuda()
+    for stride, segs in ((0, 0), (4, 1), (4, 4), (2, 2)):
+        launch = pf.launch_config(policy=1, stride=stride, segs=segs)
+        for n in range(len(text) - 70, len(text) + 1):
+            for start in (0, 5):
+                off, pid = a.match(buf[16 + start:16 + n], launch=launch, capacity=200)
+                assert_same((off.cpu().numpy(), pid.cpu().numpy()), o.match(text[start:n]), f"{stride} {segs} {start} {n}")
+        cuts = np.concatenate([[0], np.arange(len(text) - 300, len(text) + 1, 3), [len(text)]]).astype(np.int64)
+        tid, off, pid, per = (x.cpu().numpy() for x in a.match_batch(
+            buf[16:16 + len(text)], torch.from_numpy(cuts).cuda(), launch=launch))
+        for t in range(len(cuts) - 1):
+            assert_same((off[tid == t], pid[tid == t]), o.match(text[cuts[t]:cuts[t + 1]]), f"{stride} {segs} text {t}")
