@@ -56,10 +56,13 @@ struct CountSlot {
     int64_t *d_off = nullptr;
     int32_t *d_pid = nullptr;
     int64_t match_cap = 0;
-    // and the pinned arrays the scan writes its first kNearMatches matches to
+    // and the pinned arrays the scan writes its first kNearMatches matches to:
+    // every entry is kAbsent between calls (take_near)
     int64_t *h_off = nullptr;
     int32_t *h_pid = nullptr;
+    bool near_clean = false;                   // false: a failed call may have left matches there
 };
+constexpr int kAbsent = -1;                    // no offset and no keyword id
 constexpr int64_t kNearMatches = int64_t(1) << 16;
 std::mutex g_slots_mu;
 std::map<std::pair<int, hipStream_t>, CountSlot> g_slots;
@@ -95,6 +98,7 @@ int ensure_staging(CountSlot &s, int64_t text, int64_t matches) {
             (!s.h_pid && (e = hipHostMalloc(reinterpret_cast<void **>(&s.h_pid), size_t(kNearMatches) * 4,
                                             hipHostMallocCoherent)) != hipSuccess))
             return fail(AC_ENOMEM, std::string("hipHostMalloc(dispatch matches): ") + hipGetErrorString(e));
+        s.near_clean = false;
     }
     if (matches > kNearMatches && matches > s.match_cap) {
         if (s.d_off) (void)hipFree(s.d_off);
@@ -513,11 +517,47 @@ int64_t host_match_checked(const Plan &P, const uint8_t *text, int64_t len, int6
     }
 }
 
+// Takes n matches out of a pinned array, each once it is there, and leaves the
+// entries kAbsent for the next scan.  The kernel has stored them before it
+// reports their count, but stores to the host arrive in no particular order:
+// entries came later than the count in one of 3000 calls, also with stores at
+// system scope that were waited for.  Once the stream has finished they are all
+// in place.
+template <typename T>
+bool take_near(T *h, T *out, int64_t n, hipStream_t stream) {
+    constexpr int64_t kBlock = 512;
+    uint64_t spin = 0;
+    bool ended = false;
+    for (int64_t i0 = 0; i0 < n; i0 += kBlock) {
+        const int64_t m = std::min(kBlock, n - i0);
+        while (true) {
+            T any = 0;                         // negative when an entry is absent
+            for (int64_t i = 0; i < m; ++i) {
+                out[i0 + i] = h[i0 + i];
+                any |= out[i0 + i];
+            }
+            if (any >= 0) break;
+            if (ended) return false;
+#if defined(__x86_64__)
+            __builtin_ia32_pause();
+#endif
+            if (++spin % 4096 == 0) {
+                const hipError_t e = hipStreamQuery(stream);
+                if (e != hipSuccess && e != hipErrorNotReady) return false;
+                ended = e == hipSuccess;
+            }
+            __atomic_thread_fence(__ATOMIC_ACQUIRE);      // read them again
+        }
+        std::fill_n(h + i0, m, T(kAbsent));
+    }
+    return true;
+}
+
 // GPU side of the dispatch: host text -> device, scan, matches -> host.  The
-// scan writes the first kNearMatches matches straight into pinned memory, from
-// where the report finds them in place: two copies of a few hundred bytes and
-// a stream synchronisation after the scan took 27 to 32 us (64 matches of a
-// 256 KiB text: 59.7 -> 35.6 us per call, of a 16 KiB text 48.4 -> 18.6).  Only matches past them are copied.
+// scan writes the first kNearMatches matches straight into pinned memory: two
+// copies of a few hundred bytes and a stream synchronisation after the scan took
+// 27 to 32 us (64 matches of a 256 KiB text: 59.7 -> 35.6 us per call, of a 16
+// KiB text 48.4 -> 18.6).  Only matches past them are copied.
 int64_t gpu_round_trip(const ac_automaton *a, const uint8_t *text, int64_t len, int64_t *off, int32_t *pid,
                        int64_t cap, hipStream_t stream) {
     if (len == 0) return 0;
@@ -525,7 +565,15 @@ int64_t gpu_round_trip(const ac_automaton *a, const uint8_t *text, int64_t len, 
     int rc = slot_for(a, stream, &slot);
     if (rc) return rc;
     if ((rc = ensure_staging(*slot, len, std::max<int64_t>(cap, 1)))) return rc;
-    hipError_t e = hipMemcpyAsync(slot->d_text, text, size_t(len), hipMemcpyHostToDevice, stream);
+    hipError_t e = hipSuccess;
+    if (!slot->near_clean) {
+        // nothing of an earlier scan may still arrive
+        if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail("hipStreamSynchronize", e);
+        std::fill_n(slot->h_off, kNearMatches, int64_t(kAbsent));
+        std::fill_n(slot->h_pid, kNearMatches, int32_t(kAbsent));
+    }
+    slot->near_clean = false;
+    e = hipMemcpyAsync(slot->d_text, text, size_t(len), hipMemcpyHostToDevice, stream);
     if (e != hipSuccess) return hip_fail("hipMemcpyAsync(dispatch text)", e);
     ScanArgs S{};
     S.text = slot->d_text;
@@ -541,10 +589,9 @@ int64_t gpu_round_trip(const ac_automaton *a, const uint8_t *text, int64_t len, 
     const int64_t count = sync_count(a, S, nullptr, false, stream);
     if (count < 0) return count;
     const int64_t put = std::min(count, cap), near = std::min(put, kNearMatches);
-    if (near > 0) {
-        std::memcpy(off, slot->h_off, size_t(near) * 8);
-        std::memcpy(pid, slot->h_pid, size_t(near) * 4);
-    }
+    if (!take_near(slot->h_off, off, near, stream) || !take_near(slot->h_pid, pid, near, stream))
+        return fail(AC_EHIP, "scan finished without writing its matches");
+    slot->near_clean = true;
     if (put > near) {
         if ((e = hipMemcpyAsync(off + near, slot->d_off + near, size_t(put - near) * 8, hipMemcpyDeviceToHost, stream)) !=
                 hipSuccess ||

@@ -5,8 +5,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
+#include <thread>
 
 #define __align__(n) __attribute__((aligned(n)))
 #define HIP_SYMBOL(x) (x)
@@ -18,6 +22,21 @@ inline hipError_t alloc(void **p, size_t n) {
     if (refuse()) { *p = nullptr; return hipErrorOutOfMemory; }
     *p = std::malloc(n ? n : 1);
     return hipSuccess;
+}
+// Work that a stream still does after a call returned: the stream is busy until
+// it has run (`late` of 5: it never runs, and the stream is idle).
+inline int late = 0;
+inline std::thread worker;
+inline std::atomic<bool> busy{false};
+inline void join() { if (worker.joinable()) worker.join(); }
+inline void later(std::function<void()> work) {
+    join();
+    busy = true;
+    worker = std::thread([work] {
+        std::this_thread::sleep_for(std::chrono::milliseconds(3));
+        work();
+        busy = false;
+    });
 }
 }  // namespace fake
 
@@ -45,8 +64,8 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return fake::busy ? hipErrorNotReady : hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { fake::join(); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t *e) { *e = nullptr; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = nullptr; return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }

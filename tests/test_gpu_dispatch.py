@@ -94,3 +94,28 @@ def test_more_matches_than_the_pinned_arrays_hold(n):
         assert len(off) == n and (pid == 0).all()
         off = np.sort(off)
         assert off[0] >= 0 and off[-1] < n and (np.diff(off) > 0).all()
+
+
+def test_every_dispatched_call_returns_its_own_matches():
+    """Thousands of dispatched calls on texts with different matches in turn:
+    matches reach the pinned arrays in no particular order with the count that
+    reports them, and none of an earlier call may be returned."""
+    rng = np.random.default_rng(5)
+    letters = np.frombuffer(b"ACGT", dtype=np.uint8)
+    kws = sorted({bytes(letters[rng.integers(0, 4, size=int(n))]) for n in rng.integers(4, 9, size=30)})
+    a, o = pf.Automaton(kws), Oracle(kws)
+    a.dispatch_threshold = 0
+    texts = [letters[rng.integers(0, 4, size=n)] for n in (5000, 11997, 40000, 16000, 20000)]
+    exp = []
+    for t in texts:
+        off, pid = o.match(t)
+        order = np.lexsort((pid, off))
+        exp.append((off[order], pid[order]))
+    for call in range(12000):
+        t, (eo, ep) = texts[call % 5], exp[call % 5]
+        off, pid, ran = a.match_dispatch(t, capacity=len(eo))
+        order = np.lexsort((pid, off))
+        if not (np.array_equal(off[order], eo) and np.array_equal(pid[order], ep)):
+            assert_same((off, pid), (eo, ep), f"call {call}, {len(t)} bytes")
+        if call % 3000 == 0:
+            say("dispatched", call)

@@ -35,10 +35,30 @@ int launch_zero(unsigned long long *count, unsigned long long *words, int64_t *p
 int launch_scan(const ac_automaton *a, const ScanArgs &S, const ac_launch &, const HitScratch &, hipStream_t,
                 std::string &, const KernelTiming *) {
     if (S.n <= 0) return AC_OK;
+    if (S.near_cap > 0) {
+        // the pinned arrays' entries arrive at once, later, in part later, or never
+        std::vector<int64_t> off(size_t(S.near_cap));
+        std::vector<int32_t> pid(size_t(S.near_cap));
+        const int64_t n = std::min(S.near_cap, host_match(a->host, S.text, S.n, off.data(), pid.data(), S.near_cap, 1));
+        auto put = [=](int64_t i0, int64_t i1) {
+            for (int64_t i = i0; i < i1; ++i) {
+                __atomic_store_n(S.near_pid + i, pid[size_t(i)], __ATOMIC_RELAXED);
+                __atomic_store_n(S.near_off + i, off[size_t(i)], __ATOMIC_RELAXED);
+            }
+        };
+        switch (fake::late) {
+            case 0: put(0, n); break;
+            case 1: fake::later([=] { put(0, n); }); break;
+            case 2: put(0, n - 1); fake::later([=] { put(n - 1, n); }); break;
+            case 3: put(1, n); fake::later([=] { put(0, 1); }); break;
+            case 4: put(0, n / 2); fake::later([=] { put(n / 2, n); }); break;
+            default: put(0, n / 2);
+        }
+    }
     int64_t n = 0;
     for (int32_t t = 0; t < (S.text_off ? S.n_texts : 1); ++t) {
         const int64_t at = S.text_off ? S.text_off[t] : 0, end = S.text_off ? S.text_off[t + 1] : S.n;
-        const int64_t room = std::max<int64_t>(0, S.cap - n);
+        const int64_t room = S.near_cap > 0 ? 0 : std::max<int64_t>(0, S.cap - n);
         const int64_t m = host_match(a->host, S.text + at, end - at, S.out_off + n, S.out_pid + n, room, 1);
         for (int64_t i = n; S.out_tid && i < std::min(n + m, S.cap); ++i) S.out_tid[i] = t;
         n += m;
@@ -142,6 +162,38 @@ int main() {
         CHECK(serve(len) == AC_OK && r.count == len / 8);
     }
     ac_server_destroy(s);
+    ac_free(a);
+    return 0;
+}
+""")
+
+
+def test_matches_that_arrive_after_their_count(tmp_path):
+    """A kernel's stores to pinned memory may reach the host after the count that
+    reports them.  A dispatched call waits for each entry, whether the last ones
+    come late or the first, and never returns what an earlier call left; if the
+    stream ends without them the call fails, and the next one works."""
+    run(tmp_path, r"""
+int main() {
+    ac_automaton *a = make();
+    CHECK(a);
+    ac_set_dispatch_threshold(a, 0);
+    std::vector<uint8_t> text(60000, '.');
+    std::vector<int64_t> off(8000);
+    std::vector<int32_t> pid(8000);
+    auto call = [&] { return ac_match_dispatch(a, text.data(), int64_t(text.size()), off.data(), pid.data(), 8000, nullptr, nullptr); };
+    for (int round = 0; round < 12; ++round) {
+        // round + 1 bytes between the matches, so every round has other ones
+        std::fill(text.begin(), text.end(), '.');
+        int64_t n = 0;
+        for (size_t at = 0; at + 8 <= text.size(); at += size_t(9 + round), ++n) std::memcpy(text.data() + at, "abcdefgh", 8);
+        fake::late = round % 6;
+        const int64_t count = call();
+        CHECK(fake::late == 5 ? count == AC_EHIP : count == n);
+        fake::join();
+        if (count < 0) continue;
+        for (int64_t i = 0; i < n; ++i) CHECK(off[size_t(i)] == i * (9 + round) && pid[size_t(i)] == 0);
+    }
     ac_free(a);
     return 0;
 }
